@@ -8,8 +8,12 @@
 // So each voxel costs k integer compares; on the vector path two voxels
 // share each operation (packed 16-bit arithmetic).  One-shot grid over tiles
 // of the flattened batch; 16-byte loads of 8 voxels and 8-byte stores of 8
-// labels where the input and output phases agree, element-wise code
-// elsewhere.
+// labels at any alignment.
+//
+// Bound by HBM: 2 B read and NS B written per voxel.  300 slices, k = 2:
+// 512 x 512 with three sets 67 us (5.9 TB/s), with one 39 us; 511 x 511 (every
+// slice and output starts at another alignment) with three sets 65 us (6.0
+// TB/s; 221 us when such tiles went voxel by voxel), with one 41 us (49).
 #include <algorithm>
 
 #include "common.h"
@@ -28,32 +32,80 @@ __device__ __forceinline__ void wave_cuts(const LabelSets &sets, int s, int k, c
     static_assert(NS * KM <= 64, "one lane per (set, threshold)");
     const int lane = threadIdx.x & 63;
     const int u = lane / KM, j = lane % KM;
-    int c = 0x7fffffff;
-    if (u < NS && j < k) {
-        const int32_t *t = sets.thr[u] + (int64_t)s * k;
-        bool ok = true;
-        for (int i = 0; i < k; ++i) // the whole row must be a strictly ascending tuple in [0, L-2]
-            ok = ok && t[i] >= 0 && t[i] <= bm.L - 2 && (i == 0 || t[i] > t[i - 1]);
-        if (ok) {
-            const uint32_t W = (uint32_t)((int64_t)bm.hi - bm.lo + 1);
-            c = bm.lo + (int)(((uint32_t)(t[j] + 1) * W + (uint32_t)bm.L - 1) / (uint32_t)bm.L);
-        }
-    }
+    const int32_t *row = sets.thr[0];
+#pragma unroll
+    for (int u2 = 1; u2 < NS; ++u2)
+        row = u == u2 ? sets.thr[u2] : row;
+    // one load per lane, whatever k: the row's order is checked against the
+    // neighbour lane's value, so a tile waits for one round trip (with a loop
+    // over the row, which waited for k of them, two sets of four thresholds
+    // over 300 512 x 512 slices took 78 us instead of 55)
+    const bool have = u < NS && j < k;
+    const int t = have ? row[(int64_t)s * k + j] : 0;
+    const int before = __builtin_amdgcn_update_dpp(0, t, 0x138, 0xf, 0xf, false); // wave_shr:1
+    const bool good = !have || (t >= 0 && t <= bm.L - 2 && (j == 0 || t > before));
+    const unsigned long long bal = __ballot(good);
+    // the whole row must be a strictly ascending tuple in [0, L-2]
+    const bool ok = have && ((bal >> (u * KM)) & ((1ull << KM) - 1ull)) == (1ull << KM) - 1ull;
+    const uint32_t W = (uint32_t)((int64_t)bm.hi - bm.lo + 1);
+    const int c = ok ? bm.lo + (int)(((uint32_t)(t + 1) * W + (uint32_t)bm.L - 1) / (uint32_t)bm.L) : 0x7fffffff;
 #pragma unroll
     for (int u2 = 0; u2 < NS; ++u2) {
 #pragma unroll
-        for (int j2 = 0; j2 < KM; ++j2) // up to 64 values: vector registers beyond the 3-cut case
-            cuts[u2].c[j2] = KM <= 3 ? __builtin_amdgcn_readlane(c, KM * u2 + j2) : __shfl(c, KM * u2 + j2, 64);
+        for (int j2 = 0; j2 < KM; ++j2) // up to 64 values: vector registers beyond the 8-cut case
+            cuts[u2].c[j2] = KM <= 8 ? __builtin_amdgcn_readlane(c, KM * u2 + j2) : __shfl(c, KM * u2 + j2, 64);
     }
 }
 
+// The n <= blockDim * 8 * U voxels at src (one piece of one problem): 16-byte
+// loads of 8 voxels, every load of a thread in flight before the first is
+// used, 8-byte stores per set; the last n mod 8 voxel by voxel.  AL: src is
+// 16-byte and every dst 8-byte aligned (else any alignment).
+template <int NS, int U, int KM, bool AL>
+__device__ __forceinline__ void label_piece(const TS_GLOBAL int16_t *src, TS_GLOBAL uint8_t *const (&dst)[NS], int n,
+                                            const Cuts<KM> (&cuts)[NS])
+{
+    PCuts<KM> pc[NS];
+#pragma unroll
+    for (int u = 0; u < NS; ++u)
+        pc[u] = pack_cuts(cuts[u]);
+    const TS_GLOBAL v4i_any *vp = reinterpret_cast<const TS_GLOBAL v4i_any *>(src);
+    const int nvec = n >> 3;
+    v4i w[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        const int i = threadIdx.x + j * blockDim.x;
+        w[j] = i < nvec ? (v4i)__builtin_nontemporal_load(vp + i) : v4i{0, 0, 0, 0};
+    }
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        const int i = threadIdx.x + j * blockDim.x;
+        if (i < nvec) {
+#pragma unroll
+            for (int u = 0; u < NS; ++u)
+                store_lab8(dst[u], i, lab8(w[j], pc[u]), AL);
+        }
+    }
+    const int tb = nvec << 3;
+    if ((int)threadIdx.x < n - tb) {
+        const int v = src[tb + threadIdx.x];
+#pragma unroll
+        for (int u = 0; u < NS; ++u)
+            dst[u][tb + threadIdx.x] = (uint8_t)lab1p(v, pc[u]);
+    }
+}
+
+// Problems a tile may span and still be labelled piece by piece.
+constexpr int LABEL_MAX_PIECES = 4;
+
 // One workgroup per tile of blockDim * 8 * U voxels of the flattened batch,
 // one pass over the voxels for NS threshold sets (up to TS_MAX_LABEL_SETS):
-// each 16-byte load of 8 voxels feeds one 8-byte store per set.  A tile inside
-// one segment whose input and outputs share the 16/8-byte alignment phase is
-// labelled with vector accesses; any other tile voxel by voxel.  A one-shot
-// grid keeps the voxels in flight at any time in one window of HBM, which
-// streams faster on MI355X than long per-workgroup ranges.
+// each 16-byte load of 8 voxels feeds one 8-byte store per set.  A tile that
+// spans up to LABEL_MAX_PIECES problems is labelled one piece after the other
+// with vector accesses, at any alignment; a tile over more (tiny problems,
+// whose pieces would each cost a round trip for a few voxels) voxel by voxel.
+// A one-shot grid keeps the voxels in flight at any time in one window of
+// HBM, which streams faster on MI355X than long per-workgroup ranges.
 template <int NS, int U, int KM>
 __global__ void __launch_bounds__(1024) k_label(const int16_t *const *__restrict__ vox,
                                                 const int64_t *__restrict__ offs, int nseg, int64_t total, BinMap bm,
@@ -85,57 +137,43 @@ __global__ void __launch_bounds__(1024) k_label(const int16_t *const *__restrict
             os[u] = sets.out[u][s];
         wave_cuts<NS, KM>(sets, s, k, bm, cuts);
     }
-    if (t1 <= o1) { // the whole tile lies in segment s
+    if (t1 <= o1) { // the whole tile in one problem
         const TS_GLOBAL int16_t *src = gp(vs) + (t0 - o0);
+        bool al = ((uintptr_t)src & 15u) == 0;
         TS_GLOBAL uint8_t *dst[NS];
-        bool vec = ((uintptr_t)src & 15u) == 0;
 #pragma unroll
         for (int u = 0; u < NS; ++u) {
             dst[u] = gpw(os[u]) + (t0 - o0);
-            vec = vec && ((uintptr_t)dst[u] & 7u) == 0;
+            al = al && ((uintptr_t)dst[u] & 7u) == 0;
         }
-        const int n = (int)(t1 - t0);
-        if (vec) {
-            PCuts<KM> pc[NS];
+        if (al) {
+            label_piece<NS, U, KM, true>(src, dst, (int)(t1 - t0), cuts);
+            return;
+        }
+    }
+    if (t1 <= o1 || t1 <= offs[min(s + LABEL_MAX_PIECES, nseg)]) { // offs[s] <= t0 < offs[s + 1]: at most LABEL_MAX_PIECES problems
+        int64_t pos = t0;
+        for (;;) {
+            const int64_t end = min(t1, o1);
+            TS_GLOBAL uint8_t *dst[NS];
 #pragma unroll
             for (int u = 0; u < NS; ++u)
-                pc[u] = pack_cuts(cuts[u]);
-            const TS_GLOBAL v4i *vp = reinterpret_cast<const TS_GLOBAL v4i *>(src);
-            const int nvec = n >> 3;
-            v4i w[U];
+                dst[u] = gpw(os[u]) + (pos - o0);
+            label_piece<NS, U, KM, false>(gp(vs) + (pos - o0), dst, (int)(end - pos), cuts);
+            if (end >= t1)
+                return;
+            pos = end; // the next problem (an empty one gives an empty piece)
+            ++s;
+            o0 = o1;
+            o1 = offs[s + 1];
+            vs = vox[s];
 #pragma unroll
-            for (int j = 0; j < U; ++j) {
-                const int i = threadIdx.x + j * blockDim.x;
-                w[j] = i < nvec ? __builtin_nontemporal_load(vp + i) : v4i{0, 0, 0, 0};
-            }
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                const int i = threadIdx.x + j * blockDim.x;
-                if (i < nvec) {
-#pragma unroll
-                    for (int u = 0; u < NS; ++u)
-                        __builtin_nontemporal_store(lab8(w[j], pc[u]),
-                                                    reinterpret_cast<TS_GLOBAL v2u *>(dst[u]) + i);
-                }
-            }
-            const int tb = nvec << 3; // ragged end of the segment
-            if ((int)threadIdx.x < n - tb) {
-                const int v = src[tb + threadIdx.x];
-#pragma unroll
-                for (int u = 0; u < NS; ++u)
-                    dst[u][tb + threadIdx.x] = (uint8_t)lab1p(v, pc[u]);
-            }
-        } else {
-            for (int i = threadIdx.x; i < n; i += blockDim.x) {
-                const int v = src[i];
-#pragma unroll
-                for (int u = 0; u < NS; ++u)
-                    dst[u][i] = (uint8_t)lab1(v, cuts[u]);
-            }
+            for (int u = 0; u < NS; ++u)
+                os[u] = sets.out[u][s];
+            wave_cuts<NS, KM>(sets, s, k, bm, cuts);
         }
-        return;
     }
-    // the tile crosses segment ends: voxel by voxel, segments walked forward
+    // many problems in the tile: voxel by voxel, segments walked forward
     for (int64_t pos = t0 + threadIdx.x; pos < t1; pos += blockDim.x) {
         int sv = s;
         while (offs[sv + 1] <= pos)
@@ -182,10 +220,20 @@ ts_status launch_label(const ts_batch &b, const BinMap &bm, const LabelSets &set
     if (grid > 0x7fffffff)
         return fail(TS_ERR_INVALID_ARG, "ts_label: batch too large for one launch");
     const dim3 g((unsigned)grid), blk(t.label_block);
-    switch (k) { // as many cut values as thresholds up to 3, else the 16-cut instance
+    // as many cut values as thresholds up to 4, then the next of 6, 8 and 16:
+    // every cut costs three packed operations per voxel pair and set, used or
+    // not, and past about six of them per set the pass is bound by these
+    // instead of HBM (300 512 x 512 slices, two sets: k = 4 55 us, 148 us with
+    // 16 cuts; k = 6 66 us, 152 us with 16)
+    switch (k) {
     case 1: launch_label_km<1>(nsets, t.label_vecs, g, blk, st, b, bm, sets, k); break;
     case 2: launch_label_km<2>(nsets, t.label_vecs, g, blk, st, b, bm, sets, k); break;
     case 3: launch_label_km<3>(nsets, t.label_vecs, g, blk, st, b, bm, sets, k); break;
+    case 4: launch_label_km<4>(nsets, t.label_vecs, g, blk, st, b, bm, sets, k); break;
+    case 5:
+    case 6: launch_label_km<6>(nsets, t.label_vecs, g, blk, st, b, bm, sets, k); break;
+    case 7:
+    case 8: launch_label_km<8>(nsets, t.label_vecs, g, blk, st, b, bm, sets, k); break;
     default: launch_label_km<LABEL_MAX_K>(nsets, t.label_vecs, g, blk, st, b, bm, sets, k); break;
     }
     return check_launch("ts_label");

@@ -1866,40 +1866,28 @@ __device__ __forceinline__ void seg_count(uint32_t *lds, int lr, const TS_GLOBAL
 }
 
 // Labels of one whole problem for nq threshold sets (thresholds in LDS), the
-// rules of the label pass: 16-byte loads of 8 voxels and 8-byte stores per
-// set where the input and outputs share the alignment phase, else voxel by
-// voxel.
+// rules of the label pass: voxels up to the first 16-byte boundary one by
+// one, then 16-byte loads of 8 voxels and 8-byte stores per set, the stores at
+// whatever alignment the outputs have there.
 template <int K>
 __device__ __forceinline__ void seg_label(const SegArgs &g, int s, const TS_GLOBAL int16_t *src, int64_t n,
                                           const int (*tsh)[K])
 {
-    Cuts<K> cu[TS_MAX_LABEL_SETS];
     PCuts<K> pc[TS_MAX_LABEL_SETS];
     TS_GLOBAL uint8_t *dst[TS_MAX_LABEL_SETS];
     int64_t head = (int64_t)(((16u - ((uintptr_t)src & 15u)) & 15u) >> 1);
     if (head > n)
         head = n;
-    bool vec = true;
+    bool al[TS_MAX_LABEL_SETS];
 #pragma unroll
     for (int u = 0; u < TS_MAX_LABEL_SETS; ++u) {
         if (u < g.nq) {
-            cu[u] = make_cuts<K>(tsh[u], K, g.bm);
-            pc[u] = pack_cuts(cu[u]);
+            pc[u] = pack_cuts(make_cuts<K>(tsh[u], K, g.bm));
             dst[u] = gpw(g.sets.out[u][s]);
-            vec = vec && (((uintptr_t)(dst[u] + head)) & 7u) == 0;
+            al[u] = (((uintptr_t)(dst[u] + head)) & 7u) == 0;
         }
     }
     const int64_t bd = blockDim.x;
-    if (!vec) {
-        for (int64_t i = threadIdx.x; i < n; i += bd) {
-            const int v = src[i];
-#pragma unroll
-            for (int u = 0; u < TS_MAX_LABEL_SETS; ++u)
-                if (u < g.nq)
-                    dst[u][i] = (uint8_t)lab1(v, cu[u]);
-        }
-        return;
-    }
     if (threadIdx.x < head) {
         const int v = src[threadIdx.x];
 #pragma unroll
@@ -1923,8 +1911,7 @@ __device__ __forceinline__ void seg_label(const SegArgs &g, int s, const TS_GLOB
 #pragma unroll
                 for (int u = 0; u < TS_MAX_LABEL_SETS; ++u)
                     if (u < g.nq)
-                        __builtin_nontemporal_store(lab8(w[e], pc[u]),
-                                                    reinterpret_cast<TS_GLOBAL v2u *>(dst[u] + head) + i);
+                        store_lab8(dst[u] + head, i, lab8(w[e], pc[u]), al[u]);
             }
         }
     }
@@ -2360,17 +2347,11 @@ __device__ __forceinline__ void small_label(const TS_GLOBAL int16_t *src, TS_GLO
     int64_t head = (int64_t)(((16u - ((uintptr_t)(src + i0) & 15u)) & 15u) >> 1);
     if (head > i1 - i0)
         head = i1 - i0;
-    const bool vec = (((uintptr_t)(dst + i0 + head)) & 7u) == 0;
-    if (!vec) {
-        for (int64_t i = i0 + threadIdx.x; i < i1; i += blockDim.x)
-            dst[i] = (uint8_t)lab1p(src[i], pc);
-        return;
-    }
+    const bool al = (((uintptr_t)(dst + i0 + head)) & 7u) == 0;
     if (threadIdx.x < head)
         dst[i0 + threadIdx.x] = (uint8_t)lab1p(src[i0 + threadIdx.x], pc);
     const int64_t vb = i0 + head, nvec = (i1 - vb) >> 3;
     const TS_GLOBAL v4i *vp = reinterpret_cast<const TS_GLOBAL v4i *>(src + vb);
-    TS_GLOBAL v2u *op = reinterpret_cast<TS_GLOBAL v2u *>(dst + vb);
     const int64_t bd = blockDim.x;
     for (int64_t i0 = threadIdx.x; i0 < nvec; i0 += 4 * bd) { // four vectors in flight
         v4i x[4];
@@ -2380,7 +2361,7 @@ __device__ __forceinline__ void small_label(const TS_GLOBAL int16_t *src, TS_GLO
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             if (i0 + e * bd < nvec)
-                __builtin_nontemporal_store(lab8(x[e], pc), op + i0 + e * bd);
+                store_lab8(dst + vb, i0 + e * bd, lab8(x[e], pc), al);
     }
     const int64_t tb = vb + (nvec << 3);
     if (threadIdx.x < i1 - tb)

@@ -13,6 +13,22 @@ namespace ts {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+// The same vectors at any voxel (2-byte) or label (1-byte) address: gfx950
+// takes unaligned global accesses in one instruction, so problems that start
+// anywhere (slices with an odd number of pixels) keep the vector path.
+typedef v4i v4i_any __attribute__((aligned(2)));
+typedef v2u v2u_any __attribute__((aligned(1)));
+
+// Eight labels at dst + 8 i: non-temporal where dst is 8-byte aligned, else
+// ordinary stores (neighbouring wavefronts share the lines at the ends of a
+// misaligned store, which the L2 then merges).
+__device__ __forceinline__ void store_lab8(TS_GLOBAL uint8_t *dst, int64_t i, const v2u &v, bool aligned)
+{
+    if (aligned)
+        __builtin_nontemporal_store(v, reinterpret_cast<TS_GLOBAL v2u *>(dst) + i);
+    else
+        *reinterpret_cast<TS_GLOBAL v2u_any *>(dst + 8 * i) = v;
+}
 
 // Cut values of one threshold set: label = #{j : v >= c[j]}.  KM = k for k
 // <= 3; KM = LABEL_MAX_K holds up to that many, unused cuts are never
