@@ -11,15 +11,23 @@
 // and the maximum M = max over t of g(0 .. t) + V_{k-1}(t).  FP64 addition is
 // monotone, so M is exactly the largest of the per-tuple sums formed right
 // to left.  The tuple is rebuilt from the left: t_1 is the smallest t whose
-// value equals M, then t_j the smallest u > t_{j-1} whose value equals
-// V_{k-j+1}(t_{j-1}); values are recomputed by the same expressions, so the
-// equalities are exact and the tuple is the first (lexicographically) of
-// those reaching M.  A class with zero mass has g = -inf.  Empty bins repeat
+// value equals M, then t_j the smallest u > t_{j-1} reaching V_{k-j+1}(t_{j-1})
+// (kept by the level kernels; found again by k_dp_block, whose recomputed
+// values equal the maxima exactly), so the tuple is the first
+// (lexicographically) of those reaching M.  A class with zero mass has g = -inf.  Empty bins repeat
 // P and Q bit for bit (ts_prefix), so tuples that differ inside a run of
 // empty bins tie exactly, as in the exhaustive search.
 //
-// Work: k (L-1)^2 / 2 class terms (two FP64 logarithms each) per problem,
-// against C(L-1, k) tuples for the exhaustive search.
+// Only bins that change P or Q can be thresholds: where bin u repeats P and Q
+// of bin u-1, every class ending at u equals the one ending at u-1, every
+// class starting after u the one starting after u-1, and the class {u} is
+// empty.  V_m(u) is then V_m(u-1) bit for bit, its tuples tie with those of
+// u-1, and the first of them holds u-1.  So both forms leave such bins out.
+//
+// Work: n (n-1) / 2 class terms (two FP64 logarithms each) per problem and
+// level, n the bins left, against C(L-1, k) tuples for the exhaustive search.
+// k_dp_block (a whole problem per workgroup) forms each term once for all k
+// levels.
 #include <math.h>
 
 #include "common.h"
@@ -27,6 +35,10 @@
 namespace ts {
 
 constexpr int DP_THREADS = 256;
+constexpr int DP_FINAL_THREADS = 1024;
+constexpr int DP_FINAL_LDS = 16384; // first indices staged by k_dp_final
+constexpr int DP_BLOCK_BINS = 256; // levels of a problem that one workgroup takes whole
+constexpr int DP_STEP = DP_THREADS / 64; // candidates pushed per step, one per wavefront
 
 struct DPQ {
     double q[TS_MAX_Q];
@@ -36,8 +48,25 @@ struct DPArgs {
     const double *P, *Q;
     int nseg, nprob, L, k;
     DPQ qs;
-    double *V; // [k][nprob][L]
+    // Workspace of k planes of nprob L doubles: V_m in plane m & 1 (V_0 is not
+    // kept), then the levels' first indices.
+    double *V;
 };
+
+// Row of V_m, m >= 1, of problem s.
+__device__ __forceinline__ double *dp_v(const DPArgs &a, int m, int s)
+{
+    return a.V + ((int64_t)(a.k > 2 ? m & 1 : 0) * a.nprob + s) * a.L;
+}
+
+// Row of level m's first indices, 1 <= m < k, of problem s: after the planes
+// of V (one for k = 2, two for k > 2), of 2 (k - 1) bytes per bin in all,
+// which the remaining k - 1 or k - 2 planes of 8 bytes hold.
+__device__ __forceinline__ uint16_t *dp_next(const DPArgs &a, int m, int s)
+{
+    uint16_t *rows = (uint16_t *)(a.V + (int64_t)(a.k > 2 ? 2 : 1) * a.nprob * a.L);
+    return rows + ((int64_t)(m - 1) * a.nprob + s) * a.L;
+}
 
 __device__ __forceinline__ void dp_consts(double q, int L, double &sgn, double &hmax)
 {
@@ -45,32 +74,19 @@ __device__ __forceinline__ void dp_consts(double q, int L, double &sgn, double &
     hmax = (q == 1.0 ? 1.0 : fabs(1.0 - q)) * log((double)L); // a class holds at most L bins
 }
 
-// Class term of the bins a..b (a <= b) from the prefix sums; -inf if the
-// class has zero mass; clamped to [0, hmax].
-__device__ __forceinline__ double dp_g(const double *P, const double *Q, int a, int b, double q, double sgn,
-                                       double hmax)
+// Class term from the class's differences of P and Q; -inf if the class has
+// zero mass; clamped to [0, hmax].
+__device__ __forceinline__ double dp_h(double dP, double dQ, double q, double sgn, double hmax)
 {
-    const double pa = a ? P[a - 1] : 0.0, qa = a ? Q[a - 1] : 0.0;
-    const double dP = P[b] - pa, dQ = Q[b] - qa;
-    if (!(dP > 0.0))
-        return -INFINITY;
     const double h = sgn == 0.0 ? log(dP) - dQ / dP : sgn * (log(dQ) - q * log(dP));
-    return fmin(fmax(h, 0.0), hmax);
+    return dP > 0.0 ? fmin(fmax(h, 0.0), hmax) : -INFINITY;
 }
 
-// V_0(t) for every (problem, t): one thread each.
-__global__ void __launch_bounds__(DP_THREADS) k_dp_last(DPArgs a)
+// Bin u repeats the prefix sums of the bin before it (of nothing for u = 0).
+__device__ __forceinline__ bool dp_repeats(const double *P, const double *Q, int u)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int L = a.L;
-    if (i >= (int64_t)a.nprob * L)
-        return;
-    const int s = (int)(i / L), t = (int)(i % L);
-    const double q = a.qs.q[s / a.nseg];
-    double sgn, hmax;
-    dp_consts(q, L, sgn, hmax);
-    const double *P = a.P + (int64_t)(s % a.nseg) * L, *Q = a.Q + (int64_t)s * L;
-    a.V[i] = t <= L - 2 ? dp_g(P, Q, t + 1, L - 1, q, sgn, hmax) : -INFINITY;
+    const double pa = u ? P[u - 1] : 0.0, qa = u ? Q[u - 1] : 0.0;
+    return P[u] == pa && Q[u] == qa;
 }
 
 __device__ __forceinline__ double wave_max_d(double v)
@@ -81,115 +97,346 @@ __device__ __forceinline__ double wave_max_d(double v)
     return v;
 }
 
-// V_m(t) for one (problem, t) per workgroup: the threads split u.
+__device__ __forceinline__ double readlane_d(double v, int l)
+{
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)b, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// V_m(t) and the first u reaching it for one (problem, t) per workgroup: the
+// threads split u.  Bounded by one round of loads and the two logarithms of
+// its terms; rows and terms of repeating bins are left out (their V is never
+// read).  FIRST is m = 1, which forms V_0(u) itself: four logarithms per term
+// of one level take less than the launch of a kernel for V_0.
+template <bool FIRST>
 __global__ void __launch_bounds__(DP_THREADS) k_dp_level(DPArgs a, int m)
 {
     __shared__ double red[DP_THREADS / 64];
+    __shared__ int redu[DP_THREADS / 64];
     const int L = a.L;
     const int s = blockIdx.x / (L - 1), t = blockIdx.x % (L - 1);
     const double q = a.qs.q[s / a.nseg];
+    const double *P = a.P + (int64_t)(s % a.nseg) * L, *Q = a.Q + (int64_t)s * L;
+    const double *Vp = dp_v(a, m - 1, s); // not read by FIRST
+    const bool skip = dp_repeats(P, Q, t);
+    const double pt = P[t], qt = Q[t], PL = P[L - 1], QL = Q[L - 1];
+    int u = t + 1 + threadIdx.x; // u - 1 >= 0; past the row's end its last bin is read and not used
+    auto at = [&](int i) { return min(i, L - 1); };
+    double pu = P[at(u)], qu = Q[at(u)], pb = P[at(u) - 1], qb = Q[at(u) - 1], vu = FIRST ? 0.0 : Vp[at(u)];
+    if (skip)
+        return;
     double sgn, hmax;
     dp_consts(q, L, sgn, hmax);
-    const double *P = a.P + (int64_t)(s % a.nseg) * L, *Q = a.Q + (int64_t)s * L;
-    const double *Vp = a.V + ((int64_t)(m - 1) * a.nprob + s) * L;
     double best = -INFINITY;
-    for (int u = t + 1 + threadIdx.x; u <= L - 2; u += blockDim.x) {
-        const double vu = Vp[u];
-        if (vu > -INFINITY)
-            best = fmax(best, dp_g(P, Q, t + 1, u, q, sgn, hmax) + vu);
+    int bu = 0x7fffffff;
+    while (__any(u <= L - 2)) {
+        const bool use = u <= L - 2 && !(pu == pb && qu == qb);
+        const int cu = u;
+        const double cp = pu, cq = qu, cv = vu;
+        u += blockDim.x;
+        pu = P[at(u)], qu = Q[at(u)], pb = P[at(u) - 1], qb = Q[at(u) - 1], vu = FIRST ? 0.0 : Vp[at(u)];
+        if (use) {
+            const double v = FIRST ? dp_h(PL - cp, QL - cq, q, sgn, hmax) : cv;
+            const double x = dp_h(cp - pt, cq - qt, q, sgn, hmax) + v;
+            if (x > best) {
+                best = x;
+                bu = cu;
+            }
+        }
     }
-    best = wave_max_d(best);
-    if ((threadIdx.x & 63) == 0)
-        red[threadIdx.x >> 6] = best;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < (int)(blockDim.x >> 6); ++w)
-            best = fmax(best, red[w]);
-        a.V[((int64_t)m * a.nprob + s) * L + t] = best;
-    }
-}
-
-// Smallest index in [lo, hi] whose value equals target (or hi + 1), for the
-// wavefront; value(u) is evaluated once per index.
-template <typename F>
-__device__ __forceinline__ int first_equal(int lo, int hi, double target, F &&value)
-{
-    int found = 0x7fffffff;
-    for (int u = lo + (int)threadIdx.x; u <= hi; u += 64)
-        if (u < found && value(u) == target)
-            found = u;
+    const double wbest = wave_max_d(best);
+    bu = best == wbest ? bu : 0x7fffffff;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1)
-        found = min(found, __shfl_xor(found, o, 64));
-    return found;
+        bu = min(bu, __shfl_xor(bu, o, 64));
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6] = wbest;
+        redu[threadIdx.x >> 6] = bu;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        best = wbest;
+        for (int w = 1; w < (int)(blockDim.x >> 6); ++w)
+            if (red[w] > best || (red[w] == best && redu[w] < bu)) {
+                best = red[w];
+                bu = redu[w];
+            }
+        dp_v(a, m, s)[t] = best;
+        dp_next(a, m, s)[t] = (uint16_t)bu; // not read where the best is -inf
+    }
 }
 
-// One wavefront per problem: the maximum and the first tuple reaching it.
-__global__ void __launch_bounds__(64) k_dp_final(DPArgs a, int32_t *__restrict__ thr, double *__restrict__ obj,
-                                                 int32_t *__restrict__ status)
+// LDS of dp_tuple: two stages' exchange, by stage parity (one barrier each).
+struct DPTupleLds {
+    double d[2][4][DP_THREADS / 64];
+    int c[2][DP_THREADS / 64];
+};
+
+// Result of a problem whose maximum is M (-inf: no tuple), its thresholds
+// already written; by one thread.
+__device__ __forceinline__ void dp_result(double M, bool ok, int k, double q, double sgn, double last, int32_t *out,
+                                          double *obj, int32_t *status)
 {
+    if (ok) {
+        *obj = sgn == 0.0 ? M : expm1(sgn * M) / (1.0 - q);
+        *status = TS_PROBLEM_OK;
+    } else {
+        for (int j = 0; j < k; ++j)
+            out[j] = -1;
+        *obj = NAN;
+        *status = last > 0.0 ? TS_PROBLEM_DEGENERATE : TS_PROBLEM_EMPTY;
+    }
+}
+
+// The maximum and the first tuple reaching it, by the whole workgroup, from
+// candidates c = 0 .. n-1, one per thread: bins bin[c], increasing, prefix
+// sums Pc[c], Qc[c] and V[m][c].  The recomputed values equal the stored
+// maxima bit for bit, so an index is always found; should one not be, the
+// problem is reported degenerate rather than indexing past the row.  The
+// thread that owns a stage's threshold hands its values on.
+__device__ __forceinline__ void dp_tuple(DPTupleLds &sh, int n, int k, double q, double sgn, double hmax,
+                                         double last, const int *bin, const double *Pc, const double *Qc,
+                                         const double (*V)[DP_BLOCK_BINS], int32_t *out, double *obj,
+                                         int32_t *status)
+{
+    const int c = threadIdx.x, lane = c & 63, w = c >> 6, waves = blockDim.x >> 6;
+    constexpr int NONE = 0x7fffffff;
+    const bool use = c < n;
+    const double pc = use ? Pc[c] : 0.0, qc = use ? Qc[c] : 0.0;
+    double v = use ? V[k - 1][c] : -INFINITY;
+    double val = use ? dp_h(pc, qc, q, sgn, hmax) + v : -INFINITY;
+    double M = wave_max_d(val);
+    if (lane == 0)
+        sh.d[1][0][w] = M;
+    __syncthreads();
+    for (int x = 0; x < waves; ++x)
+        M = fmax(M, sh.d[1][0][x]);
+    bool ok = M > -INFINITY;
+    double target = M, pb = 0.0, qb = 0.0;
+    int c0 = 0; // candidates from here on
+    for (int j = 0; j < k && ok; ++j) {
+        const bool in = use && c >= c0;
+        if (j && in)
+            val = dp_h(pc - pb, qc - qb, q, sgn, hmax) + v;
+        const uint64_t hit = __ballot(in && val == target);
+        const int par = j & 1;
+        if (hit ? lane == __ffsll((long long)hit) - 1 : lane == 0) {
+            sh.c[par][w] = hit ? c : NONE;
+            sh.d[par][1][w] = v;
+            sh.d[par][2][w] = pc;
+            sh.d[par][3][w] = qc;
+        }
+        if (j + 1 < k && use)
+            v = V[k - 2 - j][c];
+        __syncthreads();
+        int bw = 0;
+        for (int x = 1; x < waves; ++x)
+            if (sh.c[par][x] < sh.c[par][bw])
+                bw = x;
+        const int first = sh.c[par][bw];
+        target = sh.d[par][1][bw];
+        pb = sh.d[par][2][bw];
+        qb = sh.d[par][3][bw];
+        ok = first != NONE;
+        if (ok && c == 0)
+            out[j] = bin[first];
+        c0 = first + 1; // unused once not ok
+    }
+    if (c == 0)
+        dp_result(M, ok, k, q, sgn, last, out, obj, status);
+}
+
+// One workgroup per problem: the maximum over t_1 (smallest t_1 reaching it),
+// then the thresholds after it from the levels' first indices, a chain of
+// k - 1 dependent reads: of LDS where the rows of all levels fit.  (Found
+// again by recomputing every stage's values it took 15 us at 1024 bins, k = 6:
+// 2 (k - 1) logarithms per thread on one CU.)
+__global__ void __launch_bounds__(DP_FINAL_THREADS) k_dp_final(DPArgs a, int32_t *__restrict__ thr,
+                                                               double *__restrict__ obj,
+                                                               int32_t *__restrict__ status)
+{
+    constexpr int NONE = 0x7fffffff;
+    __shared__ uint16_t snext[DP_FINAL_LDS];
+    __shared__ double redv[DP_FINAL_THREADS / 64];
+    __shared__ int redt[DP_FINAL_THREADS / 64];
     const int s = blockIdx.x, L = a.L, k = a.k;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const double q = a.qs.q[s / a.nseg];
     double sgn, hmax;
     dp_consts(q, L, sgn, hmax);
     const double *P = a.P + (int64_t)(s % a.nseg) * L, *Q = a.Q + (int64_t)s * L;
-    auto Vrow = [&](int m) { return a.V + ((int64_t)m * a.nprob + s) * L; };
-    // M = max over t of g(0..t) + V_{k-1}(t)
-    const double *Vk = Vrow(k - 1);
-    auto first = [&](int t) {
-        const double v = Vk[t];
-        return v > -INFINITY ? dp_g(P, Q, 0, t, q, sgn, hmax) + v : -INFINITY;
-    };
+    const double PL = P[L - 1], QL = Q[L - 1];
+    const bool staged = (k - 1) * L <= DP_FINAL_LDS;
+    if (staged)
+        for (int m = 1; m < k; ++m)
+            for (int t = threadIdx.x; t < L - 1; t += blockDim.x) // rows of repeating bins: never written, never used
+                snext[(m - 1) * L + t] = dp_next(a, m, s)[t];
+    const double *Vk = dp_v(a, k - 1, s); // k = 1: V_0 is formed here
     double M = -INFINITY;
-    for (int t = threadIdx.x; t <= L - 2; t += 64)
-        M = fmax(M, first(t));
-    M = wave_max_d(M);
-    int32_t *out = thr + (int64_t)s * k;
-    if (!(M > -INFINITY)) {
-        if (threadIdx.x == 0) {
-            for (int j = 0; j < k; ++j)
-                out[j] = -1;
-            obj[s] = NAN;
-            status[s] = P[L - 1] > 0.0 ? TS_PROBLEM_DEGENERATE : TS_PROBLEM_EMPTY;
+    int t1 = NONE;
+    for (int t = threadIdx.x; t <= L - 2; t += blockDim.x) {
+        const double p = P[t], x = Q[t], v = k > 1 ? Vk[t] : 0.0;
+        if (dp_repeats(P, Q, t))
+            continue;
+        const double val = dp_h(p, x, q, sgn, hmax) + (k > 1 ? v : dp_h(PL - p, QL - x, q, sgn, hmax));
+        if (val > M) {
+            M = val;
+            t1 = t;
         }
-        return;
     }
-    // the recomputed values equal the stored maxima bit for bit, so an index
-    // is always found; should one not be, the problem is reported degenerate
-    // rather than indexing past the row
-    auto lost = [&]() {
-        if (threadIdx.x == 0) {
-            for (int j = 0; j < k; ++j)
-                out[j] = -1;
-            obj[s] = NAN;
-            status[s] = TS_PROBLEM_DEGENERATE;
+    const double wM = wave_max_d(M);
+    t1 = M == wM ? t1 : NONE;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1)
+        t1 = min(t1, __shfl_xor(t1, o, 64));
+    if (lane == 0) {
+        redv[w] = wM;
+        redt[w] = t1;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        M = wM;
+        for (int x = 1; x < (int)(blockDim.x >> 6); ++x)
+            if (redv[x] > M || (redv[x] == M && redt[x] < t1)) {
+                M = redv[x];
+                t1 = redt[x];
+            }
+        int32_t *out = thr + (int64_t)s * k;
+        const bool ok = M > -INFINITY;
+        if (ok) {
+            out[0] = t1;
+            int t = t1;
+            for (int j = 1; j < k; ++j) {
+                const int m = k - j; // t_{j+1} completes m thresholds after t_j
+                t = min(staged ? (int)snext[(m - 1) * L + t] : (int)dp_next(a, m, s)[t], L - 2);
+                out[j] = t;
+            }
+        }
+        dp_result(M, ok, k, q, sgn, PL, out, obj + s, status + s);
+    }
+}
+
+// A whole problem per workgroup, for L <= DP_BLOCK_BINS and k <= KM.  The
+// bins that can be thresholds are compacted (candidates 0 .. n-1); thread c
+// owns candidate c and holds V_m(c) as running maxima, and the candidates u
+// are pushed to those before them from the last to the first,
+// V_m(t) = max(V_m(t), g(t+1 .. u) + V_{m-1}(u)),
+// so that a class term is formed once for all levels.  The terms do not
+// depend on V: four candidates u at a time, wavefront w forms those of the
+// w-th for every t into an LDS tile, one step ahead of its use.  A step:
+//   apply the four u of the step before (V from LDS) to the wavefronts below
+//   them; the wavefront owning this step's four pushes them one by one, V(u)
+//   read from its lane, and stores their V; the next step's tile; one
+//   barrier (three tiles in turn).
+// Bounded by the logarithms (about 95 FP64 instructions each, a dependent
+// chain): 600 problems of 256 levels, about 130 candidates, k = 4: 92 us
+// (three level launches and the tuple's took 733); one problem 46 us.  With
+// the terms formed by each candidate's own wavefront, where the wavefronts
+// wait for each other in turn, 115 and 102 us.
+template <int KM>
+__global__ void __launch_bounds__(DP_THREADS) k_dp_block(DPArgs a, int32_t *__restrict__ thr,
+                                                         double *__restrict__ obj, int32_t *__restrict__ status)
+{
+    __shared__ double sP[DP_BLOCK_BINS], sQ[DP_BLOCK_BINS]; // prefix sums of the candidates
+    __shared__ double sV[KM][DP_BLOCK_BINS];
+    __shared__ double sg[3][DP_STEP][DP_BLOCK_BINS];
+    __shared__ int sbin[DP_BLOCK_BINS];
+    __shared__ int wcount[DP_STEP];
+    __shared__ DPTupleLds sh;
+    const int s = blockIdx.x, L = a.L, tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const double q = a.qs.q[s / a.nseg];
+    double sgn, hmax;
+    dp_consts(q, L, sgn, hmax);
+    const double *P = a.P + (int64_t)(s % a.nseg) * L, *Q = a.Q + (int64_t)s * L;
+    const double PL = P[L - 1], QL = Q[L - 1];
+    const bool cand = tid <= L - 2 && !dp_repeats(P, Q, tid);
+    const uint64_t bal = __ballot(cand);
+    if (lane == 0)
+        wcount[w] = __popcll(bal);
+    __syncthreads();
+    int base = 0, n = 0;
+    for (int v = 0; v < DP_STEP; ++v) {
+        base += v < w ? wcount[v] : 0;
+        n += wcount[v];
+    }
+    n = __builtin_amdgcn_readfirstlane(n);
+    if (cand) {
+        const int c = base + __popcll(bal & ((1ull << lane) - 1ull));
+        sP[c] = P[tid];
+        sQ[c] = Q[tid];
+        sbin[c] = tid;
+    }
+    __syncthreads();
+    // the terms of u = 4 b + w for the candidates t of the chunks up to the
+    // step's; -inf where t does not precede u
+    auto tile = [&](int b, int buf) {
+        const int u = DP_STEP * b + w;
+        if (u >= n)
+            return;
+        const double pu = sP[u], qu = sQ[u];
+        for (int t = lane; t < DP_STEP * (b + 1); t += 64) {
+            const int tc = min(t, n - 1);
+            const double g = dp_h(pu - sP[tc], qu - sQ[tc], q, sgn, hmax);
+            sg[buf][w][t] = t < u ? g : -INFINITY;
         }
     };
-    int tj = first_equal(0, L - 2, M, first);
-    if (tj > L - 2)
-        return lost();
-    if (threadIdx.x == 0)
-        out[0] = tj;
-    double target = Vk[tj];
-    for (int j = 1; j < k; ++j) {
-        const int m = k - 1 - j; // completions after threshold j+1
-        const double *Vm = Vrow(m);
-        const int prev = tj;
-        auto val = [&](int u) {
-            const double v = Vm[u];
-            return v > -INFINITY ? dp_g(P, Q, prev + 1, u, q, sgn, hmax) + v : -INFINITY;
-        };
-        tj = first_equal(prev + 1, L - 2, target, val);
-        if (tj > L - 2)
-            return lost();
-        if (threadIdx.x == 0)
-            out[j] = tj;
-        target = Vm[tj];
+    double acc[KM]; // V_m(tid); threads past the candidates stay at -inf
+    acc[0] = tid < n ? dp_h(PL - sP[tid], QL - sQ[tid], q, sgn, hmax) : -INFINITY;
+#pragma unroll
+    for (int m = 1; m < KM; ++m)
+        acc[m] = -INFINITY;
+    const int nb = (n + DP_STEP - 1) / DP_STEP;
+    int cur = 0, prv = 2, nxt = 1; // tiles of this step, of the one before, of the next
+    if (nb > 0)
+        tile(nb - 1, cur);
+    __syncthreads();
+    for (int b = nb - 1; b >= 0; --b) {
+        const int u0 = DP_STEP * b, own = u0 >> 6;
+        if (b + 1 < nb && w < (u0 + DP_STEP) >> 6) {
+#pragma unroll
+            for (int d = DP_STEP - 1; d >= 0; --d) {
+                const int u = u0 + DP_STEP + d;
+                if (u < n) {
+                    const double g = sg[prv][d][tid];
+#pragma unroll
+                    for (int m = 1; m < KM; ++m)
+                        acc[m] = fmax(acc[m], g + sV[m - 1][u]);
+                }
+            }
+        }
+        if (w == own) {
+            // lanes past the tile's width hold candidates after u: no term
+#pragma unroll
+            for (int d = DP_STEP - 1; d >= 0; --d) {
+                if (u0 + d < n) {
+                    const double g = tid < u0 + d ? sg[cur][d][tid] : -INFINITY;
+                    double vu[KM];
+#pragma unroll
+                    for (int m = 0; m < KM - 1; ++m)
+                        vu[m] = readlane_d(acc[m], (u0 + d) & 63);
+#pragma unroll
+                    for (int m = 1; m < KM; ++m)
+                        acc[m] = fmax(acc[m], g + vu[m - 1]);
+                }
+            }
+            if (tid >= u0 && tid < u0 + DP_STEP) {
+#pragma unroll
+                for (int m = 0; m < KM; ++m)
+                    sV[m][tid] = acc[m];
+            }
+        }
+        if (b > 0)
+            tile(b - 1, nxt);
+        __syncthreads();
+        const int x = prv;
+        prv = cur;
+        cur = nxt;
+        nxt = x;
     }
-    if (threadIdx.x == 0) {
-        obj[s] = sgn == 0.0 ? M : expm1(sgn * M) / (1.0 - q);
-        status[s] = TS_PROBLEM_OK;
-    }
+    dp_tuple(sh, n, a.k, q, sgn, hmax, PL, sbin, sP, sQ, sV, thr + (int64_t)s * a.k, obj + s, status + s);
 }
 
 size_t dp_workspace_bytes(int nprob, int L, int k) { return (size_t)k * nprob * L * sizeof(double); }
@@ -207,11 +454,28 @@ ts_status launch_dp(const double *P, const double *Q, int nseg, int L, int k, in
     for (int j = 0; j < TS_MAX_Q; ++j)
         a.qs.q[j] = q[j < nq ? j : 0];
     a.V = (double *)ws;
-    const int64_t n0 = (int64_t)a.nprob * L;
-    hipLaunchKernelGGL(k_dp_last, dim3((unsigned)((n0 + DP_THREADS - 1) / DP_THREADS)), dim3(DP_THREADS), 0, st, a);
-    for (int m = 1; m < k; ++m)
-        hipLaunchKernelGGL(k_dp_level, dim3((unsigned)((int64_t)a.nprob * (L - 1))), dim3(DP_THREADS), 0, st, a, m);
-    hipLaunchKernelGGL(k_dp_final, dim3((unsigned)a.nprob), dim3(64), 0, st, a, thr, obj, status);
+    // One workgroup per problem takes as long for one problem as for the chip
+    // full of them (a chain over the candidates: k = 4, 16 us at 64 levels, 25
+    // at 128, 48 at 256, on CT slices); the level kernels take 5 us a level
+    // and more with every problem (k = 4: 18-19 us for one problem, 26 for 12
+    // at 128 levels, 46 for 24 at 256).  The two meet near this line for k = 2
+    // .. 8; more levels than threads have only the level kernels.
+    if (L <= DP_BLOCK_BINS && 5 * (int64_t)a.nprob * (k - 1) >= 2 * (L - 64)) {
+        const dim3 g((unsigned)a.nprob), blk(DP_THREADS);
+        if (k <= 4)
+            hipLaunchKernelGGL(k_dp_block<4>, g, blk, 0, st, a, thr, obj, status);
+        else if (k <= 8)
+            hipLaunchKernelGGL(k_dp_block<8>, g, blk, 0, st, a, thr, obj, status);
+        else
+            hipLaunchKernelGGL(k_dp_block<16>, g, blk, 0, st, a, thr, obj, status);
+        return check_launch("ts_threshold_search_dp");
+    }
+    const dim3 g((unsigned)((int64_t)a.nprob * (L - 1)));
+    if (k > 1)
+        hipLaunchKernelGGL(k_dp_level<true>, g, dim3(DP_THREADS), 0, st, a, 1);
+    for (int m = 2; m < k; ++m)
+        hipLaunchKernelGGL(k_dp_level<false>, g, dim3(DP_THREADS), 0, st, a, m);
+    hipLaunchKernelGGL(k_dp_final, dim3((unsigned)a.nprob), dim3(DP_FINAL_THREADS), 0, st, a, thr, obj, status);
     return check_launch("ts_threshold_search_dp");
 }
 
