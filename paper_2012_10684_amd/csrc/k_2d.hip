@@ -5,15 +5,14 @@
 // {i > t, j > s} (quadrants 1 and 3) and the arg max over (t, s) of the
 // pseudo-additive objective.  Only t thresholds the image (ts_label, k = 1).
 //
-// k_hist2d: one workgroup per band of at most 65535 pixels of one image, in
-// chunks of about 4096 pixels: the 8-bit gray levels of a chunk's rows and
-// its two halo rows are staged in LDS in one pass, so each pixel's 3x3 sum
-// reads LDS only.  The whole L x L plane is counted in LDS as 16-bit cells
-// (two per word; 128 KiB at L = 256), which cannot overflow within the
-// band; the two clamp corners (0, 0) and (L-1, L-1), which take a large share
-// of the pixels under a narrow window, count in per-lane LDS words instead of
-// one hot address.  At the end the non-zero cells are added to the global 2D
-// histogram.
+// k_hist2d: one workgroup per CU, an equal share of the images' rows each.  The
+// whole L x L plane is counted in LDS as 16-bit cells (two per word; 128 KiB
+// at L = 256).  A lane holds 8 neighbouring columns and walks down the rows:
+// gray levels, row sums of three and the sums of three rows stay in
+// registers as packed 16-bit pairs, the neighbours' edge columns come by lane
+// moves, and LDS sees nothing but one atomic per pixel.  Lanes whose 8 pixels
+// all lie in a clamp corner ((0, 0) or (L-1, L-1), a large share of the pixels
+// under a narrow window) count in a register instead of one hot address.
 //
 // k_search2d: one workgroup of four wavefronts per (q index, problem); the
 // rows holding counts are split into four blocks, one per wavefront, four
@@ -41,9 +40,9 @@ namespace ts {
 typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int H2_THREADS = 1024;
-constexpr int H2_MAX_W = 4096;    // row length held in the LDS ring
+constexpr int H2_MAX_W = 4096;    // widest row
 constexpr int H2_MAX_L = 256;     // 2D histograms up to 256 x 256
-constexpr int H2_LDS = 160 * 1024; // LDS of one workgroup: the plane (128 KiB at L = 256) and staged rows
+constexpr int H2_MIN_ROWS = 16;   // rows a workgroup takes at least
 constexpr int S2_WAVES = 4;       // wavefronts per (q, image), each a block of the rows
 constexpr int S2_THREADS = 64 * S2_WAVES;
 constexpr int S2_CPL = 4;         // columns per lane (L <= 256)
@@ -52,179 +51,457 @@ constexpr int S2_RING = 3;        // rows of counts in flight ahead of the row b
 
 // ------------------------------------------------------------------ histogram
 
-// LDS layout of k_hist2d: the packed plane, the per-lane corner counters,
-// then the staged gray levels (16-byte aligned).
-__host__ __device__ inline int hist2d_rows_offset(int L) { return (((L * L + 1) / 2 + 128) * 4 + 15) & ~15; }
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+typedef short i16x2 __attribute__((ext_vector_type(2)));
+// 8 pixels at any pixel address (gfx950 takes unaligned global loads)
+typedef v4i v4i_any __attribute__((aligned(2)));
 
-template <int MAP>
-__global__ void __launch_bounds__(H2_THREADS) k_hist2d(const int16_t *const *__restrict__ vox, int nseg, int H,
-                                                       int W, int rows_per_wg, int chunk_rows, BinMap bm,
-                                                       uint32_t *__restrict__ hist)
+__device__ __forceinline__ uint32_t pk_add(uint32_t a, uint32_t b)
 {
-    extern __shared__ uint32_t sm[];
-    const int L = bm.L;
-    const int nw2 = (L * L + 1) / 2;                       // packed 16-bit cells
-    uint32_t *plane = sm;                                  // [nw2]: cell c in half (c & 1) of word c >> 1
-    uint32_t *hot = plane + nw2;                           // [2 * 64]: (0,0), (L-1,L-1) per lane
-    uint8_t *rows = reinterpret_cast<uint8_t *>(sm) + hist2d_rows_offset(L); // [(chunk_rows + 2) * W]
-    const int lane = threadIdx.x & 63;
-    const int bands = (H + rows_per_wg - 1) / rows_per_wg;
-    const int s = blockIdx.x / bands;
-    const int r0 = (blockIdx.x % bands) * rows_per_wg;
-    const int r1 = min(H, r0 + rows_per_wg);
-    const TS_GLOBAL int16_t *img = gp(vox[s]);
-    uint32_t *hs = hist + (int64_t)s * L * L;
-    const bool vec = (W % 8) == 0 && ((uintptr_t)img & 15) == 0;
-    for (int i = threadIdx.x; i < nw2 + 128; i += blockDim.x)
-        sm[i] = 0u;
-    // one count: (f, g) = (gray level, floor of the 3x3 mean); the clamp
-    // corners count in per-lane words, every other cell in its half-word
-    auto count = [&](int f, int sum) {
-        const int g = (int)((uint32_t)sum / 9u);
-        const int c = f * L + g;
-        const bool corner = f == g && (f == 0 || f == L - 1);
-        uint32_t *a = corner ? hot + (f == 0 ? 0 : 64) + lane : plane + (c >> 1);
-        atomicAdd(a, corner ? 1u : (1u << ((c & 1) << 4)));
-    };
-    // chunks of chunk_rows image rows: the gray levels of rows r-1 .. r+n
-    // (edge rows repeated) are staged in LDS in one pass, then every pixel of
-    // rows r .. r+n-1 is counted
-    for (int r = r0; r < r1; r += chunk_rows) {
-        const int n = min(chunk_rows, r1 - r);
-        __syncthreads(); // previous chunk fully counted
-        if (vec) { // 8 pixels per 16-byte load, 8 gray levels per 8-byte LDS store
-            const int nv = (n + 2) * W / 8;
-            for (int i = threadIdx.x; i < nv; i += blockDim.x) {
-                const int e = i * 8, k = e / W, x = e - k * W;
-                const int y = min(max(r - 1 + k, 0), H - 1);
-                const v4i v = *reinterpret_cast<const TS_GLOBAL v4i *>(img + (int64_t)y * W + x);
-                const uint32_t w4[4] = {(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
-                uint32_t b[2] = {0u, 0u};
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int16_t h16 = (int16_t)(w4[j >> 1] >> ((j & 1) * 16));
-                    b[j >> 2] |= (uint32_t)bin_of_t<MAP>(h16, bm) << ((j & 3) * 8);
-                }
-                *reinterpret_cast<uint2 *>(rows + e) = make_uint2(b[0], b[1]);
-            }
-        } else {
-            for (int i = threadIdx.x; i < (n + 2) * W; i += blockDim.x) {
-                const int k = i / W, x = i - k * W;
-                const int y = min(max(r - 1 + k, 0), H - 1);
-                rows[i] = (uint8_t)bin_of_t<MAP>(img[(int64_t)y * W + x], bm);
-            }
-        }
-        __syncthreads();
-        if ((W & 3) == 0) { // 4 pixels per thread: one aligned word and its two neighbours per row
-            const int n4 = n * W / 4;
-            for (int i = threadIdx.x; i < n4; i += blockDim.x) {
-                const int e = i * 4, k = e / W + 1, x = e - (k - 1) * W;
-                int hsum[3][4];
-                int fcen[4];
-#pragma unroll
-                for (int dy = 0; dy < 3; ++dy) {
-                    const uint8_t *row = rows + (k - 1 + dy) * W;
-                    const uint32_t wd = *reinterpret_cast<const uint32_t *>(row + x);
-                    int b[6];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        b[j + 1] = (wd >> (8 * j)) & 0xff;
-                    b[0] = x > 0 ? row[x - 1] : b[1];          // edge pixel repeated
-                    b[5] = x + 4 < W ? row[x + 4] : b[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        hsum[dy][j] = b[j] + b[j + 1] + b[j + 2];
-                    if (dy == 1) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            fcen[j] = b[j + 1];
-                    }
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    count(fcen[j], hsum[0][j] + hsum[1][j] + hsum[2][j]);
-            }
-        } else {
-            for (int i = threadIdx.x; i < n * W; i += blockDim.x) {
-                const int k = i / W + 1, x = i - (k - 1) * W;
-                const int xl = max(x - 1, 0), xr = min(x + 1, W - 1);
-                const uint8_t *up = rows + (k - 1) * W, *cu = rows + k * W, *dn = rows + (k + 1) * W;
-                count(cu[x], (int)up[xl] + up[x] + up[xr] + cu[xl] + cu[x] + cu[xr] + dn[xl] + dn[x] + dn[xr]);
-            }
-        }
-    }
-    __syncthreads();
-    // every cell count is at most the workgroup's pixel count (<= 65535): no
-    // half-word overflows.  Add the non-zero cells to the global histogram.
-    for (int i = threadIdx.x; i < nw2; i += blockDim.x) {
-        uint32_t w2 = plane[i];
-        if (i == 0 || i == (L * L - 1) >> 1) { // the clamp corners' per-lane counters
-            for (int j = 0; j < 2; ++j) {
-                const int cell = j == 0 ? 0 : L * L - 1;
-                if ((cell >> 1) != i)
-                    continue;
-                uint32_t cc = 0;
-                for (int l = 0; l < 64; ++l)
-                    cc += hot[j * 64 + l];
-                atomicAdd(&hs[cell], cc); // global directly: the sum may exceed 16 bits
-            }
-        }
-        if (w2 & 0xffffu)
-            atomicAdd(&hs[2 * i], w2 & 0xffffu);
-        if ((w2 >> 16) && 2 * i + 1 < L * L)
-            atomicAdd(&hs[2 * i + 1], w2 >> 16);
-    }
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, a) + __builtin_bit_cast(u16x2, b));
 }
 
-// Band and chunk sizes: bands of at most 65535 pixels (16-bit cells),
-// balanced over the image's rows; chunks as large as the LDS left beside the
-// plane allows, balanced over the band.
+// The pair (high half of a, low half of b): the window one pixel later.
+__device__ __forceinline__ uint32_t pair_mid(uint32_t a, uint32_t b) { return __builtin_amdgcn_alignbit(b, a, 16); }
+
+// Cross-lane moves within the wavefront (DPP): lanes without a source, or in
+// rows masked off, receive 0, the identity of the sums below.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp32(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+
+// Gray levels of two pixels, packed: clamped and offset together, then the
+// map for each.  KIND: 0 the level is the offset (W = L); 1 the top byte of
+// offset * mul24, both multiplied from their halves and the bytes picked by
+// one permute; 2 any other window, by the general map.
+template <int KIND>
+__device__ __forceinline__ uint32_t levels2(uint32_t v, const BinMap &bm, uint32_t mul24)
+{
+    if constexpr (KIND == 2)
+        return (uint32_t)bin_of((int16_t)(v & 0xffffu), bm) | (uint32_t)bin_of((int)v >> 16, bm) << 16;
+    const i16x2 lo = {(short)bm.lo, (short)bm.lo}, hi = {(short)bm.hi, (short)bm.hi};
+    i16x2 c = __builtin_bit_cast(i16x2, v);
+    c = __builtin_elementwise_min(__builtin_elementwise_max(c, lo), hi);
+    const uint32_t d = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, c) - __builtin_bit_cast(u16x2, lo));
+    if constexpr (KIND == 0)
+        return d;
+    return __builtin_amdgcn_perm(__umul24(d >> 16, mul24), __umul24(d & 0xffffu, mul24), 0x0c070c03u);
+}
+
+// The multiplier of KIND 1 (0: none): ceil(2^24 L / W) reproduces
+// floor(d L / W) for every offset d when W^2 < 2^24, or the quotient is exact.
+static uint32_t hist2d_mul24(const BinMap &bm)
+{
+    const uint64_t W = (uint64_t)(bm.hi - bm.lo + 1), n = (uint64_t)bm.L << 24;
+    const uint64_t mul = (n + W - 1) / W;
+    const bool exact = n % W == 0 || W * W < (1u << 24);
+    return bm.L < (int)W && bm.L <= 256 && exact && mul < (1u << 24) ? (uint32_t)mul : 0;
+}
+
+// How the rows are laid over a workgroup: row groups of 1 << gsh lanes (8
+// columns each), nch chunks of columns per row, nrun rows walked at once.
 struct Hist2dShape {
-    int rows_per_wg, chunk_rows;
-    size_t lds;
+    int gsh, nch, nrun;
 };
 
-static Hist2dShape hist2d_shape(int L, int H, int W)
+// Words of the plane: word w holds cell w in its high half and the cell
+// hist2d_words later in its low half, so that a wavefront's words are
+// neighbouring cells twice.
+__host__ __device__ inline int hist2d_words(int L) { return (L + 1) / 2 * L; }
+
+// Bounded by its vector operations (24 per pixel, 51 when the gray levels were
+// staged in LDS as bytes and summed one by one), then by adding up the planes:
+// 300 images of 512 x 512 at 256 levels 214 -> 88 us (of 48 us of vector issue
+// at one wavefront instruction per four clocks), 37 of 301 x 415 at 200 levels
+// 53 -> 25 us, 120 residue images of 512 x 512 115 -> 48 us.  Before, 65535
+// pixels were counted between two additions of a plane's cells to the cleared
+// histogram, and one band of an image per workgroup left the last round of
+// workgroups short.  A row loop that copied its loaded registers at the end
+// waited there for the load: 99 us.
+template <int KIND, bool RAGGED>
+__global__ void __launch_bounds__(H2_THREADS) k_hist2d(const int16_t *const *__restrict__ vox, int nseg, int whole,
+                                                       int parts, int H, int W, Hist2dShape sh, BinMap bm, uint32_t mul24,
+                                                       uint32_t *__restrict__ hist)
 {
-    Hist2dShape sh;
-    const int max_rows = std::max(1, std::min(H, 65535 / std::max(W, 1)));
-    const int bands = (H + max_rows - 1) / max_rows;
-    sh.rows_per_wg = (H + bands - 1) / bands;
-    const int base = hist2d_rows_offset(L);
-    const int fit = std::max(3, (H2_LDS - base) / std::max(W, 1)); // staged rows that fit (>= 3 by the launch check)
-    int chunk = std::max(1, std::min(fit - 2, sh.rows_per_wg));
-    const int nch = (sh.rows_per_wg + chunk - 1) / chunk;
-    chunk = (sh.rows_per_wg + nch - 1) / nch;
-    sh.chunk_rows = chunk;
-    sh.lds = (size_t)base + (size_t)(chunk + 2) * W;
-    return sh;
+    // [words of the plane | two corner sums | the sweep's per-wavefront maxima]
+    extern __shared__ uint32_t sm[];
+    const int L = bm.L, nw2 = hist2d_words(L);
+    uint32_t *plane = sm;
+    const int nw4 = (nw2 + 3) & ~3; // the words past the plane stay 0
+    uint4 *plane4 = reinterpret_cast<uint4 *>(sm);
+    uint32_t *corner = plane + nw4, *wmax = corner + 2;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    // this lane's row group: chunk of columns and run of rows
+    const int grp = (wv << (6 - sh.gsh)) + (lane >> sh.gsh);
+    const int chunk = grp % sh.nch, runid = grp / sh.nch; // runid >= nrun: idle (nch need not divide the groups)
+    const int x0 = (chunk << (sh.gsh + 3)) + ((lane & ((1 << sh.gsh) - 1)) << 3);
+    const int nv = runid < sh.nrun ? min(8, W - x0) : 0; // columns of this lane (<= 0: none)
+    const bool at_left = x0 == 0, at_right = x0 + 8 >= W;
+    const int xl = nv > 0 ? x0 : 0;                               // column this lane loads
+    const bool g_first = (lane & ((1 << sh.gsh) - 1)) == 0, g_last = ((lane + 1) & ((1 << sh.gsh) - 1)) == 0;
+    const int xe = min(max(g_first ? xl - 1 : xl + 8, 0), W - 1); // and beside its chunk (nch > 1)
+    const int edge = (W - 1) & 7; // last column's place in its lane
+    const int64_t npix = (int64_t)H * W;
+    const u16x2 half2 = {(unsigned short)((L + 1) / 2), (unsigned short)((L + 1) / 2)};
+    const uint32_t fmul = (uint32_t)L << 15, top = 9u * (uint32_t)(L - 1) * 0x10001u;
+
+    for (int i = threadIdx.x; i < nw4 / 4; i += blockDim.x)
+        plane4[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (threadIdx.x < 2)
+        corner[threadIdx.x] = 0u;
+    __syncthreads();
+
+    // the largest cell of the plane, for the whole workgroup
+    auto plane_max = [&]() {
+        u16x2 m = {0, 0};
+        for (int i = threadIdx.x; i < nw4 / 4; i += blockDim.x) {
+            const uint4 w4 = plane4[i];
+            m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w4.x));
+            m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w4.y));
+            m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w4.z));
+            m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w4.w));
+        }
+        uint32_t mx = max((uint32_t)m[0], (uint32_t)m[1]);
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1)
+            mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, 64));
+        if (lane == 0)
+            wmax[wv] = mx;
+        __syncthreads();
+        for (int v = 0; v < H2_THREADS / 64; ++v)
+            mx = max(mx, wmax[v]);
+        __syncthreads(); // wmax is read before the next call writes it
+        return mx;
+    };
+
+    // rows [ra, rb) of image s counted into the plane and added to (or, for a
+    // whole image, stored as) its histogram; the plane is zero before and after
+    auto process = [&](int s, int ra, int rb, bool store) {
+        const TS_GLOBAL int16_t *img = gp(vox[s]);
+        uint32_t *hs = hist + (int64_t)s * L * L;
+        const int run = (rb - ra + sh.nrun - 1) / sh.nrun;
+        const int y0 = ra + runid * run, y1 = min(rb, y0 + run); // this lane's rows
+        const int ya = y0 - 2, steps_all = run + 2; // two rows before them fill the running sums
+        auto load = [&](int y, v4i &raw, int &ext) {
+            const int64_t at = (int64_t)min(max(y, 0), H - 1) * W;
+            const int64_t p = min(at + xl, npix - 8); // not past the image's end
+            raw = *reinterpret_cast<const TS_GLOBAL v4i_any *>(img + p);
+            if (RAGGED) {
+                const int sh16 = (int)(at + xl - p); // pixels to shift out: the image's last rows only
+                if (__any(sh16)) {
+                    uint32_t e[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        e[j] = (uint32_t)raw[j];
+#pragma unroll
+                    for (int n = 4; n >= 1; n >>= 1) {
+                        const bool on = sh16 & n;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const uint32_t up = n == 1 ? (j < 3 ? pair_mid(e[j], e[j + 1]) : e[3] >> 16)
+                                                       : (j + n / 2 < 4 ? e[(j + n / 2) & 3] : 0u);
+                            e[j] = on ? up : e[j];
+                        }
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        raw[j] = (int)e[j];
+                }
+            }
+            ext = 0;
+            if (sh.nch > 1) // the columns beside the chunk, for its end lanes
+                ext = img[at + xe];
+        };
+        // gray levels and row sums of three of a loaded row
+        auto sums = [&](const v4i &raw, int ext, uint32_t(&l)[4], uint32_t(&h)[4]) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                l[j] = levels2<KIND>((uint32_t)raw[j], bm, mul24);
+            // all four formed here: raw is free for the next load, which must not
+            // wait for a copy of it at the loop's end
+            asm volatile("" : "+v"(l[0]), "+v"(l[1]), "+v"(l[2]), "+v"(l[3]));
+            if (RAGGED) { // columns past the row's end repeat its last
+                uint32_t prev = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t a = 2 * j <= edge ? l[j] & 0xffffu : prev;
+                    prev = 2 * j + 1 <= edge ? l[j] >> 16 : a;
+                    l[j] = at_right ? a | prev << 16 : l[j];
+                }
+            }
+            uint32_t before = dpp32<0x138, 0xf>(l[3]), after = dpp32<0x130, 0xf>(l[0]); // lane - 1, lane + 1
+            if (sh.nch > 1) {
+                const uint32_t e = levels2<KIND>((uint32_t)ext & 0xffffu, bm, mul24) & 0xffffu;
+                before = g_first ? e << 16 : before;
+                after = g_last ? e : after;
+            }
+            before = at_left ? l[0] << 16 : before;
+            after = at_right ? l[3] >> 16 : after;
+            uint32_t m[5];
+            m[0] = pair_mid(before, l[0]);
+#pragma unroll
+            for (int j = 1; j < 4; ++j)
+                m[j] = pair_mid(l[j - 1], l[j]);
+            m[4] = pair_mid(l[3], after);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                h[j] = pk_add(pk_add(m[j], l[j]), m[j + 1]);
+        };
+        uint32_t hot0 = 0, hot1 = 0;
+        uint32_t h2[4] = {}, hc[4] = {}, lc[4] = {}; // row sums of rows y-1 and y together, of row y; levels at y
+        v4i raw[2];
+        int ext[2];
+        load(y0 - 1, raw[0], ext[0]);
+        load(y0, raw[1], ext[1]);
+        // one row: the row below arrives in raw (row y + 3 is loaded in its
+        // place), its sums complete the 3 x 3 sums of row y.  The two rows
+        // before the first only fill the running sums.
+        auto row = [&](int y, v4i &rw, int &ex) {
+            uint32_t ln[4], hn[4], t[4];
+            sums(rw, ex, ln, hn);
+            load(y + 3, rw, ex);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                t[j] = pk_add(h2[j], hn[j]);
+            if (nv > 0 && y >= y0 && y < y1) {
+                if ((t[0] | t[1] | t[2] | t[3]) == 0u && (!RAGGED || nv == 8)) {
+                    hot0 += 8;
+                } else if (((t[0] ^ top) | (t[1] ^ top) | (t[2] ^ top) | (t[3] ^ top)) == 0u && (!RAGGED || nv == 8)) {
+                    hot1 += 8;
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        // levels from half on move to the low halves: f - half, which
+                        // wraps past 2^15 for the levels below (kept as they are, by
+                        // the unsigned minimum), whose increments shift by 16
+                        const u16x2 l2 = __builtin_bit_cast(u16x2, lc[j]), x2 = l2 - half2;
+                        const uint32_t f = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(l2, x2));
+                        const uint32_t up = __builtin_bit_cast(uint32_t, x2 >> (u16x2){11, 11}) & 0x100010u;
+                        // word f L + floor(sum / 9) in units of 2^-15: 3641 / 2^15 is
+                        // 1/9 closely enough for every sum up to 9 * 255
+                        const uint32_t c0 = __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, t[j]), (u16x2){3641, 0},
+                                                                   __umul24(f & 0xffffu, fmul), false);
+                        const uint32_t c1 = __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, t[j]), (u16x2){0, 3641},
+                                                                   __umul24(f >> 16, fmul), false);
+                        if (!RAGGED || 2 * j < nv)
+                            atomicAdd(plane + (c0 >> 15), 1u << (up & 0xffffu));
+                        if (!RAGGED || 2 * j + 1 < nv)
+                            atomicAdd(plane + (c1 >> 15), 1u << (up >> 16));
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                h2[j] = pk_add(hc[j], hn[j]);
+                hc[j] = hn[j];
+                lc[j] = ln[j];
+            }
+        };
+        // Every cell is at most 65535 minus the budget before each stretch of
+        // rows, and the workgroup counts at most nrun * W <= 8192 pixels per
+        // row step, so no half-word overflows.
+        uint32_t budget = 65535u;
+        for (int i0 = 0;;) {
+            const int steps = min((int)(budget / (uint32_t)(sh.nrun * W)), steps_all - i0); // >= 4 or the rest
+            for (int i = 0; i + 1 < steps; i += 2) {
+                row(ya + i0 + i, raw[0], ext[0]);
+                row(ya + i0 + i + 1, raw[1], ext[1]);
+            }
+            i0 += steps;
+            if (steps & 1) { // the row after it is in raw[1]
+                row(ya + i0 - 1, raw[0], ext[0]);
+                const v4i rt = raw[0];
+                const int et = ext[0];
+                raw[0] = raw[1];
+                ext[0] = ext[1];
+                raw[1] = rt;
+                ext[1] = et;
+            }
+            __syncthreads();
+            if (i0 >= steps_all)
+                break;
+            uint32_t mx = (uint32_t)__builtin_amdgcn_readfirstlane((int)plane_max());
+            if (mx >= 32768u) { // rare: cells from there up move to the histogram
+                if (store) { // which is not cleared yet for a whole image
+                    for (int i = threadIdx.x; i < L * L; i += blockDim.x)
+                        hs[i] = 0u;
+                    __threadfence();
+                    store = false;
+                    __syncthreads();
+                }
+                for (int i = threadIdx.x; i < nw2; i += blockDim.x) {
+                    const uint32_t w2 = plane[i];
+                    uint32_t keep = w2;
+                    if (w2 & 0x8000u) {
+                        atomicAdd(&hs[nw2 + i], w2 & 0xffffu);
+                        keep &= 0xffff0000u;
+                    }
+                    if (w2 & 0x80000000u) {
+                        atomicAdd(&hs[i], w2 >> 16);
+                        keep &= 0xffffu;
+                    }
+                    if (keep != w2)
+                        plane[i] = keep;
+                }
+                mx = 32767u;
+                __syncthreads();
+            }
+            budget = 65535u - mx;
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) {
+            hot0 += __shfl_xor(hot0, o, 64);
+            hot1 += __shfl_xor(hot1, o, 64);
+        }
+        if (lane == 0) {
+            atomicAdd(&corner[0], hot0);
+            atomicAdd(&corner[1], hot1);
+        }
+        __syncthreads();
+        const int last = L * L - 1;
+        if (store) {
+            const bool vec = (nw2 & 3) == 0 && (L & 1) == 0 && ((uintptr_t)hs & 15) == 0;
+            for (int i = threadIdx.x; i < nw4 / 4; i += blockDim.x) { // 4 words: 4 cells of each half
+                const uint4 w4 = plane4[i];
+                plane4[i] = make_uint4(0u, 0u, 0u, 0u);
+                uint32_t c[4] = {w4.x >> 16, w4.y >> 16, w4.z >> 16, w4.w >> 16};
+                uint32_t d[4] = {w4.x & 0xffffu, w4.y & 0xffffu, w4.z & 0xffffu, w4.w & 0xffffu};
+                c[0] += i == 0 ? corner[0] : 0u;
+                if ((last - nw2) >> 2 == i) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        d[j] += ((last - nw2) & 3) == j ? corner[1] : 0u;
+                }
+                if (vec) {
+                    *reinterpret_cast<uint4 *>(hs + 4 * i) = make_uint4(c[0], c[1], c[2], c[3]);
+                    *reinterpret_cast<uint4 *>(hs + nw2 + 4 * i) = make_uint4(d[0], d[1], d[2], d[3]);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (4 * i + j < nw2)
+                            hs[4 * i + j] = c[j];
+                        if (4 * i + j < nw2 && nw2 + 4 * i + j <= last)
+                            hs[nw2 + 4 * i + j] = d[j];
+                    }
+                }
+            }
+        } else {
+            for (int i = threadIdx.x; i < nw2; i += blockDim.x) {
+                const uint32_t w2 = plane[i];
+                plane[i] = 0u;
+                if (w2 >> 16)
+                    atomicAdd(&hs[i], w2 >> 16);
+                if (w2 & 0xffffu) // a half past the last cell counts nothing
+                    atomicAdd(&hs[nw2 + i], w2 & 0xffffu);
+            }
+            if (threadIdx.x < 2 && corner[threadIdx.x])
+                atomicAdd(&hs[threadIdx.x ? last : 0], corner[threadIdx.x]);
+        }
+        __syncthreads();
+        if (threadIdx.x < 2)
+            corner[threadIdx.x] = 0u;
+        __syncthreads();
+    };
+    // whole images first, then a share of the rest's rows: an equal part of
+    // one image, or of all their rows in turn
+    const int64_t rest = (int64_t)(nseg - whole) * H;
+    int64_t r, r1;
+    if (parts > 0) {
+        const int s = blockIdx.x / parts, j = blockIdx.x % parts;
+        r = min(rest, (int64_t)s * H + (int64_t)H * j / parts);
+        r1 = min(rest, (int64_t)s * H + (int64_t)H * (j + 1) / parts);
+    } else {
+        r = rest * blockIdx.x / gridDim.x;
+        r1 = rest * (blockIdx.x + 1) / gridDim.x;
+    }
+    for (int i = blockIdx.x;; i += gridDim.x) {
+        const bool all = i < whole;
+        if (!all && r >= r1)
+            break;
+        const int s = all ? i : (int)(whole + r / H), ra = all ? 0 : (int)(r % H);
+        const int rb = all ? H : (int)min((int64_t)H, ra + (r1 - r));
+        process(s, ra, rb, all);
+        r += all ? 0 : rb - ra;
+    }
 }
 
-size_t hist2d_lds_bytes(int L, int H, int W) { return hist2d_shape(L, H, W).lds; }
+// Images of fewer than 8 pixels: one thread per pixel.
+__global__ void __launch_bounds__(256) k_hist2d_tiny(const int16_t *const *__restrict__ vox, int nseg, int H, int W,
+                                                     BinMap bm, uint32_t *__restrict__ hist)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int s = (int)(i >> 3), p = (int)(i & 7);
+    if (s >= nseg || p >= H * W)
+        return;
+    const TS_GLOBAL int16_t *img = gp(vox[s]);
+    const int y = p / W, x = p % W;
+    int sum = 0;
+    for (int dy = -1; dy <= 1; ++dy)
+        for (int dx = -1; dx <= 1; ++dx)
+            sum += bin_of(img[min(max(y + dy, 0), H - 1) * W + min(max(x + dx, 0), W - 1)], bm);
+    atomicAdd(&hist[(int64_t)s * bm.L * bm.L + bin_of(img[p], bm) * bm.L + sum / 9], 1u);
+}
 
 ts_status launch_hist2d(const ts_batch &b, int H, int W, const BinMap &bm, uint32_t *hist, hipStream_t st)
 {
     if (W > H2_MAX_W || bm.L > H2_MAX_L)
         return fail(TS_ERR_INVALID_ARG, "ts_histogram2d: width or nbins beyond the LDS layout");
-    const int64_t n = (int64_t)b.nseg * bm.L * bm.L;
-    {
-        ts_status e = launch_fill_u32(hist, n, st);
+    if ((int64_t)H * W < 8) { // no 8 pixels to load together
+        ts_status e = launch_fill_u32(hist, (int64_t)b.nseg * bm.L * bm.L, st);
+        if (e != TS_OK)
+            return e;
+        hipLaunchKernelGGL(k_hist2d_tiny, dim3((unsigned)(((int64_t)b.nseg * 8 + 255) / 256)), dim3(256), 0, st, b.vox,
+                           b.nseg, H, W, bm, hist);
+        return check_launch("ts_histogram2d");
+    }
+    // Row groups of 16, 32 or 64 lanes: those that leave the fewest lanes
+    // without columns, several chunks per row counted a sixteenth dearer (the
+    // columns beside a chunk are loaded apart).  552 columns are 69 lanes: 12
+    // rows of five 16-lane chunks at once keep 828 of 1024 lanes, 8 rows of two
+    // wavefronts 552.
+    Hist2dShape sh{6, 1, 1};
+    const int lanes = (W + 7) / 8;
+    for (int g = 6, best = 0; g >= 4; --g) {
+        const int nch = (lanes + (1 << g) - 1) >> g, nrun = (H2_THREADS >> g) / nch;
+        const int score = nrun * lanes * (nch > 1 ? 15 : 16);
+        if (score > best) {
+            best = score;
+            sh = Hist2dShape{g, nch, nrun};
+        }
+    }
+    // Workgroups: one per CU, with at least H2_MIN_ROWS rows each (clearing
+    // and adding up the plane takes as long as counting about as many).
+    const int64_t rows = (int64_t)b.nseg * H;
+    const int nwg = (int)std::max<int64_t>(1, std::min<int64_t>(device_cu_count(), rows / H2_MIN_ROWS));
+    // Whole images first, as many as fill every workgroup equally: those store
+    // their histograms; the rest's rows are split evenly and added to cleared
+    // histograms.
+    const int whole = b.nseg / nwg * nwg;
+    // A workgroup whose rows cross into another image adds up two planes, 5 to
+    // 10 us each: parts that keep to one image, unless they leave more than an
+    // eighth of the workgroups idle.
+    const int rest = b.nseg - whole;
+    const int parts = rest && nwg / rest * rest * 8 >= nwg * 7 ? nwg / rest : 0;
+    if (whole < b.nseg) {
+        ts_status e = launch_fill_u32(hist + (int64_t)whole * bm.L * bm.L, (int64_t)(b.nseg - whole) * bm.L * bm.L, st);
         if (e != TS_OK)
             return e;
     }
-    const Hist2dShape sh = hist2d_shape(bm.L, H, W);
-    const int rows = sh.rows_per_wg, chunk = sh.chunk_rows;
-    const size_t lds = sh.lds;
-    const int bands = (H + rows - 1) / rows;
-    const dim3 g((unsigned)((int64_t)b.nseg * bands)), blk(H2_THREADS);
-#define TS_H2(M)                                                                                                    \
-    allow_dynamic_lds((const void *)k_hist2d<M>, lds);                                                            \
-    hipLaunchKernelGGL(k_hist2d<M>, g, blk, lds, st, b.vox, b.nseg, H, W, rows, chunk, bm, hist)
-    switch (map_kind(bm)) {
-    case 0: TS_H2(0); break;
-    case 1: TS_H2(1); break;
-    case 2: TS_H2(2); break;
-    default: TS_H2(3); break;
+    const size_t lds = ((size_t)((hist2d_words(bm.L) + 3) & ~3) + 2 + H2_THREADS / 64) * 4;
+    const uint32_t mul24 = hist2d_mul24(bm);
+    const bool same = bm.hi - bm.lo + 1 == bm.L;
+    const dim3 g((unsigned)nwg), blk(H2_THREADS);
+#define TS_H2(K, R)                                                                                                 \
+    allow_dynamic_lds((const void *)k_hist2d<K, R>, lds);                                                         \
+    hipLaunchKernelGGL((k_hist2d<K, R>), g, blk, lds, st, b.vox, b.nseg, whole, parts, H, W, sh, bm,   \
+                       mul24, hist)
+    if (W % 8 == 0) {
+        if (same) { TS_H2(0, false); } else if (mul24) { TS_H2(1, false); } else { TS_H2(2, false); }
+    } else {
+        if (same) { TS_H2(0, true); } else if (mul24) { TS_H2(1, true); } else { TS_H2(2, true); }
     }
 #undef TS_H2
     return check_launch("ts_histogram2d");
@@ -251,13 +528,6 @@ __device__ __forceinline__ double cterm(uint32_t c, double q)
 // out of line for the rare counts past the table (small code in the row loops)
 __device__ __noinline__ double cterm_big(uint32_t c, double q) { return cterm(c, q); }
 
-// Cross-lane moves within the wavefront (DPP): lanes without a source, or in
-// rows masked off, receive 0, the identity of the sums below.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t dpp32(uint32_t v)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
-}
 template <int CTRL, int ROWS>
 __device__ __forceinline__ uint64_t dpp64(uint64_t v)
 {
