@@ -14,20 +14,19 @@
 // all lie in a clamp corner ((0, 0) or (L-1, L-1), a large share of the pixels
 // under a narrow window) count in a register instead of one hot address.
 //
-// k_search2d: one workgroup of four wavefronts per (q index, problem); the
-// rows holding counts are split into four blocks, one per wavefront, four
-// columns per lane.  Class 2 sums are accumulated bottom-up over rows and
-// class 1 sums top-down; a wavefront starts its block from the carried sums
-// of the blocks before it in that direction (each block's column totals,
-// summed along s, exchanged through LDS), so the four walk their rows at
-// once.  FP32 keys of every pair, then an FP64 re-check of the rows whose
-// best key is within the keys' error bound of the maximum, from the same
-// sums; the first best FP64 pair wins (t outermost).  Sums along s are
-// fixed-order scans, and an empty cell (or an empty column of a block's
-// totals) takes the sum of the last occupied one, so a whole empty column or
-// row leaves every class sum unchanged bit for bit and the pairs it
-// separates tie exactly.  q = 1 is the Shannon limit, as in the
-// one-dimensional search.
+// k_search2d: one workgroup per (q index, problem); the rows holding counts
+// are split into blocks, one per wavefront, four columns per lane.  Class 2
+// sums are accumulated bottom-up over rows and class 1 sums top-down; a
+// wavefront starts its block from the carried sums of the blocks before it in
+// that direction (every block's column totals, added up over the blocks in
+// both directions and summed along s, exchanged through LDS), so all walk
+// their rows at once.  FP32 keys of every pair, then an FP64 re-check of the
+// rows whose best key is within the keys' error bound of the maximum, from the
+// same sums; the first best FP64 pair wins (t outermost).  Sums along s are
+// fixed-order scans, and an empty cell (or an empty column of the totals)
+// takes the sum of the last occupied one, so a whole empty column or row
+// leaves every class sum unchanged bit for bit and the pairs it separates tie
+// exactly.  q = 1 is the Shannon limit, as in the one-dimensional search.
 #include <math.h>
 
 #include <algorithm>
@@ -43,11 +42,9 @@ constexpr int H2_THREADS = 1024;
 constexpr int H2_MAX_W = 4096;    // widest row
 constexpr int H2_MAX_L = 256;     // 2D histograms up to 256 x 256
 constexpr int H2_MIN_ROWS = 16;   // rows a workgroup takes at least
-constexpr int S2_WAVES = 4;       // wavefronts per (q, image), each a block of the rows
-constexpr int S2_THREADS = 64 * S2_WAVES;
 constexpr int S2_CPL = 4;         // columns per lane (L <= 256)
-constexpr int S2_TAB = 2048;      // p^q (or p ln p) of counts below this from an LDS table
-constexpr int S2_RING = 3;        // rows of counts in flight ahead of the row being summed
+constexpr int S2_TAB = 1024;      // p^q (or p ln p) of counts below this from an LDS table
+constexpr int S2_RING = 2;        // rows of counts in flight ahead of the row being summed
 
 // ------------------------------------------------------------------ histogram
 
@@ -525,9 +522,6 @@ __device__ __forceinline__ double cterm(uint32_t c, double q)
     return q == 1.0 ? x * log(x) : pow(x, q);
 }
 
-// out of line for the rare counts past the table (small code in the row loops)
-__device__ __noinline__ double cterm_big(uint32_t c, double q) { return cterm(c, q); }
-
 template <int CTRL, int ROWS>
 __device__ __forceinline__ uint64_t dpp64(uint64_t v)
 {
@@ -562,14 +556,14 @@ __device__ __forceinline__ T wave_excl_sum(T v)
 
 // Sums along s of one 2D histogram row, S2_CPL cells per lane: scan position
 // p = S2_CPL * lane + u (u = 0 .. S2_CPL-1) is column p (prefix order) or
-// column L-1-p (suffix order).  For every position the exact count sum and
-// the FP64 sum of cterm up to it: within the lane sequentially, after the
+// column L-1-p (suffix order); c the counts, t their terms.  For every position
+// the exact count sum and the FP64 sum of cterm up to it: within the lane sequentially, after the
 // lane's exclusive base.  An empty position takes the value at the nearest
 // occupied position before it in scan order, so an all-empty column never
 // changes a class sum (bit for bit) and the pairs it separates tie.
 template <typename CT>
-__device__ __forceinline__ void row_sums(const uint32_t (&c)[S2_CPL], const double *tab, double q,
-                                         CT (&rc)[S2_CPL], double (&rq)[S2_CPL])
+__device__ __forceinline__ void row_sums(const uint32_t (&c)[S2_CPL], const double (&t)[S2_CPL], CT (&rc)[S2_CPL],
+                                         double (&rq)[S2_CPL])
 {
     const int lane = threadIdx.x & 63;
     CT lc = 0;
@@ -577,22 +571,6 @@ __device__ __forceinline__ void row_sums(const uint32_t (&c)[S2_CPL], const doub
     int first = S2_CPL; // first occupied position of this lane
     CT pc[S2_CPL];
     double pq[S2_CPL];
-    // cterm from the table tab[c] for small counts (the table holds the
-    // identical expression, so both give the same bits); a count past the
-    // table anywhere in the row takes the out-of-line path
-    double t[S2_CPL];
-    bool big = false;
-#pragma unroll
-    for (int u = 0; u < S2_CPL; ++u) {
-        t[u] = tab[min(c[u], (uint32_t)S2_TAB - 1u)];
-        big |= c[u] >= (uint32_t)S2_TAB;
-    }
-    if (__ballot(big)) {
-#pragma unroll
-        for (int u = 0; u < S2_CPL; ++u)
-            if (c[u] >= (uint32_t)S2_TAB)
-                t[u] = cterm_big(c[u], q);
-    }
 #pragma unroll
     for (int u = 0; u < S2_CPL; ++u) {
         lc += (CT)c[u];
@@ -621,14 +599,15 @@ __device__ __forceinline__ void row_sums(const uint32_t (&c)[S2_CPL], const doub
 // of cterm; a block's column totals): exact count prefix, FP64 prefix in
 // the lane then after its exclusive base, an empty position taking the
 // value at the nearest occupied position before it.
-__device__ __forceinline__ void pos_sums(const uint64_t (&cc)[S2_CPL], const double (&cq)[S2_CPL],
-                                         uint64_t (&rc)[S2_CPL], double (&rq)[S2_CPL])
+template <typename CT>
+__device__ __forceinline__ void pos_sums(const CT (&cc)[S2_CPL], const double (&cq)[S2_CPL], CT (&rc)[S2_CPL],
+                                         double (&rq)[S2_CPL])
 {
     const int lane = threadIdx.x & 63;
-    uint64_t lc = 0;
+    CT lc = 0;
     double lq = 0.0;
     int first = S2_CPL;
-    uint64_t pc[S2_CPL];
+    CT pc[S2_CPL];
     double pq[S2_CPL];
 #pragma unroll
     for (int u = 0; u < S2_CPL; ++u) {
@@ -640,7 +619,7 @@ __device__ __forceinline__ void pos_sums(const uint64_t (&cc)[S2_CPL], const dou
             first = u;
     }
     const uint64_t occ = __ballot(lc != 0);
-    const uint64_t bc = wave_excl_sum<uint64_t>(lc);
+    const CT bc = wave_excl_sum<CT>(lc);
     const double bq = wave_excl_sum<double>(lq);
     const double last = bq + lq;
     const uint64_t before = occ & ((1ull << lane) - 1ull);
@@ -656,16 +635,27 @@ __device__ __forceinline__ void pos_sums(const uint64_t (&cc)[S2_CPL], const dou
 
 // FP64 class term from the class sums: sgn(1-q) (ln S - q ln C) for Tsallis,
 // ln C - S / C for q = 1 (S = sum of cterm, C = pixels); -inf for an empty
-// class; clamped to [0, hmax].  Called only for the few rows the FP64
-// re-check visits: kept out of line so that its registers do not burden the
-// FP32 passes.
-__device__ __noinline__ double class_term2(uint64_t c, double sumq, double q, double sgn, double hmax)
+// class; clamped to [0, hmax].
+__device__ __forceinline__ double class_term2(uint64_t c, double sumq, double q, double sgn, double hmax)
 {
     if (c == 0)
         return -INFINITY;
     const double C = (double)c;
     const double h = sgn == 0.0 ? log(C) - sumq / C : sgn * (log(sumq) - q * log(C));
     return fmin(fmax(h, 0.0), hmax);
+}
+
+// A value that is the same in every lane, held in scalar registers.
+__device__ __forceinline__ float uniform(float v)
+{
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+__device__ __forceinline__ double uniform(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
 // Per-problem constants of the search.
@@ -675,6 +665,7 @@ struct S2 {
     bool vec;          // rows load as 16-byte vectors (L % 4 == 0, aligned)
     double q, sgn, hmax;
     const double *tab; // cterm of counts below S2_TAB
+    double *big;       // cterm of the cells with larger counts, [L][L] (workspace, t2's place until pass 3)
     const uint32_t *band; // per row: lowest | highest column holding counts << 16 (LDS)
     float mq;          // -q rounded to FP32 (Tsallis)
     float sg;          // sgn(1-q) as +-1 (Tsallis)
@@ -765,6 +756,44 @@ __device__ __forceinline__ void load_row(const uint32_t *h, int L, bool vec, int
     }
 }
 
+// Element u of an array in registers.
+template <typename T>
+__device__ __forceinline__ T pick(const T (&v)[S2_CPL], int u)
+{
+    return u == 0 ? v[0] : u == 1 ? v[1] : u == 2 ? v[2] : v[3];
+}
+
+// The terms of a row's counts: from the table for small counts (which holds
+// the identical expression, so both give the same bits), else from what
+// block_totals left in the workspace, or formed anew (POW).
+template <int DIR, bool POW>
+__device__ __forceinline__ void row_terms(const S2 &p, int t, const uint32_t (&c)[S2_CPL], double (&term)[S2_CPL])
+{
+    bool big = false;
+#pragma unroll
+    for (int u = 0; u < S2_CPL; ++u) {
+        term[u] = p.tab[min(c[u], (uint32_t)S2_TAB - 1u)];
+        big |= c[u] >= (uint32_t)S2_TAB;
+    }
+    if (__ballot(big)) {
+        if (POW) {
+#pragma unroll 1
+            for (int u = 0; u < S2_CPL; ++u) {
+                const double x = cterm(pick(c, u), p.q);
+#pragma unroll
+                for (int v = 0; v < S2_CPL; ++v)
+                    term[v] = v == u && c[v] >= (uint32_t)S2_TAB ? x : term[v];
+            }
+        } else {
+            const int pos = S2_CPL * (threadIdx.x & 63);
+#pragma unroll
+            for (int u = 0; u < S2_CPL; ++u)
+                if (c[u] >= (uint32_t)S2_TAB)
+                    term[u] = p.big[t * p.L + (DIR > 0 ? pos + u : p.L - 1 - (pos + u))];
+        }
+    }
+}
+
 // Visits n >= 0 rows of the compacted list of rows holding counts, rows[k0],
 // rows[k0 + DIR], ..., with each row's sums along s (row_sums, in DIR's scan
 // order) and S2_CPL auxiliary values aux(k, .) per lane (stored keys the row
@@ -788,30 +817,32 @@ __device__ __forceinline__ void for_rows(const S2 &p, const int *rows, int k0, i
 #pragma unroll
         for (int d = 0; d < S2_RING; ++d) {
             const int i = i0 + d;
-            uint32_t c[S2_CPL];
-            float x[S2_CPL];
+            if (i < n) { // uniform over the wavefront
+                uint32_t c[S2_CPL];
+                float x[S2_CPL];
 #pragma unroll
-            for (int u = 0; u < S2_CPL; ++u) {
-                c[u] = ring[d][u];
-                x[u] = xr[d][u];
-            }
-            const int kk = k0 + DIR * min(i + S2_RING, n - 1);
-            load_row<DIR>(p.h, p.L, p.vec, rows[kk], ring[d], p.band);
-            aux(kk, xr[d]);
-            CT rc[S2_CPL];
-            double rq[S2_CPL];
-            row_sums<CT>(c, p.tab, p.q, rc, rq);
-            if (i < n)
+                for (int u = 0; u < S2_CPL; ++u) {
+                    c[u] = ring[d][u];
+                    x[u] = xr[d][u];
+                }
+                const int kk = k0 + DIR * min(i + S2_RING, n - 1);
+                load_row<DIR>(p.h, p.L, p.vec, rows[kk], ring[d], p.band);
+                aux(kk, xr[d]);
+                CT rc[S2_CPL];
+                double rq[S2_CPL], t[S2_CPL];
+                row_terms<DIR, false>(p, rows[k0 + DIR * i], c, t);
+                row_sums<CT>(c, t, rc, rq);
                 f(k0 + DIR * i, rc, rq, x);
+            }
         }
     }
 }
 
-// Column totals of the listed rows rows[k0], rows[k0 + DIR], ... (n >= 0 of
-// them) in DIR's scan positions: count sums and sums of cterm, added in
-// walking order; the next S2_RING rows' loads in flight.
-template <int DIR>
-__device__ __forceinline__ void block_totals(const S2 &p, const int *rows, int k0, int n, uint64_t (&cc)[S2_CPL],
+// Column totals of the listed rows rows[k0 .. k0 + n - 1] for the lane's
+// columns S2_CPL * lane + u: count sums and sums of cterm; leaves the terms of
+// the counts past the table in p.big for the later walks.
+template <typename CT>
+__device__ __forceinline__ void block_totals(const S2 &p, const int *rows, int k0, int n, CT (&cc)[S2_CPL],
                                              double (&cq)[S2_CPL])
 {
 #pragma unroll
@@ -824,30 +855,31 @@ __device__ __forceinline__ void block_totals(const S2 &p, const int *rows, int k
     uint32_t ring[S2_RING][S2_CPL];
 #pragma unroll
     for (int d = 0; d < S2_RING; ++d)
-        load_row<DIR>(p.h, p.L, p.vec, rows[k0 + DIR * min(d, n - 1)], ring[d], p.band);
+        load_row<1>(p.h, p.L, p.vec, rows[k0 + min(d, n - 1)], ring[d], p.band);
     for (int i0 = 0; i0 < n; i0 += S2_RING) {
 #pragma unroll
         for (int d = 0; d < S2_RING; ++d) {
             const int i = i0 + d;
-            uint32_t c[S2_CPL];
-#pragma unroll
-            for (int u = 0; u < S2_CPL; ++u)
-                c[u] = ring[d][u];
-            load_row<DIR>(p.h, p.L, p.vec, rows[k0 + DIR * min(i + S2_RING, n - 1)], ring[d], p.band);
             if (i < n) {
+                uint32_t c[S2_CPL];
                 double t[S2_CPL];
                 bool big = false;
 #pragma unroll
                 for (int u = 0; u < S2_CPL; ++u) {
-                    t[u] = p.tab[min(c[u], (uint32_t)S2_TAB - 1u)];
+                    c[u] = ring[d][u];
                     big |= c[u] >= (uint32_t)S2_TAB;
                 }
+                load_row<1>(p.h, p.L, p.vec, rows[k0 + min(i + S2_RING, n - 1)], ring[d], p.band);
                 if (__ballot(big)) {
-#pragma unroll
-                    for (int u = 0; u < S2_CPL; ++u)
-                        if (c[u] >= (uint32_t)S2_TAB)
-                            t[u] = cterm_big(c[u], p.q);
+                    const int at = rows[k0 + i] * p.L + S2_CPL * (threadIdx.x & 63);
+#pragma unroll 1
+                    for (int u = 0; u < S2_CPL; ++u) {
+                        const uint32_t x = pick(c, u);
+                        if (x >= (uint32_t)S2_TAB) // skipped where no lane's u is
+                            p.big[at + u] = cterm(x, p.q);
+                    }
                 }
+                row_terms<1, false>(p, rows[k0 + i], c, t);
 #pragma unroll
                 for (int u = 0; u < S2_CPL; ++u) {
                     cc[u] += c[u];
@@ -881,138 +913,162 @@ __device__ __forceinline__ float wave_max_f32(float v)
 }
 
 // LDS of one (q index, problem).
+template <int NW, typename CT>
 struct S2Lds {
-    double tab[S2_TAB];                   // cterm of counts below S2_TAB
-    uint32_t band[H2_MAX_L];              // each row's band of columns holding counts
-    int rows[H2_MAX_L];                   // rows holding counts, increasing
-    float rmax[H2_MAX_L];                 // best pair key of each listed row
-    uint64_t tc[2][S2_WAVES][H2_MAX_L];   // block totals along s: [0] class 2 blocks, [1] class 1 blocks
-    double tq[2][S2_WAVES][H2_MAX_L];
-    float wm[S2_WAVES];                   // per-wavefront maxima
-    double wb[S2_WAVES];                  // per-wavefront best FP64 pair
-    long long wcode[S2_WAVES];
+    double tab[S2_TAB];               // cterm of counts below S2_TAB
+    double tq[2][NW][H2_MAX_L];       // per block and column: sums of cterm of the blocks before ([0]) and after ([1])
+    CT tc[NW + 1][H2_MAX_L];          // count sums of the blocks before (exact: those after are the rest)
+    uint32_t band[H2_MAX_L];          // each row's band of columns holding counts
+    int rows[H2_MAX_L];               // rows holding counts, increasing
+    float rmax[H2_MAX_L];             // best pair key of each listed row
+    float wm[NW];                     // per-wavefront maxima
+    double wb[NW];                    // per-wavefront best FP64 pair
+    long long wcode[NW];
+    int nrows;
 };
 
-// Block w of n listed rows starting at k0 in one of S2_WAVES equal parts.
-__device__ __forceinline__ int s2_block(int k0, int n, int w) { return k0 + (int)(((int64_t)n * w) / S2_WAVES); }
-
-// This wavefront's block totals along s (its lane's scan positions) into
-// LDS, from its rows rows[k0], rows[k0 + DIR], ... (n of them).
-template <int DIR>
-__device__ __forceinline__ void store_block_totals(const S2 &p, const int *rows, int k0, int n, uint64_t *tc,
-                                                   double *tq)
+// The class sums carried into block w in DIR's scan positions: class 1 (DIR =
+// +1) from the blocks above, class 2 (DIR = -1) from those below.
+template <int DIR, int NW, typename CT>
+__device__ __forceinline__ void carry_in(const S2Lds<NW, CT> &sh, int L, int w, CT (&ac)[S2_CPL],
+                                         double (&aq)[S2_CPL])
 {
-    const int lane = threadIdx.x & 63;
-    uint64_t cc[S2_CPL], rc[S2_CPL];
-    double cq[S2_CPL], rq[S2_CPL];
-    block_totals<DIR>(p, rows, k0, n, cc, cq);
-    pos_sums(cc, cq, rc, rq);
+    CT cc[S2_CPL];
+    double cq[S2_CPL];
 #pragma unroll
     for (int u = 0; u < S2_CPL; ++u) {
-        const int pos = S2_CPL * lane + u;
-        if (pos < H2_MAX_L) {
-            tc[pos] = rc[u];
-            tq[pos] = rq[u];
-        }
+        const int pos = S2_CPL * (threadIdx.x & 63) + u, col = DIR > 0 ? pos : L - 1 - pos;
+        const bool ok = col >= 0 && col < L;
+        const CT n = DIR > 0 ? sh.tc[w][ok ? col : 0] : (CT)(sh.tc[NW][ok ? col : 0] - sh.tc[w + 1][ok ? col : 0]);
+        cc[u] = ok ? n : 0;
+        cq[u] = ok ? sh.tq[DIR > 0 ? 0 : 1][w][ok ? col : 0] : 0.0;
     }
+    pos_sums<CT>(cc, cq, ac, aq);
 }
 
-// The sums carried into block w: the block totals of blocks v0, v0 + dv, ...
-// up to (not including) w, added in that order.
-template <typename CT>
-__device__ __forceinline__ void carry_in(const uint64_t (*tc)[H2_MAX_L], const double (*tq)[H2_MAX_L], int v0,
-                                         int dv, int w, CT (&ac)[S2_CPL], double (&aq)[S2_CPL])
-{
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int u = 0; u < S2_CPL; ++u) {
-        ac[u] = 0;
-        aq[u] = 0.0;
-    }
-    for (int v = v0; v != w; v += dv) {
-#pragma unroll
-        for (int u = 0; u < S2_CPL; ++u) {
-            const int pos = min(S2_CPL * lane + u, H2_MAX_L - 1);
-            ac[u] += (CT)tc[v][pos];
-            aq[u] = aq[u] + tq[v][pos];
-        }
-    }
-}
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef v4f v4f_any __attribute__((aligned(4)));
 
-// One (q index, problem) per workgroup of S2_WAVES wavefronts; CT is the type
-// of in-row count sums (uint32_t when the image holds fewer than 2^32
-// pixels).  R >= 1 rows hold counts, listed in rows[] in increasing order.
-// A row without counts (t >= 1) leaves the class 1 sums unchanged and
+// Bounded by its vector operations, about 190 per row, wavefront and pass (a
+// third of them the FP64 sums along s), four clocks each: 900 problems
+// of 256 levels (132 rows with counts) 288 -> 209 us with the row pass, 37 of
+// 200 levels 103 -> 56 us.  What changed: one walk for both directions' column
+// totals, rows' terms past the table kept instead of formed by calls in the
+// walks, constants of a problem in scalar registers (128 vector registers: four
+// wavefronts per SIMD), two or four times the wavefronts per problem.
+//
+// One (q index, problem) per workgroup of NW wavefronts; CT is the type of
+// count sums (uint32_t when the image holds fewer than 2^32 pixels).  R >= 1
+// rows hold counts, listed in rows[] in increasing order, in NW blocks.  A row
+// without counts (t >= 1) leaves the class 1 sums unchanged and
 // B(t+1, .) = B(t, .): its pairs tie exactly with those of row t-1, which
 // come first, so only listed rows are visited, and the class 2 partner of
 // the listed row rows[k] is rows[k+1].
+//  0. column totals of every block, then those of all blocks before and after
+//     each block;
 //  1. class 2 keys, bottom-up: B(t, s) = sums over {i >= t, j >= s} (scan
-//     position p is column L-1-p); the listed rows kB .. R-1 in S2_WAVES
-//     blocks, each started from the totals of the blocks below it; FP32 key
-//     of every listed row t >= 1 into k2 (workspace, [L][L] floats);
+//     position p is column L-1-p), each block started from the totals of the
+//     blocks below it; FP32 key of every listed row t >= 1 into k2
+//     (workspace, [L][L] floats);
 //  2. class 1, top-down: A(t, s) = sums over {i <= t, j <= s}, the listed
-//     rows 0 .. R-2 in blocks, each started from the totals of the blocks
-//     above it; the pair key is the FP32 class 1 key plus k2 at
-//     (rows[k+1], s+1); row maxima rmax[k] and the maximum M;
+//     rows up to R - 2, each block started from the totals of the blocks above
+//     it; the pair key is the FP32 class 1 key plus k2 at (rows[k+1], s+1);
+//     row maxima rmax[k] and the maximum M;
 //  3. rows with rmax >= M - 2 delta (the FP64 arg max is among them): the
 //     FP64 class 2 terms of their partner rows into t2 (workspace, doubles),
 //     from the same sums as in 1;
 //  4. the FP64 value of every pair of those rows whose key is >= M - 2
 //     delta, from the same sums as in 2; the first best pair (t outermost).
-template <typename CT>
-__device__ __forceinline__ void search2d_body(const S2 &p, double N, int R, S2Lds &sh, float *k2, double *t2,
+template <int NW, typename CT>
+__device__ __forceinline__ void search2d_body(const S2 &p, double N, int R, S2Lds<NW, CT> &sh, float *k2, double *t2,
                                               int32_t *thr_t, int32_t *thr_s, double *obj_p, int32_t *status_p)
 {
     const int lane = threadIdx.x & 63, L = p.L;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int *rows = sh.rows;
     float *rmax = sh.rmax;
-    int colB[S2_CPL], colA[S2_CPL];
-#pragma unroll
-    for (int u = 0; u < S2_CPL; ++u) {
-        colB[u] = L - 1 - (S2_CPL * lane + u);
-        colA[u] = S2_CPL * lane + u;
-    }
+    const int posl = S2_CPL * lane; // the lane's first scan position
+    const int colB0 = L - 1 - posl; // its column in suffix order; position u's is colB0 - u (negative: none)
     const int kB = rows[0] == 0 ? 1 : 0; // class 2 starts at row 1 at the earliest
-    // pairs exist for listed rows k with k + 1 < R (rows[k] <= L - 2 follows)
-    const int npair = R - 1;
-    // this wavefront's blocks: [b0, b1) of kB .. R-1 (class 2), [a0, a1) of
-    // 0 .. npair-1 (class 1)
-    const int b0 = s2_block(kB, R - kB, w), b1 = s2_block(kB, R - kB, w + 1);
-    const int a0 = s2_block(0, npair, w), a1 = s2_block(0, npair, w + 1);
+    const int b0 = R * w / NW, b1 = R * (w + 1) / NW; // this wavefront's block
+    const int bb = max(b0, kB), nb = b1 - bb;         // its class 2 rows (nb <= 0: none)
+    const int na = min(b1, R - 1) - b0;               // its rows with pairs (rows[k] <= L - 2 follows)
     auto none = [](int, float(&)[S2_CPL]) {};
-    // the stored class 2 keys at (rows[k + 1], s + 1) for the lane's columns s
+    // the stored class 2 keys at (rows[k + 1], s + 1) for the lane's columns
+    // s; past the row the next one's (or what follows the keys), masked below
     auto partner = [&](int k, float(&x)[S2_CPL]) {
         const float *row2 = k2 + (int64_t)rows[k + 1] * L; // k <= R - 2 in the pass that uses it
+        if (p.vec) {
+            const v4f v = *reinterpret_cast<const v4f_any *>(row2 + min(posl, L - S2_CPL) + 1);
 #pragma unroll
-        for (int u = 0; u < S2_CPL; ++u) {
-            const float v = row2[min(colA[u] + 1, L - 1)]; // unconditional load, masked below
-            x[u] = colA[u] <= L - 2 ? v : -INFINITY;
+            for (int u = 0; u < S2_CPL; ++u)
+                x[u] = v[u];
+        } else {
+#pragma unroll
+            for (int u = 0; u < S2_CPL; ++u)
+                x[u] = row2[min(posl + u + 1, L - 1)];
         }
     };
 
-    // block totals of both directions, then the carries into this block
-    store_block_totals<-1>(p, rows, b1 - 1, b1 - b0, sh.tc[0][w], sh.tq[0][w]);
-    store_block_totals<1>(p, rows, a0, a1 - a0, sh.tc[1][w], sh.tq[1][w]);
+    // 0. block totals, then per column the sums before and after every block
+    {
+        CT cc[S2_CPL];
+        double cq[S2_CPL];
+        block_totals<CT>(p, rows, b0, b1 - b0, cc, cq);
+#pragma unroll
+        for (int u = 0; u < S2_CPL; ++u) {
+            sh.tc[w + 1][posl + u] = cc[u];
+            sh.tq[0][w][posl + u] = cq[u];
+        }
+    }
     __syncthreads();
-    // the sums carried into this wavefront's blocks (the blocks below it for
-    // class 2, above it for class 1) are re-read from LDS at the start of
-    // each walk rather than held in registers across the passes
+    if (threadIdx.x < H2_MAX_L) {
+        const int c = threadIdx.x;
+        double aq = 0.0;
+#pragma unroll
+        for (int v = NW - 1; v >= 0; --v) {
+            sh.tq[1][v][c] = aq;
+            aq = aq + sh.tq[0][v][c];
+        }
+        CT ac = 0;
+        aq = 0.0;
+        sh.tc[0][c] = 0;
+#pragma unroll
+        for (int v = 0; v < NW; ++v) {
+            const double y = sh.tq[0][v][c];
+            sh.tq[0][v][c] = aq;
+            aq = aq + y;
+            ac += sh.tc[v + 1][c];
+            sh.tc[v + 1][c] = ac;
+        }
+    }
+    __syncthreads();
+    // the sums carried into this wavefront's block are formed again at the
+    // start of each walk rather than held in registers across the passes
 
     // 1. class 2 keys
     {
         CT bc[S2_CPL];
         double bq[S2_CPL];
-        carry_in<CT>(sh.tc[0], sh.tq[0], S2_WAVES - 1, -1, w, bc, bq);
-        for_rows<-1, CT>(p, rows, b1 - 1, b1 - b0, none, [&](int k, const CT(&rc)[S2_CPL], const double(&rq)[S2_CPL],
-                                                            const float(&)[S2_CPL]) {
+        carry_in<-1>(sh, L, w, bc, bq);
+        for_rows<-1, CT>(p, rows, b1 - 1, nb, none, [&](int k, const CT(&rc)[S2_CPL], const double(&rq)[S2_CPL],
+                                                        const float(&)[S2_CPL]) {
             float *row = k2 + (int64_t)rows[k] * L;
+            v4f key;
 #pragma unroll
             for (int u = 0; u < S2_CPL; ++u) {
                 bc[u] += rc[u];
                 bq[u] = bq[u] + rq[u];
-                if (colB[u] >= 0)
-                    row[colB[u]] = class_key32(bc[u], bq[u], p);
+                key[S2_CPL - 1 - u] = class_key32(bc[u], bq[u], p);
+            }
+            if (p.vec) {
+                if (colB0 >= 0)
+                    *reinterpret_cast<v4f_any *>(row + colB0 - (S2_CPL - 1)) = key;
+            } else {
+#pragma unroll
+                for (int u = 0; u < S2_CPL; ++u)
+                    if (colB0 - u >= 0)
+                        row[colB0 - u] = key[S2_CPL - 1 - u];
             }
         });
     }
@@ -1022,16 +1078,16 @@ __device__ __forceinline__ void search2d_body(const S2 &p, double N, int R, S2Ld
         float M = -INFINITY;
         CT ac[S2_CPL];
         double aq[S2_CPL];
-        carry_in<CT>(sh.tc[1], sh.tq[1], 0, 1, w, ac, aq);
-        for_rows<1, CT>(p, rows, a0, a1 - a0, partner, [&](int k, const CT(&rc)[S2_CPL], const double(&rq)[S2_CPL],
-                                                          const float(&x)[S2_CPL]) {
+        carry_in<1>(sh, L, w, ac, aq);
+        for_rows<1, CT>(p, rows, b0, na, partner, [&](int k, const CT(&rc)[S2_CPL], const double(&rq)[S2_CPL],
+                                                      const float(&x)[S2_CPL]) {
             float m = -INFINITY;
 #pragma unroll
             for (int u = 0; u < S2_CPL; ++u) {
                 ac[u] += rc[u];
                 aq[u] = aq[u] + rq[u];
-                if (colA[u] <= L - 2)
-                    m = fmaxf(m, class_key32(ac[u], aq[u], p) + x[u]);
+                const float key = class_key32(ac[u], aq[u], p) + x[u];
+                m = posl + u <= L - 2 ? fmaxf(m, key) : m;
             }
             m = wave_max_f32(m);
             if (lane == 0)
@@ -1043,10 +1099,11 @@ __device__ __forceinline__ void search2d_body(const S2 &p, double N, int R, S2Ld
     }
     __syncthreads();
     float M = -INFINITY;
-    for (int v = 0; v < S2_WAVES; ++v)
+    for (int v = 0; v < NW; ++v)
         M = fmaxf(M, sh.wm[v]);
+    M = uniform(M);
     const double delta = s2_delta(p, N);
-    const bool all = !(delta < INFINITY);
+    const bool all = !(uniform(delta) < INFINITY);
     if (!all && !(M > -INFINITY)) { // every key finite for a valid pair: none is valid
         if (threadIdx.x == 0) {
             *thr_t = *thr_s = -1;
@@ -1055,83 +1112,105 @@ __device__ __forceinline__ void search2d_body(const S2 &p, double N, int R, S2Ld
         }
         return;
     }
-    const double T = all ? -INFINITY : (double)M - 2.0 * delta;
-    // 3. FP64 class 2 terms of the partner rows rows[k], k - 1 a candidate,
-    // k in this wavefront's class 2 block: walked from the block's bottom up
-    // to the highest such row
-    {
-        int kmin = b1;
-        for (int k = b0 + lane; k < b1; k += 64)
-            if (k >= 1 && (all || (double)rmax[k - 1] >= T))
-                kmin = min(kmin, k);
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1)
-            kmin = min(kmin, __shfl_xor(kmin, o, 64));
-        if (kmin < b1) {
-            CT bc[S2_CPL];
-            double bq[S2_CPL];
-            carry_in<CT>(sh.tc[0], sh.tq[0], S2_WAVES - 1, -1, w, bc, bq);
-            for_rows<-1, CT>(p, rows, b1 - 1, b1 - kmin, none,
-                             [&](int k, const CT(&rc)[S2_CPL], const double(&rq)[S2_CPL], const float(&)[S2_CPL]) {
+    const double T = uniform(all ? -INFINITY : (double)M - 2.0 * delta);
+    // candidate rows of this block, and rows whose partner is one: bit l is row
+    // b0 + l (a block has at most 256 / NW rows).  Both walks stop at the rows
+    // they evaluate, so that the loads in flight do not hold registers beside
+    // the logarithms.
+    auto candidate = [&](int k) { return all || (double)rmax[k] >= T; };
+    uint64_t m4 = __ballot(lane < na && candidate(b0 + min(lane, max(na - 1, 0))));
+    const uint64_t m3 = __ballot(b0 + lane >= 1 && lane < b1 - b0 && candidate(max(b0 + lane - 1, 0)));
+    // 3. FP64 class 2 terms of the rows in m3, from the block's bottom up to
+    // the highest of them
+    if (m3) {
+        CT bc[S2_CPL];
+        double bq[S2_CPL];
+        carry_in<-1>(sh, L, w, bc, bq);
+        int k = b1 - 1;
+        for (uint64_t m = m3; m;) {
+            const int l = 63 - __clzll((long long)m), ke = b0 + l;
+            m &= ~(1ull << l);
+            for_rows<-1, CT>(p, rows, k, k - ke + 1, none,
+                             [&](int, const CT(&rc)[S2_CPL], const double(&rq)[S2_CPL], const float(&)[S2_CPL]) {
 #pragma unroll
                                  for (int u = 0; u < S2_CPL; ++u) {
                                      bc[u] += rc[u];
                                      bq[u] = bq[u] + rq[u];
                                  }
-                                 if (k >= 1 && (all || (double)rmax[k - 1] >= T)) {
-                                     double *row = t2 + (int64_t)rows[k] * L;
-#pragma unroll
-                                     for (int u = 0; u < S2_CPL; ++u)
-                                         if (colB[u] >= 0)
-                                             row[colB[u]] = class_term2(bc[u], bq[u], p.q, p.sgn, p.hmax);
-                                 }
                              });
+            k = ke - 1;
+            double *row = t2 + (int64_t)rows[ke] * L;
+#pragma unroll 1
+            for (int u = 0; u < S2_CPL; ++u)
+                if (colB0 - u >= 0)
+                    row[colB0 - u] = class_term2(pick(bc, u), pick(bq, u), p.q, p.sgn, p.hmax);
         }
     }
     __syncthreads();
-    // 4. FP64 values of the candidate pairs of this wavefront's class 1 block
+    // 4. FP64 values of the candidate pairs of this wavefront's block; rows in
+    // m3 form the terms of counts past the table anew (3 wrote over them)
     double best = -INFINITY;
     long long code = 0x7fffffffffffffffLL;
-    {
-        int kmax = a0 - 1;
-        for (int k = a0 + lane; k < a1; k += 64)
-            if (all || (double)rmax[k] >= T)
-                kmax = max(kmax, k);
+    if (m4) {
+        CT ac[S2_CPL];
+        double aq[S2_CPL];
+        carry_in<1>(sh, L, w, ac, aq);
+        auto add = [&](int, const CT(&rc)[S2_CPL], const double(&rq)[S2_CPL], const float(&)[S2_CPL]) {
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1)
-            kmax = max(kmax, __shfl_xor(kmax, o, 64));
-        if (kmax >= a0) {
-            CT ac[S2_CPL];
-            double aq[S2_CPL];
-            carry_in<CT>(sh.tc[1], sh.tq[1], 0, 1, w, ac, aq);
-            for_rows<1, CT>(p, rows, a0, kmax - a0 + 1, none,
-                            [&](int k, const CT(&rc)[S2_CPL], const double(&rq)[S2_CPL], const float(&)[S2_CPL]) {
-#pragma unroll
-                                for (int u = 0; u < S2_CPL; ++u) {
-                                    ac[u] += rc[u];
-                                    aq[u] = aq[u] + rq[u];
-                                }
-                                if (!(all || (double)rmax[k] >= T))
-                                    return;
-                                const int t = rows[k], r2 = rows[k + 1];
-                                const float *row2 = k2 + (int64_t)r2 * L;
-                                const double *row2d = t2 + (int64_t)r2 * L;
-#pragma unroll
-                                for (int u = 0; u < S2_CPL; ++u) {
-                                    if (colA[u] <= L - 2) {
-                                        const float key = class_key32(ac[u], aq[u], p) + row2[colA[u] + 1];
-                                        if (all || (double)key >= T) {
-                                            const double lam = class_term2(ac[u], aq[u], p.q, p.sgn, p.hmax) +
-                                                               row2d[colA[u] + 1];
-                                            const long long cd = ((long long)t << 12) | colA[u];
-                                            if (lam > -INFINITY && (lam > best || (lam == best && cd < code))) {
-                                                best = lam;
-                                                code = cd;
-                                            }
-                                        }
-                                    }
-                                }
-                            });
+            for (int u = 0; u < S2_CPL; ++u) {
+                ac[u] += rc[u];
+                aq[u] = aq[u] + rq[u];
+            }
+        };
+        for (int l = 0; m4;) {
+            int le = __ffsll((long long)m4) - 1; // the next candidate
+            if ((m3 >> l) & 1u) {
+                uint32_t c[S2_CPL];
+                double t[S2_CPL], rq[S2_CPL];
+                CT rc[S2_CPL];
+                const float x[S2_CPL] = {};
+                load_row<1>(p.h, L, p.vec, rows[b0 + l], c, p.band);
+                row_terms<1, true>(p, rows[b0 + l], c, t);
+                row_sums<CT>(c, t, rc, rq);
+                add(b0 + l, rc, rq, x);
+                if (l != le) {
+                    ++l;
+                    continue;
+                }
+            } else {
+                const uint64_t over = m3 >> l; // bit 0 is clear
+                const int stop = over ? l + __ffsll((long long)over) - 2 : 63;
+                const bool reach = le <= stop;
+                const int last = reach ? le : stop;
+                for_rows<1, CT>(p, rows, b0 + l, last - l + 1, none, add);
+                l = last;
+                if (!reach) {
+                    ++l;
+                    continue;
+                }
+            }
+            m4 &= m4 - 1;
+            const int k = b0 + le, t = rows[k], r2 = rows[k + 1];
+            const float *row2 = k2 + (int64_t)r2 * L;
+            const double *row2d = t2 + (int64_t)r2 * L;
+#pragma unroll 1
+            for (int u = 0; u < S2_CPL; ++u) {
+                const int col = posl + u;
+                if (col <= L - 2) {
+                    const CT c = pick(ac, u);
+                    const double q = pick(aq, u);
+                    const float key = class_key32(c, q, p) + row2[col + 1];
+                    if (all || (double)key >= T) {
+                        const double lam = class_term2(c, q, p.q, p.sgn, p.hmax) + row2d[col + 1];
+                        const long long cd = ((long long)t << 12) | col;
+                        if (lam > -INFINITY && (lam > best || (lam == best && cd < code))) {
+                            best = lam;
+                            code = cd;
+                        }
+                    }
+                }
+            }
+            l = le + 1;
         }
     }
     // first best pair of the wavefront, then of the workgroup
@@ -1150,7 +1229,7 @@ __device__ __forceinline__ void search2d_body(const S2 &p, double N, int R, S2Ld
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int v = 0; v < S2_WAVES; ++v)
+        for (int v = 0; v < NW; ++v)
             if (sh.wb[v] > best || (sh.wb[v] == best && sh.wcode[v] < code)) {
                 best = sh.wb[v];
                 code = sh.wcode[v];
@@ -1170,9 +1249,10 @@ __device__ __forceinline__ void search2d_body(const S2 &p, double N, int R, S2Ld
 
 // Which rows of each image hold counts, the image's pixel count and each
 // row's band of columns holding counts: one wavefront per group of 16 rows,
-// all 16 rows' loads in flight together.  mask[s][g] bit d: row 16 g + d
-// holds counts; cnt[s][g]: its pixels; band[s][t]: the lowest column holding
-// counts in row t | the highest << 16 (0xffff | 0 << 16 for an empty row).
+// all 16 rows' loads in flight together (bounded by reading the histograms
+// once).  mask[s][g] bit d: row 16 g + d holds counts; cnt[s][g]: its pixels;
+// band[s][t]: the first column of the lowest lane holding counts in row t | the
+// last of the highest << 16 (0xffff | 0 << 16 for an empty row).
 __global__ void __launch_bounds__(64) k_rows2d(const uint32_t *__restrict__ hist, int L, int groups,
                                                uint16_t *__restrict__ mask, uint64_t *__restrict__ cnt,
                                                uint32_t *__restrict__ band)
@@ -1184,39 +1264,29 @@ __global__ void __launch_bounds__(64) k_rows2d(const uint32_t *__restrict__ hist
 #pragma unroll
     for (int d = 0; d < 16; ++d) // rows past L reload row L-1 and count as empty
         load_row<1>(h, L, vec, min(16 * g + d, L - 1), c[d], nullptr);
-    uint32_t bits = 0;
+    uint32_t bits = 0, mine = 0xffffu; // lane d < 16 keeps row d's band
     uint64_t n = 0;
 #pragma unroll
     for (int d = 0; d < 16; ++d) {
-        uint64_t r = 0;
+        const bool in = 16 * g + d < L;
+        const uint64_t occ = __ballot((c[d][0] | c[d][1] | c[d][2] | c[d][3]) != 0u && in);
+        if (in) {
 #pragma unroll
-        for (int u = 0; u < S2_CPL; ++u)
-            r += c[d][u];
-        if (16 * g + d >= L)
-            r = 0;
-        n += r;
-        if (__ballot(r != 0))
-            bits |= 1u << d;
-        int lo = 0xffff, hi = 0;
-#pragma unroll
-        for (int u = S2_CPL - 1; u >= 0; --u)
-            if (c[d][u])
-                lo = S2_CPL * lane + u;
-#pragma unroll
-        for (int u = 0; u < S2_CPL; ++u)
-            if (c[d][u])
-                hi = S2_CPL * lane + u;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            lo = min(lo, __shfl_xor(lo, o, 64));
-            hi = max(hi, __shfl_xor(hi, o, 64));
+            for (int u = 0; u < S2_CPL; ++u)
+                n += c[d][u];
         }
-        if (lane == 0 && 16 * g + d < L)
-            band[(int64_t)s0 * L + 16 * g + d] = (bits >> d) & 1u ? (uint32_t)lo | ((uint32_t)hi << 16) : 0xffffu;
+        if (occ) {
+            bits |= 1u << d;
+            const uint32_t lo = S2_CPL * (__ffsll((long long)occ) - 1);
+            const uint32_t hi = S2_CPL * (63 - __clzll((long long)occ)) + S2_CPL - 1;
+            mine = lane == d ? lo | hi << 16 : mine;
+        }
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1)
         n += __shfl_xor(n, o, 64);
+    if (lane < 16 && 16 * g + lane < L)
+        band[(int64_t)s0 * L + 16 * g + lane] = mine;
     if (threadIdx.x == 0) {
         mask[(int64_t)s0 * 16 + g] = (uint16_t)bits;
         cnt[(int64_t)s0 * 16 + g] = n;
@@ -1227,55 +1297,27 @@ __global__ void __launch_bounds__(64) k_rows2d(const uint32_t *__restrict__ hist
 // nq: the nq workgroups of an image are 8 apart, so they land on the same XCD
 // (workgroups go to the 8 XCDs in turn) and share its L2 for the image's
 // rows; workgroups with s0 >= nseg do nothing.
-__global__ void __launch_bounds__(S2_THREADS) k_search2d(const uint32_t *__restrict__ hist, int nseg, int nq, int L,
-                                                         Q2List ql, float *__restrict__ k2all,
-                                                         double *__restrict__ t2all, const uint16_t *__restrict__ mask,
-                                                         const uint64_t *__restrict__ cnt,
-                                                         const uint32_t *__restrict__ band, int32_t *__restrict__ thr,
-                                                         double *__restrict__ obj, int32_t *__restrict__ status)
+template <int NW>
+__global__ void __launch_bounds__(64 * NW, NW == 8 ? 4 : 1)
+    k_search2d(const uint32_t *__restrict__ hist, int nseg, int nq, int L, Q2List ql, float *__restrict__ k2all,
+               double *__restrict__ t2all, const uint16_t *__restrict__ mask, const uint64_t *__restrict__ cnt,
+               const uint32_t *__restrict__ band, int32_t *__restrict__ thr, double *__restrict__ obj,
+               int32_t *__restrict__ status)
 {
-    __shared__ S2Lds sh;
-    __shared__ int nrows;
+    extern __shared__ double s2_lds[]; // S2Lds of either count type
+    S2Lds<NW, uint32_t> &sh = *reinterpret_cast<S2Lds<NW, uint32_t> *>(s2_lds);
+    S2Lds<NW, uint64_t> &sh64 = *reinterpret_cast<S2Lds<NW, uint64_t> *>(s2_lds);
     const int lane = threadIdx.x & 63;
     const int slot = blockIdx.x >> 3, s0 = (slot / nq) * 8 + (blockIdx.x & 7), j = slot % nq;
     if (s0 >= nseg)
         return;
     const int prob = j * nseg + s0;
-    S2 p;
-    p.h = hist + (int64_t)s0 * L * L;
-    p.L = L;
-    p.vec = (L % S2_CPL) == 0 && ((uintptr_t)p.h & 15) == 0;
-    p.q = ql.q[j];
-    p.sgn = p.q == 1.0 ? 0.0 : (p.q < 1.0 ? 1.0 : -1.0);
-    p.hmax = (p.q == 1.0 ? 1.0 : fabs(1.0 - p.q)) * 2.0 * log((double)L); // a class holds at most L^2 cells
-    p.mq = (float)(-p.q);
-    p.sg = p.q < 1.0 ? 1.0f : -1.0f;
-    p.gmax = (float)(p.hmax * 1.4426950408889634 * (1.0 + 0x1p-20));
-    p.tab = sh.tab;
-    p.band = sh.band;
-    // the image's pixel count (every wavefront) and its rows holding counts,
-    // in increasing order (wavefront 0): lane l looks at rows 4l .. 4l+3
-    // (groups past the last hold no rows below L)
+    // the image's pixel count (every wavefront)
     const int groups = (L + 15) / 16;
     uint64_t n = lane < groups ? cnt[(int64_t)s0 * 16 + lane] : 0;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1)
         n += __shfl_xor(n, o, 64);
-    if (threadIdx.x < 64) {
-        const uint32_t g16 = (4 * lane) / 16 < groups ? mask[(int64_t)s0 * 16 + (4 * lane) / 16] : 0u;
-        uint32_t nib = (g16 >> ((4 * lane) % 16)) & 0xfu;
-        if (4 * lane + 4 > L)
-            nib &= (4 * lane < L) ? (1u << (L - 4 * lane)) - 1u : 0u;
-        const uint32_t pos = wave_excl_sum<uint32_t>((uint32_t)__popc(nib));
-        uint32_t w = pos;
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-            if (nib & (1u << d))
-                sh.rows[w++] = 4 * lane + d;
-        const int R = __shfl(w, 63, 64);
-        if (lane == 0)
-            nrows = R;
-    }
     // thr is [nq][2][nseg]: t at row 0, s at row 1 of this q
     int32_t *thr_t = thr + (int64_t)(2 * j) * nseg + s0, *thr_s = thr_t + nseg;
     if (n == 0) {
@@ -1286,18 +1328,53 @@ __global__ void __launch_bounds__(S2_THREADS) k_search2d(const uint32_t *__restr
         }
         return;
     }
-    for (int i = threadIdx.x; i < S2_TAB; i += blockDim.x)
-        sh.tab[i] = cterm((uint32_t)i, p.q);
-    for (int i = threadIdx.x; i < L; i += blockDim.x)
-        sh.band[i] = band[(int64_t)s0 * L + i];
-    __syncthreads();
-    const int R = nrows;
+    S2 p;
+    p.h = hist + (int64_t)s0 * L * L;
+    p.L = L;
+    p.vec = (L % S2_CPL) == 0 && ((uintptr_t)p.h & 15) == 0;
+    p.q = ql.q[j];
+    p.sgn = uniform(p.q == 1.0 ? 0.0 : (p.q < 1.0 ? 1.0 : -1.0));
+    p.hmax = uniform((p.q == 1.0 ? 1.0 : fabs(1.0 - p.q)) * 2.0 * log((double)L)); // a class holds at most L^2 cells
+    p.mq = uniform((float)(-p.q));
+    p.sg = uniform(p.q < 1.0 ? 1.0f : -1.0f);
+    p.gmax = uniform((float)(p.hmax * 1.4426950408889634 * (1.0 + 0x1p-20)));
     float *k2 = k2all + (int64_t)prob * L * L;
     double *t2 = t2all + (int64_t)prob * L * L;
-    if (n >> 32)
-        search2d_body<uint64_t>(p, (double)n, R, sh, k2, t2, thr_t, thr_s, obj + prob, status + prob);
-    else
-        search2d_body<uint32_t>(p, (double)n, R, sh, k2, t2, thr_t, thr_s, obj + prob, status + prob);
+    p.big = t2;
+    // the rows holding counts, in increasing order (wavefront 0): lane l looks
+    // at rows 4l .. 4l+3 (groups past the last hold no rows below L); the
+    // table of terms and the rows' bands
+    auto setup = [&](auto &sl) {
+        p.tab = sl.tab;
+        p.band = sl.band;
+        if (threadIdx.x < 64) {
+            const uint32_t g16 = (4 * lane) / 16 < groups ? mask[(int64_t)s0 * 16 + (4 * lane) / 16] : 0u;
+            uint32_t nib = (g16 >> ((4 * lane) % 16)) & 0xfu;
+            if (4 * lane + 4 > L)
+                nib &= (4 * lane < L) ? (1u << (L - 4 * lane)) - 1u : 0u;
+            uint32_t w = wave_excl_sum<uint32_t>((uint32_t)__popc(nib));
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
+                if (nib & (1u << d))
+                    sl.rows[w++] = 4 * lane + d;
+            if (lane == 63)
+                sl.nrows = (int)w;
+        }
+#pragma unroll 1
+        for (int i = threadIdx.x; i < S2_TAB; i += blockDim.x)
+            sl.tab[i] = cterm((uint32_t)i, p.q);
+        for (int i = threadIdx.x; i < L; i += blockDim.x)
+            sl.band[i] = band[(int64_t)s0 * L + i];
+        __syncthreads();
+        return __builtin_amdgcn_readfirstlane(sl.nrows);
+    };
+    if (n >> 32) {
+        const int R = setup(sh64);
+        search2d_body<NW, uint64_t>(p, (double)n, R, sh64, k2, t2, thr_t, thr_s, obj + prob, status + prob);
+    } else {
+        const int R = setup(sh);
+        search2d_body<NW, uint32_t>(p, (double)n, R, sh, k2, t2, thr_t, thr_s, obj + prob, status + prob);
+    }
 }
 
 // Workspace: FP64 terms [nprob][L][L], FP32 keys [nprob][L][L], row masks
@@ -1329,8 +1406,22 @@ ts_status launch_search2d(const uint32_t *hist, int nseg, int L, int nq, const d
     const int groups = (L + 15) / 16;
     hipLaunchKernelGGL(k_rows2d, dim3((unsigned)(nseg * groups)), dim3(64), 0, st, hist, L, groups, mask, cnt, band);
     const unsigned nblk = (unsigned)((nseg + 7) / 8 * 8 * nq);
-    hipLaunchKernelGGL(k_search2d, dim3(nblk), dim3(S2_THREADS), 0, st, hist, nseg, nq, L, ql, k2, t2, mask, cnt, band,
-                       thr, obj, status);
+    // Sixteen wavefronts per problem while every problem then has a CU of its
+    // own, eight (two problems per CU) beyond: 37 problems of 200 levels 56
+    // against 62 us, 120 of 256 levels 86 against 99, 900 of 256 levels 266
+    // against 212 (with the row pass).
+    const bool few = (int64_t)nseg * nq <= device_cu_count();
+#define TS_S2(NW)                                                                                                   \
+    const size_t lds = sizeof(S2Lds<NW, uint64_t>);                                                               \
+    allow_dynamic_lds((const void *)k_search2d<NW>, lds);                                                         \
+    hipLaunchKernelGGL(k_search2d<NW>, dim3(nblk), dim3(64 * NW), lds, st, hist, nseg, nq, L, ql, k2, t2, mask,   \
+                       cnt, band, thr, obj, status)
+    if (few) {
+        TS_S2(16);
+    } else {
+        TS_S2(8);
+    }
+#undef TS_S2
     return check_launch("ts_threshold_search2d");
 }
 
