@@ -22,6 +22,7 @@ import ctypes
 import os
 from typing import Iterable, List, Optional, Sequence
 
+import numpy as np
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -117,7 +118,14 @@ def _check(st: int):
         raise TsError(st, _lib.ts_last_error().decode())
 
 
+# The current stream's handle without building a Stream object (which takes as
+# long as a launch), where torch has the call.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> Optional[int]:
+    if stream is None and _raw_stream is not None and torch.cuda.is_initialized():
+        return ctypes.c_void_p(_raw_stream(torch._C._cuda_getDevice()))
     s = stream if stream is not None else torch.cuda.current_stream()
     return ctypes.c_void_p(s.cuda_stream)
 
@@ -164,8 +172,31 @@ def device_table(values: Sequence[int], device, stream=None) -> torch.Tensor:
     """int64 device array of `values`, copied from pinned host memory without
     blocking the host, ordered on `stream` (default: the current stream)."""
     h = torch.tensor(list(values) or [0], dtype=torch.int64).pin_memory()
-    with torch.cuda.stream(stream if stream is not None else torch.cuda.current_stream(device)):
+    with _on(stream):  # the device's current stream when none is given
         return h.to(device, non_blocking=True)
+
+
+def _device_tables(tables: Sequence[np.ndarray], device) -> List[torch.Tensor]:
+    """The int64 tables on the device, by one copy on its current stream."""
+    flat = np.concatenate([*tables, np.zeros(1, np.int64)])  # never empty
+    h = torch.empty(len(flat), dtype=torch.int64, pin_memory=True)
+    h.numpy()[:] = flat
+    d = h.to(device, non_blocking=True)
+    at = np.cumsum([0] + [len(t) for t in tables]).tolist()
+    return [d[a:max(b, a + 1)] for a, b in zip(at, at[1:])]  # an empty table points at something too
+
+
+def _problems(tensors: Sequence[torch.Tensor], per: str):
+    """Addresses and element counts of the problems of contiguous tensors: one
+    per slice of the first dimension or per tensor."""
+    ptrs, sizes = [], []
+    for t in tensors:
+        n = t.shape[0] if per == "slice" else 1
+        m = t.numel() // n if n else 0
+        ptrs.append(t.data_ptr() + np.arange(n, dtype=np.int64) * (m * t.element_size()))
+        sizes.append(np.full(n, m, np.int64))
+    none = np.zeros(0, np.int64)
+    return np.concatenate([none, *ptrs]), np.concatenate([none, *sizes])
 
 
 class Batch:
@@ -193,6 +224,19 @@ class Batch:
         self.ptrs = device_table([s.data_ptr() for s in segs], dev, stream)
         self.offs = device_table(offs, dev, stream)
         self._c = _Batch(self.ptrs.data_ptr(), self.offs.data_ptr(), self.nseg, self.total)
+
+    @classmethod
+    def _from_tables(cls, tensors, sizes: np.ndarray, ptrs: torch.Tensor, offs: torch.Tensor) -> "Batch":
+        """A batch of problems whose tables are on the device already; `tensors`
+        (kept alive) hold them."""
+        self = cls.__new__(cls)
+        self.segments = list(tensors)
+        self.sizes = sizes.tolist()
+        self.total = int(sizes.sum())
+        self.nseg = len(sizes)
+        self.ptrs, self.offs = ptrs, offs
+        self._c = _Batch(ptrs.data_ptr(), offs.data_ptr(), self.nseg, self.total)
+        return self
 
     @classmethod
     def slices(cls, volume: torch.Tensor, stream=None) -> "Batch":
@@ -485,26 +529,38 @@ def _batch_segment(volumes, bin, k, q, per, mode, method, open_radius, tune, str
         raise ValueError(f"at most {MAX_LABEL_SETS} q values")
     if method == "auto":
         method = "exhaustive" if k <= 3 else "dp"
+    for v in vols:
+        if (per == "volume" or v.shape[0]) and (v.dtype != torch.int16 or not v.is_cuda):
+            raise ValueError("segments must be contiguous int16 CUDA tensors")
+    dev = vols[0].device if vols else torch.device("cuda")
     residues = None
     if open_radius is not None:
         if per != "slice":
             raise ValueError("the opening works on images: use per='slice'")
-        residues = []
-        for v in vols:
-            if v.dim() != 3:
-                raise ValueError("open_radius needs (Z, H, W) volumes")
-            _, _, r16 = open2d(Batch.slices(v, stream=stream), v.shape[1], v.shape[2], bin, open_radius,
-                               want=("residue16",), stream=stream)
-            residues.append(r16)
-        src = residues
+        if any(v.dim() != 3 for v in vols):
+            raise ValueError("open_radius needs (Z, H, W) volumes")
+        residues = [torch.empty_like(v, memory_format=torch.contiguous_format) for v in vols]
+    src = vols if residues is None else residues
+    # label maps in each volume's shape; the label pass writes every problem
+    # straight into its slice (or volume) of them
+    labels = [[torch.empty(v.shape, dtype=torch.uint8, device=v.device) for v in src] for _ in qs]
+    # every table of the call in one copy: the opening's per volume, the
+    # problems', and the label maps' addresses
+    ptrs, sizes = _problems(src, per)
+    tables = [ptrs, np.concatenate([np.zeros(1, np.int64), np.cumsum(sizes)])] + [_problems(lj, per)[0] for lj in labels]
+    open_sizes = []
+    for v in vols if residues is not None else []:
+        p, m = _problems([v], "slice")
+        tables += [p, np.concatenate([np.zeros(1, np.int64), np.cumsum(m)])]
+        open_sizes.append(m)
+    d = _device_tables(tables, dev)
+    batch = Batch._from_tables(src, sizes, d[0], d[1])
+    out_ptrs = d[2:2 + len(qs)]
+    if residues is not None:
+        for i, v in enumerate(vols):
+            b = Batch._from_tables([v], open_sizes[i], d[2 + len(qs) + 2 * i], d[3 + len(qs) + 2 * i])
+            open2d(b, v.shape[1], v.shape[2], bin, open_radius, residue16=residues[i], want=(), stream=stream)
         bin = binning(0, bin.nbins - 1, bin.nbins)
-    else:
-        src = vols
-    if per == "slice":
-        segs = [v[z].reshape(-1) for v in src for z in range(v.shape[0])]
-    else:
-        segs = [v.reshape(-1) for v in src]
-    batch = Batch(segs, stream=stream)
     if method == "2d":
         if per != "slice" or k != 1:
             raise ValueError("the two-dimensional form takes per='slice' and k = 1")
@@ -514,9 +570,8 @@ def _batch_segment(volumes, bin, k, q, per, mode, method, open_radius, tune, str
         (Hh, Ww), = shapes
         h = histogram2d(batch, Hh, Ww, bin, stream=stream)
         thr2, obj, status = threshold_search2d(h, list(qs), stream=stream)  # [nq, 2, nseg]
-        labels = [[torch.empty(v.shape, dtype=torch.uint8, device=v.device) for v in src] for _ in qs]
-        outs = [[lv[z].reshape(-1) for lv in lj for z in range(lv.shape[0])] for lj in labels]
-        label_sets(batch, bin, [thr2[j, 0] for j in range(len(qs))], 1, outs=outs, tune=tune, stream=stream)
+        label_sets(batch, bin, [thr2[j, 0] for j in range(len(qs))], 1, outs=labels, out_ptrs=out_ptrs, tune=tune,
+                   stream=stream)
         return Segmentation(h, thr2.transpose(1, 2), obj, status, labels, residues)
     h = histogram(batch, bin, tune=tune, stream=stream)
     P, Q = prefix(h, list(qs), stream=stream)
@@ -524,14 +579,8 @@ def _batch_segment(volumes, bin, k, q, per, mode, method, open_radius, tune, str
         thr, obj, status = threshold_search_dp(P, Q, k, list(qs), stream=stream)
     else:
         thr, obj, status = threshold_search(P, Q, k, list(qs), mode, tune=tune, stream=stream)
-    # label maps in each volume's shape; the label pass writes every problem
-    # straight into its slice (or volume) of them
-    labels = [[torch.empty(v.shape, dtype=torch.uint8, device=v.device) for v in src] for _ in qs]
-    if per == "slice":
-        outs = [[lv[z].reshape(-1) for lv in lj for z in range(lv.shape[0])] for lj in labels]
-    else:
-        outs = [[lv.reshape(-1) for lv in lj] for lj in labels]
-    label_sets(batch, bin, [thr[j] for j in range(len(qs))], k, outs=outs, tune=tune, stream=stream)
+    label_sets(batch, bin, [thr[j] for j in range(len(qs))], k, outs=labels, out_ptrs=out_ptrs, tune=tune,
+               stream=stream)
     return Segmentation(h, thr, obj, status, labels, residues)
 
 
