@@ -79,6 +79,40 @@ __device__ __forceinline__ int bin_of(int v, const BinMap &bm)
 
 inline int map_kind(const BinMap &bm) { return (bm.wide ? 1 : 0) | (bm.narrow ? 2 : 0); }
 
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+typedef short i16x2 __attribute__((ext_vector_type(2)));
+
+// Gray levels of two pixels, packed: clamped and offset together, then the
+// map for each.  KIND: 0 the level is the offset (W = L); 1 the top byte of
+// offset * mul24, both multiplied from their halves and the bytes picked by
+// one permute; 2 any other window, by the general map.
+template <int KIND>
+__device__ __forceinline__ uint32_t levels2(uint32_t v, const BinMap &bm, uint32_t mul24)
+{
+    if constexpr (KIND == 2)
+        return (uint32_t)bin_of((int16_t)(v & 0xffffu), bm) | (uint32_t)bin_of((int)v >> 16, bm) << 16;
+    const i16x2 lo = {(short)bm.lo, (short)bm.lo}, hi = {(short)bm.hi, (short)bm.hi};
+    i16x2 c = __builtin_bit_cast(i16x2, v);
+    c = __builtin_elementwise_min(__builtin_elementwise_max(c, lo), hi);
+    const uint32_t d = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, c) - __builtin_bit_cast(u16x2, lo));
+    if constexpr (KIND == 0)
+        return d;
+    return __builtin_amdgcn_perm(__umul24(d >> 16, mul24), __umul24(d & 0xffffu, mul24), 0x0c070c03u);
+}
+
+// The multiplier of KIND 1 (0: none): ceil(2^24 L / W) reproduces
+// floor(d L / W) for every offset d when W^2 < 2^24, or the quotient is exact.
+inline uint32_t binmap_mul24(const BinMap &bm)
+{
+    const uint64_t W = (uint64_t)(bm.hi - bm.lo + 1), n = (uint64_t)bm.L << 24;
+    const uint64_t mul = (n + W - 1) / W;
+    const bool exact = n % W == 0 || W * W < (1u << 24);
+    return bm.L < (int)W && bm.L <= 256 && exact && mul < (1u << 24) ? (uint32_t)mul : 0;
+}
+
+// KIND of levels2 for a window (at most 256 levels for kind 1).
+inline int levels_kind(const BinMap &bm) { return bm.hi - bm.lo + 1 == bm.L ? 0 : binmap_mul24(bm) ? 1 : 2; }
+
 // Pointers read from a device table are generic; the voxel and label arrays
 // always live in global memory, and saying so lets the compiler use global
 // (not flat) loads and stores, which do not wait on LDS traffic.

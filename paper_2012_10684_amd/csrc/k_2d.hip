@@ -48,8 +48,6 @@ constexpr int S2_RING = 2;        // rows of counts in flight ahead of the row b
 
 // ------------------------------------------------------------------ histogram
 
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-typedef short i16x2 __attribute__((ext_vector_type(2)));
 // 8 pixels at any pixel address (gfx950 takes unaligned global loads)
 typedef v4i v4i_any __attribute__((aligned(2)));
 
@@ -67,34 +65,6 @@ template <int CTRL, int ROWS>
 __device__ __forceinline__ uint32_t dpp32(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
-}
-
-// Gray levels of two pixels, packed: clamped and offset together, then the
-// map for each.  KIND: 0 the level is the offset (W = L); 1 the top byte of
-// offset * mul24, both multiplied from their halves and the bytes picked by
-// one permute; 2 any other window, by the general map.
-template <int KIND>
-__device__ __forceinline__ uint32_t levels2(uint32_t v, const BinMap &bm, uint32_t mul24)
-{
-    if constexpr (KIND == 2)
-        return (uint32_t)bin_of((int16_t)(v & 0xffffu), bm) | (uint32_t)bin_of((int)v >> 16, bm) << 16;
-    const i16x2 lo = {(short)bm.lo, (short)bm.lo}, hi = {(short)bm.hi, (short)bm.hi};
-    i16x2 c = __builtin_bit_cast(i16x2, v);
-    c = __builtin_elementwise_min(__builtin_elementwise_max(c, lo), hi);
-    const uint32_t d = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, c) - __builtin_bit_cast(u16x2, lo));
-    if constexpr (KIND == 0)
-        return d;
-    return __builtin_amdgcn_perm(__umul24(d >> 16, mul24), __umul24(d & 0xffffu, mul24), 0x0c070c03u);
-}
-
-// The multiplier of KIND 1 (0: none): ceil(2^24 L / W) reproduces
-// floor(d L / W) for every offset d when W^2 < 2^24, or the quotient is exact.
-static uint32_t hist2d_mul24(const BinMap &bm)
-{
-    const uint64_t W = (uint64_t)(bm.hi - bm.lo + 1), n = (uint64_t)bm.L << 24;
-    const uint64_t mul = (n + W - 1) / W;
-    const bool exact = n % W == 0 || W * W < (1u << 24);
-    return bm.L < (int)W && bm.L <= 256 && exact && mul < (1u << 24) ? (uint32_t)mul : 0;
 }
 
 // How the rows are laid over a workgroup: row groups of 1 << gsh lanes (8
@@ -488,17 +458,17 @@ ts_status launch_hist2d(const ts_batch &b, int H, int W, const BinMap &bm, uint3
             return e;
     }
     const size_t lds = ((size_t)((hist2d_words(bm.L) + 3) & ~3) + 2 + H2_THREADS / 64) * 4;
-    const uint32_t mul24 = hist2d_mul24(bm);
-    const bool same = bm.hi - bm.lo + 1 == bm.L;
+    const uint32_t mul24 = binmap_mul24(bm);
+    const int kind = levels_kind(bm);
     const dim3 g((unsigned)nwg), blk(H2_THREADS);
 #define TS_H2(K, R)                                                                                                 \
     allow_dynamic_lds((const void *)k_hist2d<K, R>, lds);                                                         \
     hipLaunchKernelGGL((k_hist2d<K, R>), g, blk, lds, st, b.vox, b.nseg, whole, parts, H, W, sh, bm,   \
                        mul24, hist)
     if (W % 8 == 0) {
-        if (same) { TS_H2(0, false); } else if (mul24) { TS_H2(1, false); } else { TS_H2(2, false); }
+        if (kind == 0) { TS_H2(0, false); } else if (kind == 1) { TS_H2(1, false); } else { TS_H2(2, false); }
     } else {
-        if (same) { TS_H2(0, true); } else if (mul24) { TS_H2(1, true); } else { TS_H2(2, true); }
+        if (kind == 0) { TS_H2(0, true); } else if (kind == 1) { TS_H2(1, true); } else { TS_H2(2, true); }
     }
 #undef TS_H2
     return check_launch("ts_histogram2d");

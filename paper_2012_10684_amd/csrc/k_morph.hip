@@ -19,7 +19,8 @@ ts_status launch_open2d(const ts_batch &b, int H, int W, const BinMap &bm, int r
     a.H = H;
     a.W = W;
     a.bm = bm;
-    a.mapk = map_kind(bm);
+    a.kind = levels_kind(bm);
+    a.mul24 = binmap_mul24(bm);
     if (W <= 2 * MV_THREADS) { // one tile across, no halo columns
         a.tiles_x = 1;
         a.tp = MV_THREADS;

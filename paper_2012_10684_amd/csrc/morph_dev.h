@@ -21,8 +21,8 @@
 // 16-bit values per 32-bit register (packed min/max: one instruction for two
 // pixels).  A thread loads its column pair over the tile's rows and r rows
 // above and below into registers (all loads in flight before the first is
-// used) and grows V_h one unit of height at a time: two packed operations
-// per row and unit, no cross-lane traffic.  At each distinct height the rows
+// used) and forms V_h from windows of a power of two of rows, doubled in place as
+// the height grows, no cross-lane traffic.  At each distinct height the rows
 // of V go to an LDS plane (two planes alternate, so one barrier per height
 // suffices) and every thread folds in the offsets a with that height from
 // its neighbours' words: a word d / 2 away for even d, the halves of two
@@ -91,7 +91,8 @@ struct MorphArgs {
     const uint8_t *src8;         // dilation: the eroded gray levels [nseg][H][W]
     int H, W;
     BinMap bm;
-    int mapk;              // map_kind(bm)
+    int kind;              // levels_kind(bm)
+    uint32_t mul24;        // binmap_mul24(bm)
     int tiles_x, tiles;    // tiles per image row band, per image
     int tp, hw;            // output column pairs per tile, halo column pairs left of them
     int ntiles;            // nseg * tiles
@@ -112,8 +113,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t mv_rsrc(const void *base, int 
 
 // The tile's outputs from O (rows y0 ..): erosion, the gray levels of the
 // minima of the raw values; dilation, the opened gray levels and the residue
-// gray(original) - opened, the originals F loaded before the compute.
-template <bool MAXOP, int MAP>
+// gray(original) - opened, the originals F loaded before the compute.  Both
+// pixels of a pair are mapped and subtracted together.
+template <bool MAXOP, int KIND>
 __device__ __forceinline__ void mv_epilogue(const MorphArgs &g, const uint32_t (&O)[MV_TY], const uint32_t (&F)[MV_TY],
                                             int64_t img, int y0, int x, bool out, bool pairs)
 {
@@ -122,45 +124,37 @@ __device__ __forceinline__ void mv_epilogue(const MorphArgs &g, const uint32_t (
     const __amdgpu_buffer_rsrc_t d8 = mv_rsrc(g.dst + img, npix), r8 = mv_rsrc(g.res + img, npix),
                                  r16 = mv_rsrc(g.res16 + img, 2 * npix);
     const bool want_res = MAXOP && (g.res || g.res16);
+    auto bytes = [](uint32_t v) { return __builtin_amdgcn_perm(0u, v, 0x0c0c0200u); }; // low bytes of both halves
 #pragma unroll
     for (int i = 0; i < MV_TY; ++i) {
         const int y = y0 + i;
         if (!out || y >= H)
             continue;
         const int ro = y * W;
-        int v0, v1, g0 = 0, g1 = 0;
-        if (!MAXOP) {
-            v0 = bin_of_t<MAP>((int)(int16_t)(O[i] & 0xffffu), g.bm);
-            v1 = bin_of_t<MAP>((int)(int16_t)(O[i] >> 16), g.bm);
-        } else {
-            v0 = (int)(O[i] & 0xffffu);
-            v1 = (int)(O[i] >> 16);
-            if (want_res) {
-                g0 = bin_of_t<MAP>((int)(int16_t)(F[i] & 0xffffu), g.bm) - v0;
-                g1 = bin_of_t<MAP>((int)(int16_t)(F[i] >> 16), g.bm) - v1;
-            }
-        }
+        const uint32_t v = MAXOP ? O[i] : levels2<KIND>(O[i], g.bm, g.mul24);
+        uint32_t gr = 0;
+        if (want_res)
+            gr = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, levels2<KIND>(F[i], g.bm, g.mul24)) -
+                                                  __builtin_bit_cast(u16x2, v));
         if (pairs) {
             if (g.dst)
-                __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(v0 | (v1 << 8)), d8, xo, ro, 0);
+                __builtin_amdgcn_raw_buffer_store_b16((unsigned short)bytes(v), d8, xo, ro, 0);
             if (MAXOP && g.res)
-                __builtin_amdgcn_raw_buffer_store_b16((unsigned short)((g0 & 0xff) | ((g1 & 0xff) << 8)), r8, xo, ro,
-                                                      0);
+                __builtin_amdgcn_raw_buffer_store_b16((unsigned short)bytes(gr), r8, xo, ro, 0);
             if (MAXOP && g.res16)
-                __builtin_amdgcn_raw_buffer_store_b32((g0 & 0xffff) | ((uint32_t)(g1 & 0xffff) << 16), r16, 2 * xo,
-                                                      2 * ro, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(gr, r16, 2 * xo, 2 * ro, 0);
         } else {
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 if (x + e >= W)
                     continue;
-                const int v = e ? v1 : v0, gr = e ? g1 : g0;
                 if (g.dst)
-                    __builtin_amdgcn_raw_buffer_store_b8((unsigned char)v, d8, xo + e, ro, 0);
+                    __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(v >> (16 * e)), d8, xo + e, ro, 0);
                 if (MAXOP && g.res)
-                    __builtin_amdgcn_raw_buffer_store_b8((unsigned char)gr, r8, xo + e, ro, 0);
+                    __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(gr >> (16 * e)), r8, xo + e, ro, 0);
                 if (MAXOP && g.res16)
-                    __builtin_amdgcn_raw_buffer_store_b16((unsigned short)gr, r16, 2 * (xo + e), 2 * ro, 0);
+                    __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(gr >> (16 * e)), r16, 2 * (xo + e), 2 * ro,
+                                                          0);
             }
         }
     }
@@ -208,18 +202,26 @@ constexpr bool mv_needs_plane(int R, int h)
     return false;
 }
 
-// Heights HH..R: grow V by one unit of height, and at each distinct height
-// publish V and fold in its offsets.
-template <bool MAXOP, int R, int HH, int NI, int PS>
-__device__ __forceinline__ void mv_levels(uint32_t (&O)[MV_TY], uint32_t (&V)[MV_TY], const uint32_t (&I)[NI],
+// The distinct heights HH..R in order: V of the height, published, and its
+// offsets folded in.  I[j] holds the minimum over S rows from row j on, S a
+// power of two: where the height's run of 2 HH + 1 rows holds 2 S rows, S is
+// doubled in place (one operation per row still needed), and the run is the
+// two windows of S rows at its ends.
+template <bool MAXOP, int R, int HH, int NI, int PS, int S = 1>
+__device__ __forceinline__ void mv_levels(uint32_t (&O)[MV_TY], uint32_t (&V)[MV_TY], uint32_t (&I)[NI],
                                           uint32_t *planes, int c)
 {
-    if constexpr (HH > 0) {
+    if constexpr (mv_is_level(R, HH) && 2 * S <= 2 * HH + 1) {
 #pragma unroll
-        for (int i = 0; i < MV_TY; ++i)
-            V[i] = mv_op<MAXOP>(V[i], mv_op<MAXOP>(I[i + R - HH], I[i + R + HH]));
+        for (int j = 0; j + 2 * S <= NI; ++j)
+            I[j] = mv_op<MAXOP>(I[j], I[j + S]);
+        mv_levels<MAXOP, R, HH, NI, PS, 2 * S>(O, V, I, planes, c);
+        return;
     }
     if constexpr (mv_is_level(R, HH)) {
+#pragma unroll
+        for (int i = 0; i < MV_TY; ++i)
+            V[i] = S == 2 * HH + 1 ? I[i + R - HH] : mv_op<MAXOP>(I[i + R - HH], I[i + R + HH + 1 - S]);
         constexpr int B = mv_levels_below(R, HH) & 1;
         uint32_t *p = planes + B * (MV_TY * PS) + c;
         if constexpr (mv_needs_plane(R, HH)) {
@@ -231,9 +233,17 @@ __device__ __forceinline__ void mv_levels(uint32_t (&O)[MV_TY], uint32_t (&V)[MV
         mv_combine<MAXOP, R, HH, PS>(O, V, p);
     }
     if constexpr (HH < R)
-        mv_levels<MAXOP, R, HH + 1, NI, PS>(O, V, I, planes, c);
+        mv_levels<MAXOP, R, HH + 1, NI, PS, S>(O, V, I, planes, c);
 }
 
+// Bounded by the vector operations (packed minima and byte aligns, about 30
+// wavefront instructions per row of 128 pixels at r = 10) and the LDS reads of
+// the offsets (26 words per column pair and row, 57 % of the time at 128 B per
+// clock): 300 slices of 512 x 512, r = 10, both passes 207 -> 193 us when the
+// runs were formed by doubling (17 instead of 20 operations per row), whole
+// pairs mapped at the end and inner tiles left unmasked.  The packed
+// three-operand half-precision minimum issues at half the rate: no gain.
+//
 // MAXOP = false: erosion of the raw values of the int16 images (src16) into
 // the gray levels dst; MAXOP = true: dilation of the gray levels src8 into
 // dst (opened) and/or the residue gray(src16) - opened into res (uint8) and
@@ -300,10 +310,14 @@ __global__ void __launch_bounds__(MV_THREADS) k_morph(MorphArgs g)
             for (int i = 0; i < MV_TY; ++i)
                 F[i] = __builtin_amdgcn_raw_buffer_load_b32(b16, 2 * xo, 2 * min(y0 + i, H - 1) * W, 0);
         }
+        // a tile whose rows and columns all lie inside the image needs no mask
+        const int xt = tx * 2 * g.tp - 2 * g.hw;
+        if (y0 < R || y0 + MV_TY + R > H || xt < 0 || xt + 2 * MV_THREADS > W) {
 #pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const int y = y0 - R + i;
-            I[i] = (y >= 0 && y < H && xin0) ? I[i] : NEUT;
+            for (int i = 0; i < NI; ++i) {
+                const int y = y0 - R + i;
+                I[i] = (y >= 0 && y < H && xin0) ? I[i] : NEUT;
+            }
         }
     } else {
         const int xo0 = min(max(x, 0), W - 1), xo1 = min(max(x + 1, 0), W - 1);
@@ -334,16 +348,13 @@ __global__ void __launch_bounds__(MV_THREADS) k_morph(MorphArgs g)
     }
     uint32_t V[MV_TY], O[MV_TY];
 #pragma unroll
-    for (int i = 0; i < MV_TY; ++i) {
-        V[i] = I[i + R];
+    for (int i = 0; i < MV_TY; ++i)
         O[i] = NEUT;
-    }
     mv_levels<MAXOP, R, 0, NI, PS>(O, V, I, planes, HP + t);
-    switch (g.mapk) {
+    switch (g.kind) {
     case 0: mv_epilogue<MAXOP, 0>(g, O, F, img, y0, x, out, pairs); break;
     case 1: mv_epilogue<MAXOP, 1>(g, O, F, img, y0, x, out, pairs); break;
-    case 2: mv_epilogue<MAXOP, 2>(g, O, F, img, y0, x, out, pairs); break;
-    default: mv_epilogue<MAXOP, 3>(g, O, F, img, y0, x, out, pairs); break;
+    default: mv_epilogue<MAXOP, 2>(g, O, F, img, y0, x, out, pairs); break;
     }
 }
 
