@@ -231,12 +231,15 @@ __device__ __forceinline__ double lambda64_k(const double *P, const double *Q, i
                                              double sgn, double hmax)
 {
     const int t0 = t[0], t1 = K > 1 ? t[1] : 0, t2 = K > 2 ? t[2] : 0;
+    // every boundary's sums in one round of loads
+    const double p0 = P[t0], p1 = K > 1 ? P[t1] : 0.0, p2 = K > 2 ? P[t2] : 0.0, pL = P[L - 1];
+    const double q0 = Q[t0], q1 = K > 1 ? Q[t1] : 0.0, q2 = K > 2 ? Q[t2] : 0.0, qL = Q[L - 1];
     double acc = 0.0;
     double pa = 0.0, qa = 0.0;
 #pragma unroll 1
     for (int j = 0; j <= K; ++j) {
-        const int b = j == K ? L - 1 : (j == 0 ? t0 : (j == 1 ? t1 : t2));
-        const double pb = P[b], qb = Q[b];
+        const double pb = j == K ? pL : (j == 0 ? p0 : (j == 1 ? p1 : p2));
+        const double qb = j == K ? qL : (j == 0 ? q0 : (j == 1 ? q1 : q2));
         const double dP = pb - pa, dQ = qb - qa;
         if (!(dP > 0.0))
             return -INFINITY;
@@ -488,14 +491,14 @@ __device__ __forceinline__ float prune_threshold(float Ms, float delta)
     return t;
 }
 
-__global__ void __launch_bounds__(256) k_setup(Args a)
+// Head and tail rows, split prefixes, error bound and threshold of the seeds
+// of problem s by the calling workgroup (at least 256 threads), from its
+// prefix sums P, Q [L] (global memory or LDS).  red holds 2 doubles per
+// wavefront.
+__device__ __forceinline__ void setup_body(const Args &a, int s, const double *P, const double *Q, double *red)
 {
-    const int s = blockIdx.x; // problem
     const QConst &c = a.qc[s / a.nseg];
-    const double *P = a.P + (int64_t)(s % a.nseg) * a.L;
-    const double *Q = a.Q + (int64_t)s * a.L;
     const int L = a.L, Lp = a.Lp;
-    __shared__ double red[8];
     Steps stp;
     if (a.mode == TS_SEARCH_FP64)
         stp = block_steps(P, Q, L, red);
@@ -510,31 +513,33 @@ __global__ void __launch_bounds__(256) k_setup(Args a)
                              a.hl + (int64_t)s * Lp, red);
     // k = 3 with the FP64 re-check: the largest FP32 key of a coarse grid of
     // tuples (seeds) gives the threshold below which k_rows3 skips row groups
-    // (rows3_body); the rows written above are visible after the barrier
+    // (rows3_body); the grid positions' terms, formed as for the rows above,
+    // go through LDS
     float ms = -INFINITY;
     if (a.k == 3 && a.mode == TS_SEARCH_FP32_TIECHECK) {
-        __syncthreads();
-        const float *hd = (const float *)a.head + (int64_t)s * Lp, *tl = (const float *)a.tail + (int64_t)s * Lp;
-        const float4 *hl = a.hl + (int64_t)s * Lp;
         constexpr int G = 16; // grid positions over [0, L - 2]
+        __shared__ float4 ghl[G];
+        __shared__ float ghd[G], gtl[G];
         const int S = (L - 1 + G - 1) / G;
+        auto pos = [&](int i) { return min(i * S + S / 2, L - 2); };
+        auto cls = [&](const float4 &hb, const float4 &ha) {
+            return c.sgn > 0 ? cls32<1>(hb, ha, c.mq, c.gmax)
+                             : (c.sgn < 0 ? cls32<-1>(hb, ha, c.mq, c.gmax) : cls32<0>(hb, ha, c.mq, c.gmax));
+        };
+        if (threadIdx.x < G) {
+            const int t = pos(threadIdx.x);
+            const float4 h = split_hl(P[t], Q[t]);
+            ghl[threadIdx.x] = h;
+            ghd[threadIdx.x] = cls(h, make_float4(0.0f, 0.0f, 0.0f, 0.0f));
+            gtl[threadIdx.x] = cls(split_hl(P[L - 1], Q[L - 1]), h);
+        }
+        __syncthreads();
         const int i = threadIdx.x / G, j = threadIdx.x % G;
-        const int t1 = min(i * S + S / 2, L - 2), t2 = min(j * S + S / 2, L - 2);
-        if (i < G && t1 < t2) {
-            const float4 h1 = hl[t1], h2 = hl[t2];
-            const float ar = hd[t1] + (c.sgn > 0 ? cls32<1>(h2, h1, c.mq, c.gmax)
-                                                  : (c.sgn < 0 ? cls32<-1>(h2, h1, c.mq, c.gmax)
-                                                               : cls32<0>(h2, h1, c.mq, c.gmax)));
-            for (int m = j + 1; m < G; ++m) {
-                const int t3 = min(m * S + S / 2, L - 2);
-                if (t3 <= t2)
-                    continue;
-                const float4 h3 = hl[t3];
-                const float g3 = c.sgn > 0 ? cls32<1>(h3, h2, c.mq, c.gmax)
-                                           : (c.sgn < 0 ? cls32<-1>(h3, h2, c.mq, c.gmax)
-                                                        : cls32<0>(h3, h2, c.mq, c.gmax));
-                ms = fmaxf(ms, ar + (g3 + tl[t3])); // the A row term plus the column term, as in phase 1
-            }
+        if (i < G && pos(i) < pos(j)) {
+            const float ar = ghd[i] + cls(ghl[j], ghl[i]);
+            for (int m = j + 1; m < G; ++m)
+                if (pos(m) > pos(j))
+                    ms = fmaxf(ms, ar + (cls(ghl[m], ghl[j]) + gtl[m])); // the A row term plus the column term, as in phase 1
         }
         ms = wave_max(ms);
         if ((threadIdx.x & 63) == 0)
@@ -565,6 +570,36 @@ __global__ void __launch_bounds__(256) k_setup(Args a)
             tl[t] = g;
         }
     }
+}
+
+__global__ void __launch_bounds__(256) k_setup(Args a)
+{
+    __shared__ double red[8];
+    const int s = blockIdx.x; // problem
+    setup_body(a, s, a.P + (int64_t)(s % a.nseg) * a.L, a.Q + (int64_t)s * a.L, red);
+}
+
+// The prefix pass and the set-up of one problem in one launch (ts_segment): the
+// set-up reads the prefix sums from LDS, and the launch between the two and its
+// loads (about 4 us) are gone.  Same bins per thread as the prefix pass, hence
+// the same bits.  LDS: Q before the fix-up and last occupied bins [L], then P
+// and Q [L].
+__global__ void __launch_bounds__(PREFIX_THREADS) k_scan_setup(Args a, const uint32_t *__restrict__ hist, int E,
+                                                               double *__restrict__ Pout, double *__restrict__ Qout)
+{
+    extern __shared__ double scan_lds[];
+    __shared__ PrefixLds ps;
+    __shared__ double red[2 * PREFIX_THREADS / 64];
+    const int s = blockIdx.x, L = a.L;
+    const uint32_t *h = hist + (int64_t)(s % a.nseg) * L;
+    double *qs = scan_lds, *Pl = qs + L + (L + 1) / 2, *Ql = Pl + L;
+    prefix_row([h](int b) { return h[b]; }, L, E, a.qc[s / a.nseg].q, Pl, Ql, qs, reinterpret_cast<int *>(qs + L), ps);
+    for (int t = threadIdx.x; t < L; t += blockDim.x) {
+        if (s < a.nseg) // P is the same for every q
+            Pout[(int64_t)s * L + t] = Pl[t];
+        Qout[(int64_t)s * L + t] = Ql[t];
+    }
+    setup_body(a, s, Pl, Ql, red);
 }
 
 // ---------------------------------------------------------------- k = 3 rows
@@ -887,47 +922,27 @@ __device__ __forceinline__ float phase2_threshold(float M, float delta)
     return t;
 }
 
-// Multi-launch path, one tile per wavefront.  PHASE 1 writes the tile max and
-// the problem max; PHASE 2 re-checks tiles whose max reaches the threshold.
-template <int SGN, int COLS, int PHASE, int K>
+// Multi-launch path, phase 1, one tile per wavefront: the tile max and the
+// problem max.
+template <int SGN, int COLS, int K>
 __device__ __forceinline__ void tiles32_wave(const Args &a, const Tile &tl)
 {
-    const int lane = threadIdx.x & 63;
     const int s = tl.s;
-    const int64_t tid = (int64_t)s * a.tiles + tl.tile;
     const TileCtx x = make_ctx(a, s, (const float *)a.head + (int64_t)s * a.Lp, (const float *)a.tail + (int64_t)s * a.Lp,
                                a.hl + (int64_t)s * a.Lp);
-    float thr = -INFINITY;
-    if (PHASE == 2) {
-        const Meta m = a.meta[s];
-        const float M = ordered_to_float(m.menc);
-        const float tm = a.tmax[tid];
-        thr = phase2_threshold(M, m.delta);
-        if (!(tm > -INFINITY) || M == -INFINITY || tm < thr) {
-            if (lane == 0)
-                a.best[tid] = Best{-INFINITY, -INFINITY, 0x7fffffffffffffffLL, 0};
-            return;
-        }
-    }
     float acc = -INFINITY;
     Cand best = {-INFINITY, -INFINITY, 0x7fffffffffffffffLL};
-    tile_body<SGN, COLS, PHASE, K>(x, tl.b, tl.c, thr, acc, best);
-    if (PHASE == 1) {
-        acc = wave_max(acc);
-        if (lane == 0) {
-            a.tmax[tid] = acc;
-            if (acc > -INFINITY)
-                atomicMax(&a.meta[s].menc, float_to_ordered(acc));
-        }
-    } else {
-        wave_best(best.r, best.l, best.c);
-        if (lane == 0)
-            a.best[tid] = Best{best.r, best.l, best.c, 0};
+    tile_body<SGN, COLS, 1, K>(x, tl.b, tl.c, 0.0f, acc, best);
+    acc = wave_max(acc);
+    if ((threadIdx.x & 63) == 0) {
+        a.tmax[(int64_t)s * a.tiles + tl.tile] = acc;
+        if (acc > -INFINITY)
+            atomicMax(&a.meta[s].menc, float_to_ordered(acc));
     }
 }
 
 // The sign of 1 - q is uniform over a tile's wavefront.
-template <int COLS, int PHASE, int K>
+template <int COLS, int K>
 __global__ void __launch_bounds__(256) k_tiles32(Args a)
 {
     const Tile tl = tile_of(a);
@@ -935,19 +950,12 @@ __global__ void __launch_bounds__(256) k_tiles32(Args a)
         return;
     const double sgn = a.qc[tl.s / a.nseg].sgn;
     if (sgn > 0)
-        tiles32_wave<1, COLS, PHASE, K>(a, tl);
+        tiles32_wave<1, COLS, K>(a, tl);
     else if (sgn < 0)
-        tiles32_wave<-1, COLS, PHASE, K>(a, tl);
+        tiles32_wave<-1, COLS, K>(a, tl);
     else
-        tiles32_wave<0, COLS, PHASE, K>(a, tl);
+        tiles32_wave<0, COLS, K>(a, tl);
 }
-
-// k = 3, one workgroup per (problem, row t2, chunk of 1024 columns).  The A
-// row head(t1) + g(t1, t2), t1 < t2, is built in LDS; lane columns are
-// t3 = t2 + 1 + c for c in the chunk, each holding R(t3) = g(t2, t3) + tail(t3)
-// in a register.  Every tuple's key is A[t1] + R[t3]: one add, and one max3 per
-// two tuples.  Tiles are (row, chunk, wavefront); rows are visited from the
-// middle outwards so the heaviest rows (t2 (L - t2) tuples) start first.
 
 __device__ __forceinline__ int k3_row(int r, int L)
 {
@@ -957,62 +965,62 @@ __device__ __forceinline__ int k3_row(int r, int L)
     return t2; // r in [0, L-3) visits every row in [1, L-3] once
 }
 
-// Rows t1 in [g0, g1) of one wavefront: key = A[t1] + R[t3] (g0, g1 multiples
-// of 8; A is -inf from t2 up to the padded end).
-template <int COLS, int PHASE>
-__device__ __forceinline__ void rows3_loop(const TileCtx &x, const float *Arow, int g0, int g1,
-                                           const float (&r)[K3_COLS], int t2, const int (&t3v)[K3_COLS], float thr,
-                                           float &acc, Cand &best)
+// Largest key A[t1] + R[t3] over the rows t1 in [g0, g1) of one wavefront (g0,
+// g1 multiples of 8; A is -inf from t2 up to the padded end).
+template <int COLS>
+__device__ __forceinline__ float rows3_max(const float *Arow, int g0, int g1, const float (&r)[K3_COLS])
 {
     const float4 *A4 = reinterpret_cast<const float4 *>(Arow);
     float acc0 = -INFINITY, acc1 = -INFINITY;
     for (int t1 = g0; t1 < g1; t1 += 8) {
         const float4 u0 = A4[t1 >> 2], u1 = A4[(t1 >> 2) + 1];
         const float av[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
-        if (PHASE == 1) {
 #pragma unroll
-            for (int v = 0; v < COLS; ++v) {
+        for (int v = 0; v < COLS; ++v) {
 #pragma unroll
-                for (int u = 0; u < 8; u += 2) {
-                    const float m = __builtin_fmaxf(av[u] + r[v], av[u + 1] + r[v]);
-                    if (v & 1)
-                        acc1 = __builtin_fmaxf(acc1, m);
-                    else
-                        acc0 = __builtin_fmaxf(acc0, m);
-                }
-            }
-        } else {
-#pragma unroll 1
-            for (int u = 0; u < 8; ++u) {
-                const float a = Arow[t1 + u];
-                float key[COLS];
-                int tv[COLS];
-                unsigned valid = 0;
-#pragma unroll
-                for (int v = 0; v < COLS; ++v) {
-                    key[v] = a + r[v]; // -inf for columns past the row end
-                    tv[v] = t3v[v];
-                    // rows t1 >= t2 (A is -inf there) and columns past L - 2 hold no tuple
-                    valid |= (t1 + u < t2 && t3v[v] <= x.L - 2) ? (1u << v) : 0u;
-                }
-                take_cols<3, COLS>(x, key, tv, valid, thr, best, t1 + u, t2);
+            for (int u = 0; u < 8; u += 2) {
+                const float m = __builtin_fmaxf(av[u] + r[v], av[u + 1] + r[v]);
+                if (v & 1)
+                    acc1 = __builtin_fmaxf(acc1, m);
+                else
+                    acc0 = __builtin_fmaxf(acc0, m);
             }
         }
     }
-    acc = fmaxf(acc, fmaxf(acc0, acc1));
+    return fmaxf(acc0, acc1);
 }
 
-// k = 3, one workgroup per (problem, row t2, chunk of 1024 columns).  The A
-// row head(t1) + g(t1, t2), t1 < t2, is built in LDS; column c of the chunk is
-// t3 = t2 + 1 + c, held by lane c % 64 of wavefront (c / 64) % 4 as
-// R(t3) = g(t2, t3) + tail(t3) in a register, so the valid columns of a short
-// row are spread over all four wavefronts (and SIMDs).  Every tuple's key is
-// A[t1] + R[t3]: one add, and one max3 per two tuples.  Phase 1 records the
-// wavefront max of every group of K3_GROUP rows; phase 2 re-checks only groups
-// whose max reaches the threshold.  Rows are visited from the middle
-// outwards so the heaviest rows (t2 (L - t2) tuples) start first.
-template <int SGN, int PHASE>
-__device__ __forceinline__ void rows3_body(const Args &a, float *Arow, float *wm)
+// Column terms R(t3) of wavefront w (of K3_THREADS / 64) of a chunk starting
+// at column c0: column c is t3 = t2 + 1 + c, held by lane c % 64 of wavefront
+// (c / 64) % 4; -inf past the row's ncols.  Returns the column blocks holding a
+// valid column.
+template <int SGN>
+__device__ __forceinline__ int rows3_cols(const TileCtx &x, const float4 &h2, int t2, int c0, int w, int ncols,
+                                          float (&r)[K3_COLS], int (&t3v)[K3_COLS])
+{
+    int nv = 0;
+#pragma unroll
+    for (int v = 0; v < K3_COLS; ++v) {
+        const int cb = c0 + v * K3_THREADS + w * 64;
+        const int c = cb + (threadIdx.x & 63);
+        const int t3 = t2 + 1 + c;
+        t3v[v] = t3;
+        r[v] = c < ncols ? cls32<SGN>(x.hl[t3], h2, x.mq, x.gmax) + x.tr[t3] : -INFINITY;
+        nv += cb < ncols ? 1 : 0;
+    }
+    return nv;
+}
+
+// k = 3, phase 1, one workgroup per (problem, row t2, chunk of 1024 columns).
+// The A row head(t1) + g(t1, t2), t1 < t2, is built in LDS; the column terms
+// R(t3) = g(t2, t3) + tail(t3) are in registers, the valid columns of a short
+// row spread over all four wavefronts (and SIMDs).  Every tuple's key is A[t1]
+// + R[t3]: one add, and one max3 per two tuples.  Records the wavefront max of
+// every group of K3_GROUP rows and of all of them (tilemax).  Rows are visited
+// from the middle outwards so the heaviest rows (t2 (L - t2) tuples) start
+// first.
+template <int SGN>
+__device__ __forceinline__ void rows3_body(const Args &a, float *tilemax, float *Arow, float *wm)
 {
     const int L = a.L;
     const int nrow = L - 3, nch = a.NC; // NC = column chunks per row
@@ -1031,70 +1039,33 @@ __device__ __forceinline__ void rows3_body(const Args &a, float *Arow, float *wm
     const int ngr = (n1 + K3_GROUP - 1) / K3_GROUP; // groups used by this row
     const TileCtx x = make_ctx(a, s, (const float *)a.head + (int64_t)s * a.Lp, (const float *)a.tail + (int64_t)s * a.Lp,
                                a.hl + (int64_t)s * a.Lp);
-    const Best none = {-INFINITY, -INFINITY, 0x7fffffffffffffffLL, 0};
     float *gmax_w = a.tmax + (tid0 + w) * ng; // this wavefront's group maxima
-    if (c0 >= ncols) { // empty chunk (whole workgroup)
-        if (PHASE == 1) {
-            for (int i = threadIdx.x; i < (K3_THREADS / 64) * ng; i += K3_THREADS)
-                a.tmax[tid0 * ng + i] = -INFINITY;
-        } else if (threadIdx.x < K3_THREADS / 64) {
-            a.best[tid0 + threadIdx.x] = none;
-        }
+    if (c0 >= ncols) { // empty chunk (whole workgroup): its groups are never looked at
+        if (lane == 0)
+            tilemax[tid0 + w] = -INFINITY;
         return;
-    }
-    float thr = -INFINITY;
-    if (PHASE == 2) {
-        const Meta m = a.meta[s];
-        const float M = ordered_to_float(m.menc);
-        thr = phase2_threshold(M, m.delta);
-        bool any = false;
-        for (int i = threadIdx.x; i < (K3_THREADS / 64) * ng; i += K3_THREADS) {
-            const float tm = a.tmax[tid0 * ng + i];
-            any = any || (tm > -INFINITY && tm >= thr);
-        }
-        any = __syncthreads_or(any) && M > -INFINITY;
-        if (!any) {
-            if (threadIdx.x < K3_THREADS / 64)
-                a.best[tid0 + threadIdx.x] = none;
-            return;
-        }
     }
     const float4 h2 = x.hl[t2];
     for (int t1 = threadIdx.x; t1 < n1; t1 += K3_THREADS)
         Arow[t1] = t1 < t2 ? x.hd[t1] + cls32<SGN>(h2, x.hl[t1], x.mq, x.gmax) : -INFINITY;
     float r[K3_COLS];
     int t3v[K3_COLS];
-    int nv = 0; // column blocks of this wavefront holding a valid column
-#pragma unroll
-    for (int v = 0; v < K3_COLS; ++v) {
-        const int cb = c0 + v * K3_THREADS + w * 64;
-        const int c = cb + lane;
-        const int t3 = t2 + 1 + c;
-        t3v[v] = t3;
-        r[v] = c < ncols ? cls32<SGN>(x.hl[t3], h2, x.mq, x.gmax) + x.tr[t3] : -INFINITY;
-        nv += cb < ncols ? 1 : 0;
-    }
+    const int nv = rows3_cols<SGN>(x, h2, t2, c0, w, ncols, r, t3v);
     __syncthreads();
-    Cand best = {-INFINITY, -INFINITY, 0x7fffffffffffffffLL};
-    float wmax = -INFINITY;
-    // phase 1 skips a group when the largest A of its rows plus the largest
+    // a group is skipped when the largest A of its rows plus the largest
     // column term of this wavefront is below the seeds' threshold: that sum
     // bounds every FP32 key of the block (rounded addition is monotone), and
     // no tuple of it is the arg max or ties with it (the argument of the k = 2
-    // row pruning, k_setup)
-    float pthr = -INFINITY, rmx = -INFINITY;
-    if (PHASE == 1) {
-        pthr = a.meta[s].pthr;
+    // row pruning, setup_body)
+    const float pthr = a.meta[s].pthr;
+    float rmx = -INFINITY, wmax = -INFINITY;
 #pragma unroll
-        for (int v = 0; v < K3_COLS; ++v)
-            rmx = fmaxf(rmx, r[v]);
-        rmx = wave_max(rmx);
-    }
+    for (int v = 0; v < K3_COLS; ++v)
+        rmx = fmaxf(rmx, r[v]);
+    rmx = wave_max(rmx);
     for (int g = 0; g < ngr; ++g) {
         const int g0 = g * K3_GROUP, g1 = min(n1, g0 + K3_GROUP);
-        if (PHASE == 2 && !(gmax_w[g] >= thr))
-            continue;
-        if (PHASE == 1 && pthr > -INFINITY) {
+        if (pthr > -INFINITY) {
             const float ga = wave_max(lane < K3_GROUP && g0 + lane < g1 ? Arow[g0 + lane] : -INFINITY);
             if (ga + rmx < pthr) {
                 if (lane == 0)
@@ -1104,41 +1075,32 @@ __device__ __forceinline__ void rows3_body(const Args &a, float *Arow, float *wm
         }
         float acc = -INFINITY;
         if (nv > 2)
-            rows3_loop<4, PHASE>(x, Arow, g0, g1, r, t2, t3v, thr, acc, best);
+            acc = rows3_max<4>(Arow, g0, g1, r);
         else if (nv == 2)
-            rows3_loop<2, PHASE>(x, Arow, g0, g1, r, t2, t3v, thr, acc, best);
+            acc = rows3_max<2>(Arow, g0, g1, r);
         else if (nv == 1)
-            rows3_loop<1, PHASE>(x, Arow, g0, g1, r, t2, t3v, thr, acc, best);
-        if (PHASE == 1) {
-            acc = wave_max(acc);
-            if (lane == 0)
-                gmax_w[g] = acc;
-            wmax = fmaxf(wmax, acc);
-        }
+            acc = rows3_max<1>(Arow, g0, g1, r);
+        acc = wave_max(acc);
+        if (lane == 0)
+            gmax_w[g] = acc;
+        wmax = fmaxf(wmax, acc);
     }
-    if (PHASE == 1) {
-        for (int g = ngr + lane; g < ng; g += 64)
-            gmax_w[g] = -INFINITY;
-        // one atomic per workgroup for the problem max
-        if (lane == 0)
-            wm[w] = wmax;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            float m = wm[0];
-            for (int i = 1; i < K3_THREADS / 64; ++i)
-                m = fmaxf(m, wm[i]);
-            if (m > -INFINITY)
-                atomicMax(&a.meta[s].menc, float_to_ordered(m));
-        }
-    } else {
-        wave_best(best.r, best.l, best.c);
-        if (lane == 0)
-            a.best[tid0 + w] = Best{best.r, best.l, best.c, 0};
+    // one atomic per workgroup for the problem max
+    if (lane == 0) {
+        tilemax[tid0 + w] = wmax;
+        wm[w] = wmax;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float m = wm[0];
+        for (int i = 1; i < K3_THREADS / 64; ++i)
+            m = fmaxf(m, wm[i]);
+        if (m > -INFINITY)
+            atomicMax(&a.meta[s].menc, float_to_ordered(m));
     }
 }
 
-template <int PHASE>
-__global__ void __launch_bounds__(K3_THREADS) k_rows3(Args a)
+__global__ void __launch_bounds__(K3_THREADS) k_rows3(Args a, float *tilemax)
 {
     extern __shared__ float4 arow_dyn[]; // Lp floats: the A row up to t2 (rounded up to 8)
     float *Arow = reinterpret_cast<float *>(arow_dyn);
@@ -1146,11 +1108,116 @@ __global__ void __launch_bounds__(K3_THREADS) k_rows3(Args a)
     const int s = (int)((int64_t)blockIdx.x / ((int64_t)(a.L - 3) * a.NC));
     const double sgn = a.qc[s / a.nseg].sgn;
     if (sgn > 0)
-        rows3_body<1, PHASE>(a, Arow, wm);
+        rows3_body<1>(a, tilemax, Arow, wm);
     else if (sgn < 0)
-        rows3_body<-1, PHASE>(a, Arow, wm);
+        rows3_body<-1>(a, tilemax, Arow, wm);
     else
-        rows3_body<0, PHASE>(a, Arow, wm);
+        rows3_body<0>(a, tilemax, Arow, wm);
+}
+
+// Phase 2 of the multi-launch paths: G workgroups per problem, tile t (its max
+// in tilemax) belonging to workgroup t mod G (tiles that qualify are
+// neighbours).  The four wavefronts share the rows of every tile whose max
+// reaches the threshold, typically one or two per problem, and the workgroup
+// leaves its best in best[problem][workgroup].  Bounded by latency: a workgroup
+// per tile or row, of which nearly all only found that they had nothing to do,
+// and a wavefront with a whole tile took 13.5 us at 512 levels, k = 3, against
+// 9.0, and left every tile's best to be reduced.
+template <int SGN, int COLS, int K>
+__device__ __forceinline__ void recheck_body(const Args &a, const float *tilemax, int s, int g, int G, float thr,
+                                             Cand &best)
+{
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const TileCtx x = make_ctx(a, s, (const float *)a.head + (int64_t)s * a.Lp, (const float *)a.tail + (int64_t)s * a.Lp,
+                               a.hl + (int64_t)s * a.Lp);
+    const float *tm = tilemax + (int64_t)s * a.tiles;
+    for (int t0 = g; t0 < a.tiles; t0 += 64 * G) {
+        const int ti = t0 + lane * G;
+        float mine = ti < a.tiles ? tm[ti] : -INFINITY;
+        if (K == 3 && !(thr > -INFINITY) && ti < a.tiles) { // every tuple: the whole chunk if it holds any
+            const int c4 = ti & ~(K3_THREADS / 64 - 1);
+            for (int i = 0; i < K3_THREADS / 64; ++i)
+                mine = fmaxf(mine, tm[c4 + i]);
+        }
+        unsigned long long m = __ballot(mine > -INFINITY && mine >= thr);
+        while (m) {
+            const int tile = t0 + __builtin_ctzll(m) * G;
+            m &= m - 1;
+            if constexpr (K == 1) {
+                float acc = -INFINITY;
+                if (w == 0)
+                    tile_k1<COLS, 2>(x, tile, thr, acc, best);
+            } else if constexpr (K == 2) {
+                float acc = -INFINITY;
+                tile_k2<SGN, COLS, 2>(x, tile % a.NB, tile / a.NB, thr, acc, best, w, 4);
+            } else {
+                const int nch = a.NC, ng = a.T1, L = x.L;
+                const int tw = tile % (K3_THREADS / 64), rc = tile / (K3_THREADS / 64);
+                const int t2 = 1 + rc / nch, c0 = (rc % nch) * K3_CHUNK;
+                const int n1 = (t2 + 7) & ~7, ngr = (n1 + K3_GROUP - 1) / K3_GROUP;
+                const float4 h2 = x.hl[t2];
+                float r[K3_COLS];
+                int t3v[K3_COLS];
+                (void)rows3_cols<SGN>(x, h2, t2, c0, tw, L - 2 - t2, r, t3v);
+                const float *gm = a.tmax + ((int64_t)s * a.tiles + tile) * ng;
+                for (int b = 0; b < ngr; b += 64) {
+                    unsigned long long mg = __ballot(b + lane < ngr && gm[min(b + lane, ngr - 1)] >= thr);
+                    while (mg) {
+                        const int g0 = (b + __builtin_ctzll(mg)) * K3_GROUP;
+                        mg &= mg - 1;
+                        // this wavefront's share of the group's rows
+                        const int r0 = g0 + w * (K3_GROUP / 4), r1 = min(t2, r0 + K3_GROUP / 4);
+                        // the rows' A as in phase 1, one per lane
+                        const int tl = min(r0 + lane, t2 - 1);
+                        const float al = x.hd[tl] + cls32<SGN>(h2, x.hl[tl], x.mq, x.gmax);
+#pragma unroll 1
+                        for (int t1 = r0; t1 < r1; ++t1) {
+                            const float ar = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(al), t1 - r0));
+                            float key[K3_COLS];
+                            unsigned valid = 0;
+#pragma unroll
+                            for (int v = 0; v < K3_COLS; ++v) {
+                                key[v] = ar + r[v];
+                                valid |= t3v[v] <= L - 2 ? (1u << v) : 0u;
+                            }
+                            take_cols<3, K3_COLS>(x, key, t3v, valid, thr, best, t1, t2);
+                        }
+                    }
+                }
+            }
+        }
+    }
+}
+
+template <int COLS, int K>
+__global__ void __launch_bounds__(256) k_recheck(Args a, const float *tilemax, int G)
+{
+    __shared__ Cand wb[4];
+    const int s = blockIdx.x / G, g = blockIdx.x % G;
+    const Meta meta = a.meta[s];
+    const float M = ordered_to_float(meta.menc);
+    Cand best = {-INFINITY, -INFINITY, 0x7fffffffffffffffLL};
+    if (M > -INFINITY) {
+        const float thr = phase2_threshold(M, meta.delta);
+        const double sgn = a.qc[s / a.nseg].sgn;
+        if (sgn > 0)
+            recheck_body<1, COLS, K>(a, tilemax, s, g, G, thr, best);
+        else if (sgn < 0)
+            recheck_body<-1, COLS, K>(a, tilemax, s, g, G, thr, best);
+        else
+            recheck_body<0, COLS, K>(a, tilemax, s, g, G, thr, best);
+    }
+    wave_best(best.r, best.l, best.c);
+    if ((threadIdx.x & 63) == 0)
+        wb[threadIdx.x >> 6] = best;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < 4; ++i)
+            if (better(wb[i].r, wb[i].c, best.r, best.c))
+                best = wb[i];
+        a.best[(int64_t)s * G + g] = Best{best.r, best.l, best.c, 0};
+    }
 }
 
 // Write problem s's result from its best candidate (plast = P(L-1) of the
@@ -1416,6 +1483,52 @@ __global__ void __launch_bounds__(FUSED_THREADS) k_fused(Args a, int32_t *__rest
         fused_body<-1, COLS, K>(a, sh, s, P, Q, true, thr_out, obj, status);
     else
         fused_body<0, COLS, K>(a, sh, s, P, Q, true, thr_out, obj, status);
+}
+
+// The prefix pass and the one-workgroup search in one launch (ts_segment): the
+// prefix sums stay in LDS.  The same bins per thread as the prefix pass, hence
+// the same bits.  Dynamic LDS (scan_fused_lds): the scan's scratch, later the
+// search's rows | P [Lp] | Q [Lp].  82 problems of 200 levels, k = 2:
+// 19.3 us, against 4.8 for the prefix pass and 28 for the search in four
+// launches; 900 of 256 levels 37.4 against 6.8 and 32.8.
+template <int COLS, int K>
+__global__ void __launch_bounds__(FUSED_THREADS) k_scan_fused(Args a, const uint32_t *__restrict__ hist, int E,
+                                                              int area, int32_t *__restrict__ thr_out,
+                                                              double *__restrict__ obj, int32_t *__restrict__ status)
+{
+    __shared__ FusedLds sh;
+    __shared__ PrefixLds ps;
+    extern __shared__ float4 dyn[];
+    char *lds = reinterpret_cast<char *>(dyn);
+    double *Pl = reinterpret_cast<double *>(lds + area), *Ql = Pl + a.Lp;
+    sh.hls = dyn;
+    sh.pd = nullptr;
+    sh.qd = nullptr;
+    sh.hd = reinterpret_cast<float *>(lds + (K == 2 ? (size_t)16 * a.Lp : 0));
+    sh.tr = sh.hd + a.Lp;
+    sh.tmax = sh.tr + a.Lp;
+    const int s = blockIdx.x, L = a.L;
+    const uint32_t *h = hist + (int64_t)(s % a.nseg) * L;
+    double *qs = reinterpret_cast<double *>(lds);
+    prefix_row([h](int b) { return h[b]; }, L, E, a.qc[s / a.nseg].q, Pl, Ql, qs, reinterpret_cast<int *>(qs + L), ps);
+    const double sgn = a.qc[s / a.nseg].sgn;
+    if (sgn > 0)
+        fused_body<1, COLS, K>(a, sh, s, Pl, Ql, false, thr_out, obj, status);
+    else if (sgn < 0)
+        fused_body<-1, COLS, K>(a, sh, s, Pl, Ql, false, thr_out, obj, status);
+    else
+        fused_body<0, COLS, K>(a, sh, s, Pl, Ql, false, thr_out, obj, status);
+}
+
+// LDS area A of k_scan_fused, and all of it.
+static size_t scan_fused_area(int L, int Lp, int k, int tiles)
+{
+    const size_t rows = (size_t)Lp * (2 * sizeof(float) + (k == 2 ? sizeof(float4) : 0)) + (size_t)tiles * sizeof(float);
+    return (std::max(rows, (size_t)L * (sizeof(double) + sizeof(int))) + 15) & ~(size_t)15;
+}
+static size_t scan_fused_lds(int L, int Lp, int k, int tiles)
+{
+    return scan_fused_area(L, Lp, k, tiles) + (size_t)Lp * 2 * sizeof(double);
 }
 
 // FP64 mode: exhaustive FP64 keys with the lexicographic tie rule.
@@ -2145,6 +2258,10 @@ static void launch_seg_km(dim3 g, dim3 b, size_t lds, hipStream_t st, const SegA
     hipLaunchKernelGGL((k_segment<K, MAP>), g, b, lds, st, sa, a, thr, obj, status);
 }
 
+static ts_status launch_scan_search(const uint32_t *hist, double *P, double *Q, int nseg, int L, int k, int nq,
+                                    const double *q, int mode, void *ws, int32_t *thr, double *obj, int32_t *status,
+                                    const Tune &t, hipStream_t st);
+
 ts_status launch_segment(const ts_batch &b, const BinMap &bm, int k, int nq, const double *q, int mode,
                          uint32_t *hist, int32_t *thr, double *obj, int32_t *status, const LabelSets *sets, void *ws,
                          const Tune &t, hipStream_t st)
@@ -2160,10 +2277,7 @@ ts_status launch_segment(const ts_batch &b, const BinMap &bm, int k, int nq, con
         ts_status e;
         if ((e = launch_histogram(b, bm, hist, t, st)) != TS_OK)
             return e;
-        if ((e = launch_prefix(hist, nseg, L, nq, q, P, Q, st)) != TS_OK)
-            return e;
-        if ((e = launch_search(P, Q, nseg, L, k, nq, q, mode, sw, search_workspace_bytes(nseg * nq, L, k, mode, 4),
-                               thr, obj, status, t, st)) != TS_OK)
+        if ((e = launch_scan_search(hist, P, Q, nseg, L, k, nq, q, mode, sw, thr, obj, status, t, st)) != TS_OK)
             return e;
         return sets ? launch_label(b, bm, *sets, nq, k, t, st) : TS_OK;
     }
@@ -2711,37 +2825,102 @@ static ts_status launch_small(const ts_batch &b, const BinMap &bm, const double 
 
 // ---------------------------------------------------------------- dispatch
 
-template <int COLS>
-static void launch_fp32(int fused_block, int k, dim3 g, hipStream_t st, const Args &a, int32_t *thr, double *obj,
-                        int32_t *status)
+// How the FP32 search of a call runs: the prefix sums from hist when it is not
+// null (ts_segment), else from P, Q.
+struct Fp32Launch {
+    const uint32_t *hist;
+    double *P, *Q; // written when hist is given and the multi-launch path reads them
+    int32_t *thr;
+    double *obj;
+    int32_t *status;
+    hipStream_t st;
+};
+
+template <int COLS, int K>
+static void launch_fused(const Args &a, int block, const Fp32Launch &f)
 {
-    if (fused_block) {
-        const dim3 gf((unsigned)a.nprob), bf((unsigned)fused_block);
-        const size_t lds = fused_lds_bytes(a.Lp, k, a.tiles);
-        if (k == 1)
-            hipLaunchKernelGGL((k_fused<COLS, 1>), gf, bf, lds, st, a, thr, obj, status);
-        else
-            hipLaunchKernelGGL((k_fused<COLS, 2>), gf, bf, lds, st, a, thr, obj, status);
+    const dim3 g((unsigned)a.nprob);
+    if (!f.hist) {
+        hipLaunchKernelGGL((k_fused<COLS, K>), g, dim3((unsigned)block), fused_lds_bytes(a.Lp, K, a.tiles), f.st, a,
+                           f.thr, f.obj, f.status);
         return;
     }
-    if (k == 1) {
-        hipLaunchKernelGGL((k_tiles32<COLS, 1, 1>), g, dim3(256), 0, st, a);
-        hipLaunchKernelGGL((k_tiles32<COLS, 2, 1>), g, dim3(256), 0, st, a);
+    const int E = prefix_bins_per_thread(a.L);
+    while (block * E < a.L) // the scan needs every bin
+        block *= 2;
+    const size_t lds = scan_fused_lds(a.L, a.Lp, K, a.tiles);
+    allow_dynamic_lds((const void *)k_scan_fused<COLS, K>, lds);
+    hipLaunchKernelGGL((k_scan_fused<COLS, K>), g, dim3((unsigned)block), lds, f.st, a, f.hist, E,
+                       (int)scan_fused_area(a.L, a.Lp, K, a.tiles), f.thr, f.obj, f.status);
+}
+
+static void launch_setup(const Args &a, const Fp32Launch &f)
+{
+    if (!f.hist) {
+        hipLaunchKernelGGL(k_setup, dim3((unsigned)a.nprob), dim3(256), 0, f.st, a);
+        return;
+    }
+    const size_t lds = ((size_t)a.L * 3 + (a.L + 1) / 2) * sizeof(double);
+    allow_dynamic_lds((const void *)k_scan_setup, lds);
+    hipLaunchKernelGGL(k_scan_setup, dim3((unsigned)a.nprob), dim3((unsigned)prefix_threads(a.L)), lds, f.st, a, f.hist,
+                       prefix_bins_per_thread(a.L), f.P, f.Q);
+}
+
+// Phase 2 and the result: G workgroups per problem, enough to fill the chip,
+// at most 7/8 of the tiles (the tile maxima of k = 3 lie after their bests in
+// the workspace's tile bests).
+template <int COLS, int K>
+static void launch_recheck(const Args &a, const float *tilemax, int G, const Fp32Launch &f)
+{
+    hipLaunchKernelGGL((k_recheck<COLS, K>), dim3((unsigned)((int64_t)a.nprob * G)), dim3(256), 0, f.st, a, tilemax, G);
+    hipLaunchKernelGGL(k_final, dim3((unsigned)a.nprob), dim3(256), 0, f.st, a, a.best, G, f.thr, f.obj, f.status, 0);
+}
+
+static int recheck_groups(const Args &a)
+{
+    const int want = std::max(8, std::min(256, 1024 / std::max(a.nprob, 1)));
+    return std::max(1, std::min(want, a.tiles * 7 / 8));
+}
+
+template <int COLS>
+static void launch_fp32(bool fused, const Args &a, const Tune &t, const Fp32Launch &f)
+{
+    if (fused) {
+        if (a.k == 1)
+            launch_fused<COLS, 1>(a, t.search_block, f);
+        else
+            launch_fused<COLS, 2>(a, t.search_block, f);
+        return;
+    }
+    const int64_t waves = (int64_t)a.nprob * a.tiles;
+    const dim3 g((unsigned)((waves + 3) / 4));
+    launch_setup(a, f);
+    if (a.k == 1) {
+        hipLaunchKernelGGL((k_tiles32<COLS, 1>), g, dim3(256), 0, f.st, a);
+        launch_recheck<COLS, 1>(a, a.tmax, recheck_groups(a), f);
     } else { // k = 3 uses k_rows3
-        hipLaunchKernelGGL((k_tiles32<COLS, 1, 2>), g, dim3(256), 0, st, a);
-        hipLaunchKernelGGL((k_tiles32<COLS, 2, 2>), g, dim3(256), 0, st, a);
+        hipLaunchKernelGGL((k_tiles32<COLS, 2>), g, dim3(256), 0, f.st, a);
+        launch_recheck<COLS, 2>(a, a.tmax, recheck_groups(a), f);
     }
 }
 
-static void launch_fp32_cols(int cols, int fused, int k, dim3 g, hipStream_t st, const Args &a, int32_t *thr,
-                             double *obj, int32_t *status)
+// The FP32 search with its re-check (both modes), planned as p.
+static void launch_fp32_search(const Plan &p, bool fused, const Args &a, const Tune &t, const Fp32Launch &f)
 {
-    if (cols == 1)
-        launch_fp32<1>(fused, k, g, st, a, thr, obj, status);
-    else if (cols == 2)
-        launch_fp32<2>(fused, k, g, st, a, thr, obj, status);
-    else
-        launch_fp32<4>(fused, k, g, st, a, thr, obj, status);
+    if (a.k == 3) {
+        const int G = recheck_groups(a);
+        float *tilemax = (float *)(a.best + (int64_t)a.nprob * G);
+        launch_setup(a, f);
+        hipLaunchKernelGGL(k_rows3, dim3((unsigned)((int64_t)(a.L - 3) * p.NC * a.nprob)), dim3(K3_THREADS),
+                           (size_t)p.Lp * sizeof(float), f.st, a, tilemax);
+        launch_recheck<K3_COLS, 3>(a, tilemax, G, f);
+    } else if (t.search_cols == 1) {
+        launch_fp32<1>(fused, a, t, f);
+    } else if (t.search_cols == 2) {
+        launch_fp32<2>(fused, a, t, f);
+    } else {
+        launch_fp32<4>(fused, a, t, f);
+    }
 }
 
 QConst make_qconst(double q, int L)
@@ -2766,13 +2945,16 @@ QConst make_qconst(double q, int L)
 }
 
 // One workgroup per problem (k_fused, nothing in the workspace) when that
-// fills the chip or the problem is small, unless the tuning forces a path.
+// fills the chip or the problem is small, unless the tuning forces a path.  At
+// k = 2 the one workgroup takes 17 to 23 us up to 384 levels, for one problem
+// as for 250, against 19 to 45 over several launches; 24 to 28 at 512 levels,
+// against 20 for one problem, 27 for 16 and 41 for 82.
 static bool fused_path(const Plan &p, int nprob, const Tune &t)
 {
     const bool fp32 = p.mode == TS_SEARCH_FP32_TIECHECK || p.mode == TS_SEARCH_FP32_ONLY;
     const bool can_fuse = fp32 && p.tiles <= FUSED_MAX_TILES && p.Lp <= FUSED_MAX_L &&
                           (p.k == 1 || (p.k == 2 && p.L <= FUSED_MAX_L2));
-    return can_fuse && (t.search_path == 1 || (t.search_path == 0 && (p.k == 1 || nprob >= 128)));
+    return can_fuse && (t.search_path == 1 || (t.search_path == 0 && (p.k == 1 || p.L <= 384 || nprob >= 16)));
 }
 
 size_t search_need_bytes(int nprob, int L, int k, int mode, const Tune &t)
@@ -2781,25 +2963,20 @@ size_t search_need_bytes(int nprob, int L, int k, int mode, const Tune &t)
     return fused_path(p, nprob, t) ? 0 : p.bytes;
 }
 
-ts_status launch_search(const double *P, const double *Q, int nseg, int L, int k, int nq, const double *q, int mode,
-                        void *ws, size_t ws_bytes, int32_t *thr, double *obj, int32_t *status, const Tune &t,
-                        hipStream_t st)
+static Args plan_args(const Plan &p, const double *P, const double *Q, int nseg, int nq, const double *q, void *ws)
 {
-    (void)ws_bytes;
-    const int nprob = nq * nseg;
-    const Plan p = make_plan(nprob, L, k, mode, t.search_cols, t.search_rows);
     char *base = (char *)ws;
     Args a;
     a.P = P;
     a.Q = Q;
     a.nseg = nseg;
-    a.nprob = nprob;
-    a.L = L;
+    a.nprob = nq * nseg;
+    a.L = p.L;
     a.Lp = p.Lp;
-    a.k = k;
-    a.mode = mode;
+    a.k = p.k;
+    a.mode = p.mode;
     for (int j = 0; j < TS_MAX_Q; ++j)
-        a.qc[j] = make_qconst(q[j < nq ? j : 0], L);
+        a.qc[j] = make_qconst(q[j < nq ? j : 0], p.L);
     a.CW = p.CW;
     a.NB = p.NB;
     a.NC = p.NC;
@@ -2813,6 +2990,40 @@ ts_status launch_search(const double *P, const double *Q, int nseg, int L, int k
     a.R = base + p.off_R;
     a.tmax = (float *)(base + p.off_tmax);
     a.best = (Best *)(base + p.off_best);
+    return a;
+}
+
+// ts_segment's prefix sums and search from the histograms: in the search's own
+// launches for the FP32 search, as separate calls for the other modes.
+static ts_status launch_scan_search(const uint32_t *hist, double *P, double *Q, int nseg, int L, int k, int nq,
+                                    const double *q, int mode, void *ws, int32_t *thr, double *obj, int32_t *status,
+                                    const Tune &t, hipStream_t st)
+{
+    if (mode == TS_SEARCH_FP32_TIECHECK || mode == TS_SEARCH_FP32_ONLY) {
+        const Plan p = make_plan(nseg * nq, L, k, mode, t.search_cols, t.search_rows);
+        const bool fused = fused_path(p, nseg * nq, t);
+        if (!fused || scan_fused_lds(L, p.Lp, k, p.tiles) <= SEG_MAX_LDS) {
+            launch_fp32_search(p, fused, plan_args(p, P, Q, nseg, nq, q, ws), t,
+                               Fp32Launch{hist, P, Q, thr, obj, status, st});
+            return check_launch("ts_segment");
+        }
+    }
+    const ts_status e = launch_prefix(hist, nseg, L, nq, q, P, Q, st);
+    if (e != TS_OK)
+        return e;
+    return launch_search(P, Q, nseg, L, k, nq, q, mode, ws, search_workspace_bytes(nseg * nq, L, k, mode, 4), thr, obj,
+                         status, t, st);
+}
+
+ts_status launch_search(const double *P, const double *Q, int nseg, int L, int k, int nq, const double *q, int mode,
+                        void *ws, size_t ws_bytes, int32_t *thr, double *obj, int32_t *status, const Tune &t,
+                        hipStream_t st)
+{
+    (void)ws_bytes;
+    const int nprob = nq * nseg;
+    const Plan p = make_plan(nprob, L, k, mode, t.search_cols, t.search_rows);
+    const Args a = plan_args(p, P, Q, nseg, nq, q, ws);
+    char *base = (char *)ws;
 
     if (mode == TS_SEARCH_SUMPROD) {
         const int per = sumprod_blocks(L, k);
@@ -2854,37 +3065,24 @@ ts_status launch_search(const double *P, const double *Q, int nseg, int L, int k
         return check_launch("ts_threshold_search (plain)");
     }
 
-    const bool fp32 = mode == TS_SEARCH_FP32_TIECHECK || mode == TS_SEARCH_FP32_ONLY;
-    const bool fused = fused_path(p, nprob, t);
-    const int64_t waves = (int64_t)nprob * p.tiles;
-    dim3 g((unsigned)((waves + 3) / 4));
-    if (fused) {
-        launch_fp32_cols(t.search_cols, t.search_block, k, g, st, a, thr, obj, status);
+    if (mode == TS_SEARCH_FP32_TIECHECK || mode == TS_SEARCH_FP32_ONLY) {
+        launch_fp32_search(p, fused_path(p, nprob, t), a, t,
+                           Fp32Launch{nullptr, nullptr, nullptr, thr, obj, status, st});
         return check_launch("ts_threshold_search");
     }
+    const int64_t waves = (int64_t)nprob * p.tiles;
+    const dim3 g((unsigned)((waves + 3) / 4));
     hipLaunchKernelGGL(k_setup, dim3(nprob), dim3(256), 0, st, a);
-    if (k == 3 && mode == TS_SEARCH_FP64) {
+    if (k == 3) {
         dim3 gp((unsigned)((int64_t)(L - 3) * nprob));
         hipLaunchKernelGGL(k_pairs64, gp, dim3(256), 0, st, a);
     }
-    if (k == 3 && fp32) {
-        dim3 gr((unsigned)((int64_t)(L - 3) * p.NC * nprob));
-        const size_t lds = (size_t)p.Lp * sizeof(float);
-        hipLaunchKernelGGL(k_rows3<1>, gr, dim3(K3_THREADS), lds, st, a);
-        hipLaunchKernelGGL(k_rows3<2>, gr, dim3(K3_THREADS), lds, st, a);
-        hipLaunchKernelGGL(k_final, dim3(nprob), dim3(1024), 0, st, a, a.best, p.tiles, thr, obj, status, 0);
-        return check_launch("ts_threshold_search");
-    }
-    if (mode == TS_SEARCH_FP64) {
-        if (t.search_cols == 1)
-            hipLaunchKernelGGL(k_tiles64<1>, g, dim3(256), 0, st, a);
-        else if (t.search_cols == 2)
-            hipLaunchKernelGGL(k_tiles64<2>, g, dim3(256), 0, st, a);
-        else
-            hipLaunchKernelGGL(k_tiles64<4>, g, dim3(256), 0, st, a);
-    } else {
-        launch_fp32_cols(t.search_cols, 0, k, g, st, a, thr, obj, status);
-    }
+    if (t.search_cols == 1)
+        hipLaunchKernelGGL(k_tiles64<1>, g, dim3(256), 0, st, a);
+    else if (t.search_cols == 2)
+        hipLaunchKernelGGL(k_tiles64<2>, g, dim3(256), 0, st, a);
+    else
+        hipLaunchKernelGGL(k_tiles64<4>, g, dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_final, dim3(nprob), dim3(1024), 0, st, a, a.best, p.tiles, thr, obj, status, 0);
     return check_launch("ts_threshold_search");
 }
