@@ -87,7 +87,7 @@ ts_status resolve_tuning(const ts_tuning *t, int nbins, Tune *o)
     o->search_rows = t->search_rows ? t->search_rows : 16;
     o->min_chunk = t->min_chunk ? t->min_chunk : 8192;
     o->search_path = t->search_path;
-    o->search_block = t->search_block ? t->search_block : 512;
+    o->search_block = t->search_block; // 0: by the number of problems, at the launch
     o->segment_parts = t->segment_parts;
     o->segment_block = t->segment_block;
     if (o->hist_block < 64 || o->hist_block > 1024 || o->hist_block % 64)
@@ -110,7 +110,7 @@ ts_status resolve_tuning(const ts_tuning *t, int nbins, Tune *o)
         return fail(TS_ERR_INVALID_ARG, "tuning: min_chunk must be >= 512");
     if (o->search_path < 0 || o->search_path > 2)
         return fail(TS_ERR_INVALID_ARG, "tuning: search_path must be 0, 1 or 2");
-    if (o->search_block != 256 && o->search_block != 512 && o->search_block != 1024)
+    if (o->search_block != 0 && o->search_block != 256 && o->search_block != 512 && o->search_block != 1024)
         return fail(TS_ERR_INVALID_ARG, "tuning: search_block must be 256, 512 or 1024");
     if (o->segment_parts < 0 || o->segment_parts > 64)
         return fail(TS_ERR_INVALID_ARG, "tuning: segment_parts must be in [1, 64]");

@@ -479,6 +479,85 @@ __device__ __forceinline__ Steps head_tail32(const Args &a, const QConst &c, con
     return r;
 }
 
+// The same rows for the bins that can be thresholds only, in order: n of them,
+// row i being bin bins[i].  A bin that repeats P and Q of the bin before it
+// bounds the same classes as that one, the class between the two is empty, so
+// its tuples tie exactly, in both precisions, with tuples that come first.
+// Entries from n up to the next multiple of 256 past n hold no threshold
+// (-inf).  cnt holds one count per 64 bins.
+template <int SGN>
+__device__ __forceinline__ Steps head_tail_occupied(const Args &a, const QConst &c, const double *P, const double *Q,
+                                                    float *hd, float *tl, float4 *hl, unsigned short *bins, int *cnt,
+                                                    int &n, double *red, double *pl, double *ql)
+{
+    const int L = a.L, lane = threadIdx.x & 63;
+    const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    auto before = [](const double *X, int t) { return t ? X[t - 1] : 0.0; };
+    auto occupied = [&](int t) {
+        return t <= L - 2 && !(P[t] == before(P, t) && Q[t] == before(Q, t));
+    };
+    double pm = 1.0, qm = INFINITY;
+#pragma unroll 1
+    for (int t0 = 0; t0 < L; t0 += blockDim.x) {
+        const int t = t0 + threadIdx.x;
+        if (t < L) {
+            const double p = P[t], q = Q[t];
+            const double dps = p - before(P, t), dqs = fabs(q - before(Q, t)); // Shannon: Q falls
+            if (dps > 0.0)
+                pm = fmin(pm, dps);
+            if (dqs > 0.0)
+                qm = fmin(qm, dqs);
+            if (pl) {
+                pl[t] = p;
+                ql[t] = q;
+            }
+        }
+        const unsigned long long m = __ballot(t < L && occupied(t));
+        if (lane == 0 && t < L)
+            cnt[t >> 6] = __popcll(m);
+    }
+    pm = wave_min_f64(pm);
+    qm = wave_min_f64(qm);
+    const int nw = blockDim.x >> 6;
+    if (lane == 0) {
+        red[threadIdx.x >> 6] = pm;
+        red[nw + (threadIdx.x >> 6)] = qm;
+    }
+    __syncthreads();
+    const float4 last = split_hl(P[L - 1], Q[L - 1]);
+    n = 0;
+    for (int i = 0; i < (L + 63) >> 6; ++i)
+        n += cnt[i];
+    n = __builtin_amdgcn_readfirstlane(n);
+#pragma unroll 1
+    for (int t0 = 0; t0 < L; t0 += blockDim.x) {
+        const int t = t0 + threadIdx.x;
+        const bool occ = t < L && occupied(t);
+        const unsigned long long m = __ballot(occ);
+        if (occ) {
+            int i = __popcll(m & ((1ull << lane) - 1ull));
+            for (int j = 0; j < t >> 6; ++j)
+                i += cnt[j];
+            const float4 h4 = split_hl(P[t], Q[t]);
+            hd[i] = cls32<SGN>(h4, zero, c.mq, c.gmax);
+            tl[i] = cls32<SGN>(last, h4, c.mq, c.gmax);
+            hl[i] = h4;
+            bins[i] = (unsigned short)t;
+        }
+    }
+    for (int i = n + threadIdx.x; i < ((n + 256) & ~255); i += blockDim.x) { // n <= L - 1: within Lp
+        hd[i] = tl[i] = -INFINITY;
+        hl[i] = zero;
+    }
+    Steps r = {red[0], red[nw]};
+    for (int i = 1; i < nw; ++i) {
+        r.pmin = fmin(r.pmin, red[i]);
+        r.dqmin = fmin(r.dqmin, red[nw + i]);
+    }
+    __syncthreads();
+    return r;
+}
+
 // Ms - 3 delta rounded down; -inf (nothing pruned) unless both are finite.
 __device__ __forceinline__ float prune_threshold(float Ms, float delta)
 {
@@ -663,9 +742,13 @@ struct TileCtx {
     const float4 *hl;     // split prefixes (LDS or global)
     const float *A, *R;   // k = 3 rows of the problem (global)
     const unsigned long long *prune; // k = 2: rows skipped in phase 1, [NB][Lp / 64] bit words (or null)
+    const unsigned short *bins; // bin of each row and column (or null: the same)
     int L, Lp, mode, CW, T1;
+    int Lb; // bins of P and Q (L counts rows and columns, one past the last threshold)
     double q, sgn, hmax;
     float mq, gmax, cw;
+
+    __device__ __forceinline__ int bin(int t) const { return bins ? (int)bins[t] : t; }
 };
 
 __device__ __forceinline__ TileCtx make_ctx(const Args &a, int s, const float *hd, const float *tr,
@@ -692,6 +775,8 @@ __device__ __forceinline__ TileCtx make_ctx(const Args &a, int s, const float *h
     x.gmax = c.gmax;
     x.cw = c.cw;
     x.prune = nullptr;
+    x.bins = nullptr;
+    x.Lb = a.L;
     return x;
 }
 
@@ -714,8 +799,8 @@ __device__ __forceinline__ void take(const TileCtx &x, float key, float thr, flo
     if (PHASE == 1) {
         acc = fmaxf(acc, key);
     } else if (rechecked(is_tuple, key, thr)) {
-        const int t[3] = {t1, t2, t3};
-        const double lam = lambda64_k<K>(x.P, x.Q, x.L, t, x.q, x.sgn, x.hmax);
+        const int t[3] = {x.bin(t1), K > 1 ? x.bin(t2) : t2, K > 2 ? x.bin(t3) : t3};
+        const double lam = lambda64_k<K>(x.P, x.Q, x.Lb, t, x.q, x.sgn, x.hmax);
         const double rank = x.mode == TS_SEARCH_FP32_ONLY ? (double)key : lam;
         const long long code = make_code(K, t);
         if (better(rank, code, b.r, b.c)) {
@@ -751,8 +836,8 @@ __device__ __forceinline__ void take_cols(const TileCtx &x, const float (&key)[C
                 tl = tv[w];
                 kv = key[w];
             }
-        const int t[3] = {t1, K == 2 ? tl : t2, tl};
-        const double lam = lambda64_k<K>(x.P, x.Q, x.L, t, x.q, x.sgn, x.hmax);
+        const int t[3] = {x.bin(t1), x.bin(K == 2 ? tl : t2), x.bin(tl)};
+        const double lam = lambda64_k<K>(x.P, x.Q, x.Lb, t, x.q, x.sgn, x.hmax);
         const double rank = x.mode == TS_SEARCH_FP32_ONLY ? (double)kv : lam;
         const long long code = make_code(K, t);
         if (better(rank, code, b.r, b.c)) {
@@ -1262,6 +1347,8 @@ struct FusedLds {
     float wmax[FUSED_THREADS / 64];
     float wseed[FUSED_THREADS / 64];
     unsigned long long prune[PRUNE_WORDS];
+    unsigned short bins[FUSED_MAX_L2];  // k = 2: bins that can be thresholds
+    int cnt[FUSED_MAX_L2 / 64];
     double wr[FUSED_THREADS / 64], wl[FUSED_THREADS / 64];
     long long wc[FUSED_THREADS / 64];
     float sdelta;
@@ -1356,15 +1443,30 @@ __device__ __forceinline__ long long fused_body(const Args &a, FusedLds &sh, int
     float *hd = sh.hd, *tr = sh.tr, *tmax = sh.tmax, *wmax = sh.wmax;
     float4 *hls = sh.hls;
     const QConst &qc = a.qc[s / a.nseg];
-    // k = 2: split prefixes (and FP64 prefixes, when staged) in LDS
-    const Steps stp = head_tail32<SGN>(a, qc, P, Q, hd, tr, K == 2 ? hls : nullptr, sh.red,
-                                       K == 2 && stage ? sh.pd : nullptr, K == 2 && stage ? sh.qd : nullptr);
+    // k = 2: split prefixes (and FP64 prefixes, when staged) in LDS, and only
+    // the bins that can be thresholds (CT slices of 256 levels over the airway
+    // window: about 130, a quarter of the tuples)
     TileCtx x = make_ctx(a, s, hd, tr, hls);
+    int NB = a.NB, NC = a.NC;
+    Steps stp;
+    if constexpr (K == 2) {
+        int n;
+        stp = head_tail_occupied<SGN>(a, qc, P, Q, hd, tr, hls, sh.bins, sh.cnt, n, sh.red, stage ? sh.pd : nullptr,
+                                      stage ? sh.qd : nullptr);
+        x.bins = sh.bins;
+        x.L = n + 1;
+        x.Lp = (n + 256) & ~255;
+        NB = (n + a.CW - 1) / a.CW; // at most the plan's
+        NC = (max(n - 1, 1) + a.T1 - 1) / a.T1;
+    } else {
+        stp = head_tail32<SGN>(a, qc, P, Q, hd, tr, nullptr, sh.red);
+    }
+    const int tiles = NB * NC;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int nw = blockDim.x >> 6;
     const bool prune = K == 2 && a.mode == TS_SEARCH_FP32_TIECHECK && a.NB * (a.Lp >> 6) <= PRUNE_WORDS;
-    if (prune) { // the rows are in LDS (head_tail32 ends with a barrier)
+    if (prune) { // the rows are in LDS (head_tail_occupied ends with a barrier)
         const float sk = wave_max(seed_key<SGN>(x));
         if (lane == 0)
             sh.wseed[w] = sk;
@@ -1380,7 +1482,7 @@ __device__ __forceinline__ long long fused_body(const Args &a, FusedLds &sh, int
             ms = fmaxf(ms, sh.wseed[i]);
         const float pthr = prune_threshold(ms, sh.sdelta); // the same in every thread
         if (pthr > -INFINITY) {
-            prune_rows<SGN>(x, a.NB, pthr, sh.prune);
+            prune_rows<SGN>(x, NB, pthr, sh.prune);
             __syncthreads();
             x.prune = sh.prune;
         }
@@ -1401,10 +1503,10 @@ __device__ __forceinline__ long long fused_body(const Args &a, FusedLds &sh, int
         if (lane == 0)
             t = atomicAdd(&sh.next, 1);
         t = __builtin_amdgcn_readfirstlane(t);
-        if (t >= a.tiles)
+        if (t >= tiles)
             break;
-        const int b = a.NB - 1 - t / a.NC, c = t % a.NC;
-        const int tile = c * a.NB + b;
+        const int b = NB - 1 - t / NC, c = t % NC;
+        const int tile = c * NB + b;
         float acc = -INFINITY;
         tile_body<SGN, COLS, 1, K>(x, b, c, 0.0f, acc, best);
         acc = wave_max(acc);
@@ -1424,18 +1526,18 @@ __device__ __forceinline__ long long fused_body(const Args &a, FusedLds &sh, int
         // typically one); k = 1: the i-th goes to wavefront i mod nw; k = 2:
         // every wavefront takes a share of the rows of each of them
         int nth = 0;
-        for (int base = 0; base < a.tiles; base += 64) {
+        for (int base = 0; base < tiles; base += 64) {
             const int t = base + lane;
-            unsigned long long m = __ballot(t < a.tiles && tmax[t] >= thr);
+            unsigned long long m = __ballot(t < tiles && tmax[t] >= thr);
             while (m) {
                 const int tile = base + __builtin_ctzll(m);
                 m &= m - 1;
                 float acc = -INFINITY;
                 if (K == 1) {
                     if (nth++ % nw == w)
-                        tile_body<SGN, COLS, 2, K>(x, tile % a.NB, tile / a.NB, thr, acc, best);
+                        tile_body<SGN, COLS, 2, K>(x, tile % NB, tile / NB, thr, acc, best);
                 } else {
-                    tile_k2<SGN, COLS, 2>(x, tile % a.NB, tile / a.NB, thr, acc, best, w, nw);
+                    tile_k2<SGN, COLS, 2>(x, tile % NB, tile / NB, thr, acc, best, w, nw);
                 }
             }
         }
@@ -1489,8 +1591,8 @@ __global__ void __launch_bounds__(FUSED_THREADS) k_fused(Args a, int32_t *__rest
 // prefix sums stay in LDS.  The same bins per thread as the prefix pass, hence
 // the same bits.  Dynamic LDS (scan_fused_lds): the scan's scratch, later the
 // search's rows | P [Lp] | Q [Lp].  82 problems of 200 levels, k = 2:
-// 19.3 us, against 4.8 for the prefix pass and 28 for the search in four
-// launches; 900 of 256 levels 37.4 against 6.8 and 32.8.
+// 18.2 us, against 4.8 for the prefix pass and 28 for the search in four
+// launches; 900 of 256 levels 33.5 against 6.8 and 32.8.
 template <int COLS, int K>
 __global__ void __launch_bounds__(FUSED_THREADS) k_scan_fused(Args a, const uint32_t *__restrict__ hist, int E,
                                                               int area, int32_t *__restrict__ thr_out,
@@ -2840,6 +2942,11 @@ template <int COLS, int K>
 static void launch_fused(const Args &a, int block, const Fp32Launch &f)
 {
     const dim3 g((unsigned)a.nprob);
+    // 512 threads finish a problem sooner (82 problems of 200 levels, k = 2:
+    // 18 against 20 us), 256 more of them at once where several share a CU (900
+    // of 256 levels: 33 against 43 us)
+    if (!block)
+        block = a.nprob > 2 * device_cu_count() ? 256 : 512;
     if (!f.hist) {
         hipLaunchKernelGGL((k_fused<COLS, K>), g, dim3((unsigned)block), fused_lds_bytes(a.Lp, K, a.tiles), f.st, a,
                            f.thr, f.obj, f.status);
