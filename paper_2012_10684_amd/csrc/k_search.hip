@@ -231,15 +231,19 @@ __device__ __forceinline__ double lambda64_k(const double *P, const double *Q, i
                                              double sgn, double hmax)
 {
     const int t0 = t[0], t1 = K > 1 ? t[1] : 0, t2 = K > 2 ? t[2] : 0;
-    // every boundary's sums in one round of loads
-    const double p0 = P[t0], p1 = K > 1 ? P[t1] : 0.0, p2 = K > 2 ? P[t2] : 0.0, pL = P[L - 1];
-    const double q0 = Q[t0], q1 = K > 1 ? Q[t1] : 0.0, q2 = K > 2 ? Q[t2] : 0.0, qL = Q[L - 1];
+    // k = 3, from global memory: every boundary's sums in one round of loads
+    double pt[4], qt[4];
+    if (K == 3) {
+        pt[0] = P[t0], pt[1] = P[t1], pt[2] = P[t2], pt[3] = P[L - 1];
+        qt[0] = Q[t0], qt[1] = Q[t1], qt[2] = Q[t2], qt[3] = Q[L - 1];
+    }
     double acc = 0.0;
     double pa = 0.0, qa = 0.0;
 #pragma unroll 1
     for (int j = 0; j <= K; ++j) {
-        const double pb = j == K ? pL : (j == 0 ? p0 : (j == 1 ? p1 : p2));
-        const double qb = j == K ? qL : (j == 0 ? q0 : (j == 1 ? q1 : q2));
+        const int b = j == K ? L - 1 : (j == 0 ? t0 : (j == 1 ? t1 : t2));
+        const double pb = K < 3 ? P[b] : (j == 3 ? pt[3] : (j == 0 ? pt[0] : (j == 1 ? pt[1] : pt[2])));
+        const double qb = K < 3 ? Q[b] : (j == 3 ? qt[3] : (j == 0 ? qt[0] : (j == 1 ? qt[1] : qt[2])));
         const double dP = pb - pa, dQ = qb - qa;
         if (!(dP > 0.0))
             return -INFINITY;
