@@ -64,7 +64,8 @@ __device__ __forceinline__ uint32_t pair_mid(uint32_t a, uint32_t b) { return __
 template <int CTRL, int ROWS>
 __device__ __forceinline__ uint32_t dpp32(uint32_t v)
 {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+    // where every row takes part the move itself fills in the zeros
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, ROWS == 0xf);
 }
 
 // How the rows are laid over a workgroup: row groups of 1 << gsh lanes (8
@@ -636,7 +637,6 @@ struct S2 {
     double q, sgn, hmax;
     const double *tab; // cterm of counts below S2_TAB
     double *big;       // cterm of the cells with larger counts, [L][L] (workspace, t2's place until pass 3)
-    const uint32_t *band; // per row: lowest | highest column holding counts << 16 (LDS)
     float mq;          // -q rounded to FP32 (Tsallis)
     float sg;          // sgn(1-q) as +-1 (Tsallis)
     float gmax;        // hmax / ln 2 rounded up
@@ -698,15 +698,12 @@ __device__ __forceinline__ double s2_delta(const S2 &p, double N)
 // (clamped addresses, masked values) so that several rows' loads can be in
 // flight at once.
 template <int DIR>
-__device__ __forceinline__ void load_row(const uint32_t *h, int L, bool vec, int t, uint32_t (&c)[S2_CPL],
-                                         const uint32_t *band)
+__device__ __forceinline__ void load_row(const uint32_t *h, int L, bool vec, int t, int jlo, int jhi,
+                                         uint32_t (&c)[S2_CPL])
 {
     const int lane = threadIdx.x & 63;
     const uint32_t *row = h + (int64_t)t * L;
-    // columns outside the row's band hold no counts: those lanes load nothing
-    // (band null: every column)
-    const uint32_t bd = band ? band[t] : 0xffff0000u;
-    const int jlo = (int)(bd & 0xffffu), jhi = (int)(bd >> 16);
+    // columns outside [jlo, jhi] hold no counts: those lanes load nothing
     const int c0 = DIR > 0 ? S2_CPL * lane : L - S2_CPL - S2_CPL * lane; // the lane's lowest column (vec)
     if (vec) {
         const bool ok = S2_CPL * lane < L && c0 <= jhi && c0 + S2_CPL - 1 >= jlo;
@@ -731,6 +728,22 @@ template <typename T>
 __device__ __forceinline__ T pick(const T (&v)[S2_CPL], int u)
 {
     return u == 0 ? v[0] : u == 1 ? v[1] : u == 2 ? v[2] : v[3];
+}
+
+// A listed row: the row | the lowest column of its band << 8 | the highest <<
+// 16 (levels are below 256), read once as a scalar.
+struct S2Row {
+    int t, lo, hi;
+};
+__device__ __forceinline__ S2Row listed(const uint32_t *rows, int k)
+{
+    const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)rows[k]);
+    return S2Row{(int)(v & 0xffu), (int)((v >> 8) & 0xffu), (int)(v >> 16)};
+}
+template <int DIR>
+__device__ __forceinline__ void load_row(const S2 &p, const S2Row &r, uint32_t (&c)[S2_CPL])
+{
+    load_row<DIR>(p.h, p.L, p.vec, r.t, r.lo, r.hi, c);
 }
 
 // The terms of a row's counts: from the table for small counts (which holds
@@ -771,7 +784,7 @@ __device__ __forceinline__ void row_terms(const S2 &p, int t, const uint32_t (&c
 // flight meanwhile.  Past the last row the ring reloads the last row and its
 // sums are discarded.
 template <int DIR, typename CT, typename A, typename F>
-__device__ __forceinline__ void for_rows(const S2 &p, const int *rows, int k0, int n, A &&aux, F &&f)
+__device__ __forceinline__ void for_rows(const S2 &p, const uint32_t *rows, int k0, int n, A &&aux, F &&f)
 {
     if (n <= 0)
         return;
@@ -780,7 +793,7 @@ __device__ __forceinline__ void for_rows(const S2 &p, const int *rows, int k0, i
 #pragma unroll
     for (int d = 0; d < S2_RING; ++d) {
         const int kk = k0 + DIR * min(d, n - 1);
-        load_row<DIR>(p.h, p.L, p.vec, rows[kk], ring[d], p.band);
+        load_row<DIR>(p, listed(rows, kk), ring[d]);
         aux(kk, xr[d]);
     }
     for (int i0 = 0; i0 < n; i0 += S2_RING) {
@@ -796,11 +809,11 @@ __device__ __forceinline__ void for_rows(const S2 &p, const int *rows, int k0, i
                     x[u] = xr[d][u];
                 }
                 const int kk = k0 + DIR * min(i + S2_RING, n - 1);
-                load_row<DIR>(p.h, p.L, p.vec, rows[kk], ring[d], p.band);
+                load_row<DIR>(p, listed(rows, kk), ring[d]);
                 aux(kk, xr[d]);
                 CT rc[S2_CPL];
                 double rq[S2_CPL], t[S2_CPL];
-                row_terms<DIR, false>(p, rows[k0 + DIR * i], c, t);
+                row_terms<DIR, false>(p, listed(rows, k0 + DIR * i).t, c, t);
                 row_sums<CT>(c, t, rc, rq);
                 f(k0 + DIR * i, rc, rq, x);
             }
@@ -812,7 +825,7 @@ __device__ __forceinline__ void for_rows(const S2 &p, const int *rows, int k0, i
 // columns S2_CPL * lane + u: count sums and sums of cterm; leaves the terms of
 // the counts past the table in p.big for the later walks.
 template <typename CT>
-__device__ __forceinline__ void block_totals(const S2 &p, const int *rows, int k0, int n, CT (&cc)[S2_CPL],
+__device__ __forceinline__ void block_totals(const S2 &p, const uint32_t *rows, int k0, int n, CT (&cc)[S2_CPL],
                                              double (&cq)[S2_CPL])
 {
 #pragma unroll
@@ -825,7 +838,7 @@ __device__ __forceinline__ void block_totals(const S2 &p, const int *rows, int k
     uint32_t ring[S2_RING][S2_CPL];
 #pragma unroll
     for (int d = 0; d < S2_RING; ++d)
-        load_row<1>(p.h, p.L, p.vec, rows[k0 + min(d, n - 1)], ring[d], p.band);
+        load_row<1>(p, listed(rows, k0 + min(d, n - 1)), ring[d]);
     for (int i0 = 0; i0 < n; i0 += S2_RING) {
 #pragma unroll
         for (int d = 0; d < S2_RING; ++d) {
@@ -839,9 +852,9 @@ __device__ __forceinline__ void block_totals(const S2 &p, const int *rows, int k
                     c[u] = ring[d][u];
                     big |= c[u] >= (uint32_t)S2_TAB;
                 }
-                load_row<1>(p.h, p.L, p.vec, rows[k0 + min(i + S2_RING, n - 1)], ring[d], p.band);
+                load_row<1>(p, listed(rows, k0 + min(i + S2_RING, n - 1)), ring[d]);
                 if (__ballot(big)) {
-                    const int at = rows[k0 + i] * p.L + S2_CPL * (threadIdx.x & 63);
+                    const int at = listed(rows, k0 + i).t * p.L + S2_CPL * (threadIdx.x & 63);
 #pragma unroll 1
                     for (int u = 0; u < S2_CPL; ++u) {
                         const uint32_t x = pick(c, u);
@@ -849,7 +862,7 @@ __device__ __forceinline__ void block_totals(const S2 &p, const int *rows, int k
                             p.big[at + u] = cterm(x, p.q);
                     }
                 }
-                row_terms<1, false>(p, rows[k0 + i], c, t);
+                row_terms<1, false>(p, listed(rows, k0 + i).t, c, t);
 #pragma unroll
                 for (int u = 0; u < S2_CPL; ++u) {
                     cc[u] += c[u];
@@ -888,8 +901,7 @@ struct S2Lds {
     double tab[S2_TAB];               // cterm of counts below S2_TAB
     double tq[2][NW][H2_MAX_L];       // per block and column: sums of cterm of the blocks before ([0]) and after ([1])
     CT tc[NW + 1][H2_MAX_L];          // count sums of the blocks before (exact: those after are the rest)
-    uint32_t band[H2_MAX_L];          // each row's band of columns holding counts
-    int rows[H2_MAX_L];               // rows holding counts, increasing
+    uint32_t rows[H2_MAX_L];          // rows holding counts, increasing, as listed rows (S2Row)
     float rmax[H2_MAX_L];             // best pair key of each listed row
     float wm[NW];                     // per-wavefront maxima
     double wb[NW];                    // per-wavefront best FP64 pair
@@ -921,8 +933,8 @@ typedef v4f v4f_any __attribute__((aligned(4)));
 
 // Bounded by its vector operations, about 190 per row, wavefront and pass (a
 // third of them the FP64 sums along s), four clocks each: 900 problems
-// of 256 levels (132 rows with counts) 288 -> 209 us with the row pass, 37 of
-// 200 levels 103 -> 56 us.  What changed: one walk for both directions' column
+// of 256 levels (132 rows with counts) 288 -> 201 us with the row pass, 37 of
+// 200 levels 103 -> 55 us.  What changed: one walk for both directions' column
 // totals, rows' terms past the table kept instead of formed by calls in the
 // walks, constants of a problem in scalar registers (128 vector registers: four
 // wavefronts per SIMD), two or four times the wavefronts per problem.
@@ -955,11 +967,11 @@ __device__ __forceinline__ void search2d_body(const S2 &p, double N, int R, S2Ld
 {
     const int lane = threadIdx.x & 63, L = p.L;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int *rows = sh.rows;
+    const uint32_t *rows = sh.rows;
     float *rmax = sh.rmax;
     const int posl = S2_CPL * lane; // the lane's first scan position
     const int colB0 = L - 1 - posl; // its column in suffix order; position u's is colB0 - u (negative: none)
-    const int kB = rows[0] == 0 ? 1 : 0; // class 2 starts at row 1 at the earliest
+    const int kB = listed(rows, 0).t == 0 ? 1 : 0; // class 2 starts at row 1 at the earliest
     const int b0 = R * w / NW, b1 = R * (w + 1) / NW; // this wavefront's block
     const int bb = max(b0, kB), nb = b1 - bb;         // its class 2 rows (nb <= 0: none)
     const int na = min(b1, R - 1) - b0;               // its rows with pairs (rows[k] <= L - 2 follows)
@@ -967,7 +979,7 @@ __device__ __forceinline__ void search2d_body(const S2 &p, double N, int R, S2Ld
     // the stored class 2 keys at (rows[k + 1], s + 1) for the lane's columns
     // s; past the row the next one's (or what follows the keys), masked below
     auto partner = [&](int k, float(&x)[S2_CPL]) {
-        const float *row2 = k2 + (int64_t)rows[k + 1] * L; // k <= R - 2 in the pass that uses it
+        const float *row2 = k2 + (int64_t)listed(rows, k + 1).t * L; // k <= R - 2 in the pass that uses it
         if (p.vec) {
             const v4f v = *reinterpret_cast<const v4f_any *>(row2 + min(posl, L - S2_CPL) + 1);
 #pragma unroll
@@ -1023,7 +1035,7 @@ __device__ __forceinline__ void search2d_body(const S2 &p, double N, int R, S2Ld
         carry_in<-1>(sh, L, w, bc, bq);
         for_rows<-1, CT>(p, rows, b1 - 1, nb, none, [&](int k, const CT(&rc)[S2_CPL], const double(&rq)[S2_CPL],
                                                         const float(&)[S2_CPL]) {
-            float *row = k2 + (int64_t)rows[k] * L;
+            float *row = k2 + (int64_t)listed(rows, k).t * L;
             v4f key;
 #pragma unroll
             for (int u = 0; u < S2_CPL; ++u) {
@@ -1109,7 +1121,7 @@ __device__ __forceinline__ void search2d_body(const S2 &p, double N, int R, S2Ld
                                  }
                              });
             k = ke - 1;
-            double *row = t2 + (int64_t)rows[ke] * L;
+            double *row = t2 + (int64_t)listed(rows, ke).t * L;
 #pragma unroll 1
             for (int u = 0; u < S2_CPL; ++u)
                 if (colB0 - u >= 0)
@@ -1139,8 +1151,9 @@ __device__ __forceinline__ void search2d_body(const S2 &p, double N, int R, S2Ld
                 double t[S2_CPL], rq[S2_CPL];
                 CT rc[S2_CPL];
                 const float x[S2_CPL] = {};
-                load_row<1>(p.h, L, p.vec, rows[b0 + l], c, p.band);
-                row_terms<1, true>(p, rows[b0 + l], c, t);
+                const S2Row r = listed(rows, b0 + l);
+                load_row<1>(p, r, c);
+                row_terms<1, true>(p, r.t, c, t);
                 row_sums<CT>(c, t, rc, rq);
                 add(b0 + l, rc, rq, x);
                 if (l != le) {
@@ -1160,7 +1173,7 @@ __device__ __forceinline__ void search2d_body(const S2 &p, double N, int R, S2Ld
                 }
             }
             m4 &= m4 - 1;
-            const int k = b0 + le, t = rows[k], r2 = rows[k + 1];
+            const int k = b0 + le, t = listed(rows, k).t, r2 = listed(rows, k + 1).t;
             const float *row2 = k2 + (int64_t)r2 * L;
             const double *row2d = t2 + (int64_t)r2 * L;
 #pragma unroll 1
@@ -1233,7 +1246,7 @@ __global__ void __launch_bounds__(64) k_rows2d(const uint32_t *__restrict__ hist
     uint32_t c[16][S2_CPL];
 #pragma unroll
     for (int d = 0; d < 16; ++d) // rows past L reload row L-1 and count as empty
-        load_row<1>(h, L, vec, min(16 * g + d, L - 1), c[d], nullptr);
+        load_row<1>(h, L, vec, min(16 * g + d, L - 1), 0, L - 1, c[d]);
     uint32_t bits = 0, mine = 0xffffu; // lane d < 16 keeps row d's band
     uint64_t n = 0;
 #pragma unroll
@@ -1316,7 +1329,6 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 4 : 1)
     // table of terms and the rows' bands
     auto setup = [&](auto &sl) {
         p.tab = sl.tab;
-        p.band = sl.band;
         if (threadIdx.x < 64) {
             const uint32_t g16 = (4 * lane) / 16 < groups ? mask[(int64_t)s0 * 16 + (4 * lane) / 16] : 0u;
             uint32_t nib = (g16 >> ((4 * lane) % 16)) & 0xfu;
@@ -1325,16 +1337,16 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 4 : 1)
             uint32_t w = wave_excl_sum<uint32_t>((uint32_t)__popc(nib));
 #pragma unroll
             for (int d = 0; d < 4; ++d)
-                if (nib & (1u << d))
-                    sl.rows[w++] = 4 * lane + d;
+                if (nib & (1u << d)) {
+                    const uint32_t bd = band[(int64_t)s0 * L + 4 * lane + d];
+                    sl.rows[w++] = (uint32_t)(4 * lane + d) | (bd & 0xffu) << 8 | (bd >> 16) << 16;
+                }
             if (lane == 63)
                 sl.nrows = (int)w;
         }
 #pragma unroll 1
         for (int i = threadIdx.x; i < S2_TAB; i += blockDim.x)
             sl.tab[i] = cterm((uint32_t)i, p.q);
-        for (int i = threadIdx.x; i < L; i += blockDim.x)
-            sl.band[i] = band[(int64_t)s0 * L + i];
         __syncthreads();
         return __builtin_amdgcn_readfirstlane(sl.nrows);
     };
