@@ -72,7 +72,7 @@ struct Meta {
     int menc;    // ordered-int encoding of the problem's FP32 max key
     float delta; // bound on |key32 - key64 / ln 2|
     float pthr;  // k = 3: phase 1 skips row groups whose key bound is below this (-inf: none)
-    int pad1;
+    int n;       // k = 3: bins that can be thresholds
 };
 
 struct Best {
@@ -339,6 +339,7 @@ struct Args {
     void *head, *tail, *A, *R;
     float *tmax;
     Best *best;
+    unsigned short *bins; // k = 3: [nprob][L], the bins that can be thresholds (FP32 search)
 };
 
 // ---------------------------------------------------------------- setup
@@ -488,7 +489,8 @@ __device__ __forceinline__ Steps head_tail32(const Args &a, const QConst &c, con
 // bounds the same classes as that one, the class between the two is empty, so
 // its tuples tie exactly, in both precisions, with tuples that come first.
 // Entries from n up to the next multiple of 256 past n hold no threshold
-// (-inf).  cnt holds one count per 64 bins.
+// (-inf).  cnt holds one count per 64 bins.  Its barriers order LDS only: rows
+// in global memory are not read again by the same kernel.
 template <int SGN>
 __device__ __forceinline__ Steps head_tail_occupied(const Args &a, const QConst &c, const double *P, const double *Q,
                                                     float *hd, float *tl, float4 *hl, unsigned short *bins, int *cnt,
@@ -527,7 +529,7 @@ __device__ __forceinline__ Steps head_tail_occupied(const Args &a, const QConst 
         red[threadIdx.x >> 6] = pm;
         red[nw + (threadIdx.x >> 6)] = qm;
     }
-    __syncthreads();
+    lds_barrier();
     const float4 last = split_hl(P[L - 1], Q[L - 1]);
     n = 0;
     for (int i = 0; i < (L + 63) >> 6; ++i)
@@ -558,7 +560,7 @@ __device__ __forceinline__ Steps head_tail_occupied(const Args &a, const QConst 
         r.pmin = fmin(r.pmin, red[i]);
         r.dqmin = fmin(r.dqmin, red[nw + i]);
     }
-    __syncthreads();
+    lds_barrier();
     return r;
 }
 
@@ -582,10 +584,22 @@ __device__ __forceinline__ void setup_body(const Args &a, int s, const double *P
 {
     const QConst &c = a.qc[s / a.nseg];
     const int L = a.L, Lp = a.Lp;
+    __shared__ int cnt[MAX_BINS / 64];
+    int n = 0;
     Steps stp;
     if (a.mode == TS_SEARCH_FP64)
         stp = block_steps(P, Q, L, red);
-    else if (c.sgn > 0)
+    else if (a.k == 3) { // only the bins that can be thresholds
+        float *hd = (float *)a.head + (int64_t)s * Lp, *tl = (float *)a.tail + (int64_t)s * Lp;
+        float4 *hl = a.hl + (int64_t)s * Lp;
+        unsigned short *bins = a.bins + (int64_t)s * L;
+        if (c.sgn > 0)
+            stp = head_tail_occupied<1>(a, c, P, Q, hd, tl, hl, bins, cnt, n, red, nullptr, nullptr);
+        else if (c.sgn < 0)
+            stp = head_tail_occupied<-1>(a, c, P, Q, hd, tl, hl, bins, cnt, n, red, nullptr, nullptr);
+        else
+            stp = head_tail_occupied<0>(a, c, P, Q, hd, tl, hl, bins, cnt, n, red, nullptr, nullptr);
+    } else if (c.sgn > 0)
         stp = head_tail32<1>(a, c, P, Q, (float *)a.head + (int64_t)s * Lp, (float *)a.tail + (int64_t)s * Lp,
                              a.hl + (int64_t)s * Lp, red);
     else if (c.sgn < 0)
@@ -616,7 +630,7 @@ __device__ __forceinline__ void setup_body(const Args &a, int s, const double *P
             ghd[threadIdx.x] = cls(h, make_float4(0.0f, 0.0f, 0.0f, 0.0f));
             gtl[threadIdx.x] = cls(split_hl(P[L - 1], Q[L - 1]), h);
         }
-        __syncthreads();
+        lds_barrier();
         const int i = threadIdx.x / G, j = threadIdx.x % G;
         if (i < G && pos(i) < pos(j)) {
             const float ar = ghd[i] + cls(ghl[j], ghl[i]);
@@ -627,14 +641,14 @@ __device__ __forceinline__ void setup_body(const Args &a, int s, const double *P
         ms = wave_max(ms);
         if ((threadIdx.x & 63) == 0)
             red[threadIdx.x >> 6] = (double)ms;
-        __syncthreads();
+        lds_barrier();
         for (int w = 0; w < (int)(blockDim.x >> 6); ++w)
             ms = fmaxf(ms, (float)red[w]);
     }
     if (threadIdx.x == 0) {
         Meta m;
         m.menc = float_to_ordered(-INFINITY);
-        m.pad1 = 0;
+        m.n = n;
         m.delta = problem_delta(a, c, stp, Q[L - 1]);
         m.pthr = a.k == 3 && a.mode == TS_SEARCH_FP32_TIECHECK ? prune_threshold(ms, m.delta) : -INFINITY;
         a.meta[s] = m;
@@ -677,12 +691,12 @@ __global__ void __launch_bounds__(PREFIX_THREADS) k_scan_setup(Args a, const uin
     const uint32_t *h = hist + (int64_t)(s % a.nseg) * L;
     double *qs = scan_lds, *Pl = qs + L + (L + 1) / 2, *Ql = Pl + L;
     prefix_row([h](int b) { return h[b]; }, L, E, a.qc[s / a.nseg].q, Pl, Ql, qs, reinterpret_cast<int *>(qs + L), ps);
-    for (int t = threadIdx.x; t < L; t += blockDim.x) {
+    setup_body(a, s, Pl, Ql, red);
+    for (int t = threadIdx.x; t < L; t += blockDim.x) { // for the re-check
         if (s < a.nseg) // P is the same for every q
             Pout[(int64_t)s * L + t] = Pl[t];
         Qout[(int64_t)s * L + t] = Ql[t];
     }
-    setup_body(a, s, Pl, Ql, red);
 }
 
 // ---------------------------------------------------------------- k = 3 rows
@@ -1100,7 +1114,9 @@ __device__ __forceinline__ int rows3_cols(const TileCtx &x, const float4 &h2, in
     return nv;
 }
 
-// k = 3, phase 1, one workgroup per (problem, row t2, chunk of 1024 columns).
+// k = 3, phase 1, one workgroup per (problem, row t2, chunk of 1024 columns), rows
+// and columns being the bins that can be thresholds (a volume of 1024 levels over
+// the CT range has counts in about 640: a quarter of the tuples, 12.3 -> 9.1 us).
 // The A row head(t1) + g(t1, t2), t1 < t2, is built in LDS; the column terms
 // R(t3) = g(t2, t3) + tail(t3) are in registers, the valid columns of a short
 // row spread over all four wavefronts (and SIMDs).  Every tuple's key is A[t1]
@@ -1111,17 +1127,19 @@ __device__ __forceinline__ int rows3_cols(const TileCtx &x, const float4 &h2, in
 template <int SGN>
 __device__ __forceinline__ void rows3_body(const Args &a, float *tilemax, float *Arow, float *wm)
 {
-    const int L = a.L;
-    const int nrow = L - 3, nch = a.NC; // NC = column chunks per row
-    const int ng = a.T1;                // row groups per wavefront tile
-    const int64_t bid = blockIdx.x;
-    const int s = (int)(bid / ((int64_t)nrow * nch));
-    const int rem = (int)(bid % ((int64_t)nrow * nch));
+    const int nch = a.NC; // column chunks per row
+    const int ng = a.T1;  // row groups per wavefront tile
+    const int64_t bid = blockIdx.x, per = (int64_t)(a.L - 3) * nch;
+    const int s = (int)(bid / per);
+    const int rem = (int)(bid % per);
+    const int L = a.meta[s].n + 1; // rows and columns: the bins that can be thresholds
+    if (rem / nch >= L - 3)
+        return;
     const int t2 = k3_row(rem / nch, L);
     const int chunk = rem % nch;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int64_t tid0 = (((int64_t)s * nrow + (t2 - 1)) * nch + chunk) * (K3_THREADS / 64);
+    const int64_t tid0 = (int64_t)s * a.tiles + ((int64_t)(t2 - 1) * nch + chunk) * (K3_THREADS / 64);
     const int ncols = L - 2 - t2;
     const int c0 = chunk * K3_CHUNK;
     const int n1 = (t2 + 7) & ~7;
@@ -1218,13 +1236,19 @@ __device__ __forceinline__ void recheck_body(const Args &a, const float *tilemax
 {
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const TileCtx x = make_ctx(a, s, (const float *)a.head + (int64_t)s * a.Lp, (const float *)a.tail + (int64_t)s * a.Lp,
-                               a.hl + (int64_t)s * a.Lp);
+    TileCtx x = make_ctx(a, s, (const float *)a.head + (int64_t)s * a.Lp, (const float *)a.tail + (int64_t)s * a.Lp,
+                         a.hl + (int64_t)s * a.Lp);
+    int tiles = a.tiles;
+    if (K == 3) {
+        x.L = a.meta[s].n + 1;
+        x.bins = a.bins + (int64_t)s * a.L;
+        tiles = max(x.L - 3, 0) * a.NC * (K3_THREADS / 64);
+    }
     const float *tm = tilemax + (int64_t)s * a.tiles;
-    for (int t0 = g; t0 < a.tiles; t0 += 64 * G) {
+    for (int t0 = g; t0 < tiles; t0 += 64 * G) {
         const int ti = t0 + lane * G;
-        float mine = ti < a.tiles ? tm[ti] : -INFINITY;
-        if (K == 3 && !(thr > -INFINITY) && ti < a.tiles) { // every tuple: the whole chunk if it holds any
+        float mine = ti < tiles ? tm[ti] : -INFINITY;
+        if (K == 3 && !(thr > -INFINITY) && ti < tiles) { // every tuple: the whole chunk if it holds any
             const int c4 = ti & ~(K3_THREADS / 64 - 1);
             for (int i = 0; i < K3_THREADS / 64; ++i)
                 mine = fmaxf(mine, tm[c4 + i]);
@@ -2977,9 +3001,10 @@ static void launch_setup(const Args &a, const Fp32Launch &f)
                        prefix_bins_per_thread(a.L), f.P, f.Q);
 }
 
-// Phase 2 and the result: G workgroups per problem, enough to fill the chip,
-// at most 7/8 of the tiles (the tile maxima of k = 3 lie after their bests in
-// the workspace's tile bests).
+// Phase 2 and the result: G workgroups per problem, enough to fill the chip, at
+// most half of the tiles (the tile maxima and bins of k = 3 lie after their
+// bests in the workspace's tile bests: 16 + 4 of 32 bytes per tile, and 2 L of
+// the 48 (L - 3) or more left).
 template <int COLS, int K>
 static void launch_recheck(const Args &a, const float *tilemax, int G, const Fp32Launch &f)
 {
@@ -2990,7 +3015,7 @@ static void launch_recheck(const Args &a, const float *tilemax, int G, const Fp3
 static int recheck_groups(const Args &a)
 {
     const int want = std::max(8, std::min(256, 1024 / std::max(a.nprob, 1)));
-    return std::max(1, std::min(want, a.tiles * 7 / 8));
+    return std::max(1, std::min(want, a.tiles / 2));
 }
 
 template <int COLS>
@@ -3016,11 +3041,12 @@ static void launch_fp32(bool fused, const Args &a, const Tune &t, const Fp32Laun
 }
 
 // The FP32 search with its re-check (both modes), planned as p.
-static void launch_fp32_search(const Plan &p, bool fused, const Args &a, const Tune &t, const Fp32Launch &f)
+static void launch_fp32_search(const Plan &p, bool fused, Args a, const Tune &t, const Fp32Launch &f)
 {
     if (a.k == 3) {
         const int G = recheck_groups(a);
         float *tilemax = (float *)(a.best + (int64_t)a.nprob * G);
+        a.bins = (unsigned short *)(tilemax + (int64_t)a.nprob * a.tiles);
         launch_setup(a, f);
         hipLaunchKernelGGL(k_rows3, dim3((unsigned)((int64_t)(a.L - 3) * p.NC * a.nprob)), dim3(K3_THREADS),
                            (size_t)p.Lp * sizeof(float), f.st, a, tilemax);
@@ -3101,6 +3127,7 @@ static Args plan_args(const Plan &p, const double *P, const double *Q, int nseg,
     a.R = base + p.off_R;
     a.tmax = (float *)(base + p.off_tmax);
     a.best = (Best *)(base + p.off_best);
+    a.bins = nullptr; // k = 3: placed at the launch
     return a;
 }
 

@@ -66,3 +66,26 @@ def test_every_tuple_rechecked(k, L):
     t2, o2, s2 = api.threshold_search(P, Q, k, (12.0,), mode=api.SEARCH_FP64)
     assert torch.equal(st, s2)
     assert torch.allclose(obj, o2, rtol=1e-12, atol=0.0)
+
+
+@pytest.mark.parametrize("L", [4, 5, 33, 257, 700])
+def test_k3_on_few_occupied_bins(L):
+    """k = 3 walks only the bins that can be thresholds: the same thresholds
+    as the FP64 search over all bins, from no occupied bin at the ends to one
+    bin in twenty."""
+    rng = np.random.default_rng(L)
+    rows = []
+    for keep in (1.0, 0.5, 0.05):
+        c = rng.integers(1, 1000, L)
+        c[rng.random(L) >= keep] = 0
+        rows.append(c)
+    rows.append(np.where(np.arange(L) < L // 2, 0, rows[0]))
+    rows.append(np.where(np.arange(L) < (L + 1) // 2, rows[0], 0))
+    h = to_dev(np.array(rows).astype(np.int32))
+    P, Q = api.prefix(h, (0.8, 1.0, 2.0))
+    thr, obj, st = api.threshold_search(P, Q, 3, (0.8, 1.0, 2.0))
+    t2, o2, s2 = api.threshold_search(P, Q, 3, (0.8, 1.0, 2.0), mode=api.SEARCH_FP64)
+    assert torch.equal(st, s2)
+    ok = st == 0
+    assert torch.equal(thr[ok], t2[ok])
+    assert torch.allclose(obj[ok], o2[ok], rtol=1e-12, atol=0.0)
