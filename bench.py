@@ -131,7 +131,8 @@ POOL = 4
 KERNEL_FILES = (("ts::k_label", "k_label.hip"), ("ts::k_histogram", "k_histogram.hip"),
                 ("ts::k_fill_u32", "k_histogram.hip"), ("ts::k_prefix", "k_prefix.hip"),
                 ("ts::k_fused", "k_search.hip"), ("ts::k_segment", "k_search.hip"), ("ts::k_setup", "k_search.hip"), ("ts::k_rows3", "k_search.hip"),
-                ("ts::k_tiles32", "k_search.hip"), ("ts::k_final", "k_search.hip"), ("ts::k_hist2d", "k_2d.hip"),
+                ("ts::k_tiles32", "k_search.hip"), ("ts::k_scan_", "k_search.hip"), ("ts::k_recheck", "k_search.hip"),
+                ("ts::k_final", "k_search.hip"), ("ts::k_hist2d", "k_2d.hip"),
                 ("ts::k_search2d", "k_2d.hip"), ("ts::k_morph", "k_morph.hip"))
 
 
