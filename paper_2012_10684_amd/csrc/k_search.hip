@@ -79,7 +79,7 @@ struct Best {
     double rank; // value the arg max is taken over
     double lam;  // FP64 signed Lambda (natural log) of the tuple
     long long code;
-    long long pad;
+    long long done; // in a problem's first: workgroups of k_recheck that have stored theirs
 };
 
 __device__ __forceinline__ bool better(double r1, long long c1, double r2, long long c2)
@@ -340,6 +340,7 @@ struct Args {
     float *tmax;
     Best *best;
     unsigned short *bins; // k = 3: [nprob][L], the bins that can be thresholds (FP32 search)
+    int G;                // workgroups of k_recheck per problem (0: no k_recheck)
 };
 
 // ---------------------------------------------------------------- setup
@@ -652,6 +653,8 @@ __device__ __forceinline__ void setup_body(const Args &a, int s, const double *P
         m.delta = problem_delta(a, c, stp, Q[L - 1]);
         m.pthr = a.k == 3 && a.mode == TS_SEARCH_FP32_TIECHECK ? prune_threshold(ms, m.delta) : -INFINITY;
         a.meta[s] = m;
+        if (a.G)
+            a.best[(int64_t)s * a.G].done = 0;
     }
     if (a.mode == TS_SEARCH_FP64) {
         double *hd = (double *)a.head + (int64_t)s * Lp;
@@ -1303,36 +1306,6 @@ __device__ __forceinline__ void recheck_body(const Args &a, const float *tilemax
     }
 }
 
-template <int COLS, int K>
-__global__ void __launch_bounds__(256) k_recheck(Args a, const float *tilemax, int G)
-{
-    __shared__ Cand wb[4];
-    const int s = blockIdx.x / G, g = blockIdx.x % G;
-    const Meta meta = a.meta[s];
-    const float M = ordered_to_float(meta.menc);
-    Cand best = {-INFINITY, -INFINITY, 0x7fffffffffffffffLL};
-    if (M > -INFINITY) {
-        const float thr = phase2_threshold(M, meta.delta);
-        const double sgn = a.qc[s / a.nseg].sgn;
-        if (sgn > 0)
-            recheck_body<1, COLS, K>(a, tilemax, s, g, G, thr, best);
-        else if (sgn < 0)
-            recheck_body<-1, COLS, K>(a, tilemax, s, g, G, thr, best);
-        else
-            recheck_body<0, COLS, K>(a, tilemax, s, g, G, thr, best);
-    }
-    wave_best(best.r, best.l, best.c);
-    if ((threadIdx.x & 63) == 0)
-        wb[threadIdx.x >> 6] = best;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 1; i < 4; ++i)
-            if (better(wb[i].r, wb[i].c, best.r, best.c))
-                best = wb[i];
-        a.best[(int64_t)s * G + g] = Best{best.r, best.l, best.c, 0};
-    }
-}
-
 // Write problem s's result from its best candidate (plast = P(L-1) of the
 // problem: 1, or 0 when it holds no voxel).
 __device__ __forceinline__ void write_result(const Cand &b, const Args &a, int s, double plast, int32_t *thr,
@@ -1356,6 +1329,71 @@ __device__ __forceinline__ void write_result(const Cand &b, const Args &a, int s
         obj[s] = (sgn == 0.0 || a.mode == TS_SEARCH_SUMPROD) ? b.l : expm1(sgn * b.l) / (1.0 - q);
         status[s] = TS_PROBLEM_OK;
     }
+}
+
+// Phase 2 and the result.  A workgroup's best goes out as device-coherent
+// stores; once they are acknowledged it counts itself in (the set-up cleared
+// the count), and the last one of the problem picks the first best of all, with
+// device-coherent loads, and writes the result: no workgroup waits for another.
+// A chain of round trips: 11.5 us at 512 levels, k = 3, where the re-check and a
+// launch of k_final took 9.3 + 3.0 and the gap between them (the whole call of
+// 60 x 256 x 256 voxels: 44.5 -> 43.8 us).
+template <int COLS, int K>
+__global__ void __launch_bounds__(256) k_recheck(Args a, const float *tilemax, int32_t *__restrict__ thr_out,
+                                                 double *__restrict__ obj, int32_t *__restrict__ status)
+{
+    __shared__ Cand wb[4];
+    __shared__ int last;
+    const int G = a.G, s = blockIdx.x / G, g = blockIdx.x % G;
+    const Meta meta = a.meta[s];
+    const float M = ordered_to_float(meta.menc);
+    Cand best = {-INFINITY, -INFINITY, 0x7fffffffffffffffLL};
+    if (M > -INFINITY) {
+        const float thr = phase2_threshold(M, meta.delta);
+        const double sgn = a.qc[s / a.nseg].sgn;
+        if (sgn > 0)
+            recheck_body<1, COLS, K>(a, tilemax, s, g, G, thr, best);
+        else if (sgn < 0)
+            recheck_body<-1, COLS, K>(a, tilemax, s, g, G, thr, best);
+        else
+            recheck_body<0, COLS, K>(a, tilemax, s, g, G, thr, best);
+    }
+    auto block_best = [&]() { // of the workgroup, in thread 0
+        wave_best(best.r, best.l, best.c);
+        if ((threadIdx.x & 63) == 0)
+            wb[threadIdx.x >> 6] = best;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int i = 1; i < 4; ++i)
+                if (better(wb[i].r, wb[i].c, best.r, best.c))
+                    best = wb[i];
+        }
+    };
+    block_best();
+    Best *b = a.best + (int64_t)s * G;
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(&b[g].rank, best.r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&b[g].lam, best.l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&b[g].code, best.c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __atomic_signal_fence(__ATOMIC_SEQ_CST); // the compiler keeps the order too
+        __builtin_amdgcn_s_waitcnt(0);
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        last = __hip_atomic_fetch_add(&b->done, 1LL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == G - 1;
+    }
+    __syncthreads();
+    if (!last)
+        return;
+    best = {-INFINITY, -INFINITY, 0x7fffffffffffffffLL};
+    for (int i = threadIdx.x; i < G; i += blockDim.x) {
+        const Cand x = {__hip_atomic_load(&b[i].rank, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                        __hip_atomic_load(&b[i].lam, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                        __hip_atomic_load(&b[i].code, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)};
+        if (better(x.r, x.c, best.r, best.c))
+            best = x;
+    }
+    block_best();
+    if (threadIdx.x == 0)
+        write_result(best, a, s, a.P[(int64_t)(s % a.nseg) * a.L + a.L - 1], thr_out, obj, status);
 }
 
 // Single-launch path: one workgroup per problem does the setup, phase 1,
@@ -3001,25 +3039,27 @@ static void launch_setup(const Args &a, const Fp32Launch &f)
                        prefix_bins_per_thread(a.L), f.P, f.Q);
 }
 
-// Phase 2 and the result: G workgroups per problem, enough to fill the chip, at
-// most half of the tiles (the tile maxima and bins of k = 3 lie after their
-// bests in the workspace's tile bests: 16 + 4 of 32 bytes per tile, and 2 L of
-// the 48 (L - 3) or more left).
+// Phase 2 and the result: G workgroups per problem, at most half of the tiles
+// (the tile maxima and bins of k = 3 lie after their bests in the workspace's
+// tile bests: 16 + 4 of 32 bytes per tile, and 2 L of the 48 (L - 3) or more
+// left).
 template <int COLS, int K>
-static void launch_recheck(const Args &a, const float *tilemax, int G, const Fp32Launch &f)
+static void launch_recheck(const Args &a, const float *tilemax, const Fp32Launch &f)
 {
-    hipLaunchKernelGGL((k_recheck<COLS, K>), dim3((unsigned)((int64_t)a.nprob * G)), dim3(256), 0, f.st, a, tilemax, G);
-    hipLaunchKernelGGL(k_final, dim3((unsigned)a.nprob), dim3(256), 0, f.st, a, a.best, G, f.thr, f.obj, f.status, 0);
+    hipLaunchKernelGGL((k_recheck<COLS, K>), dim3((unsigned)((int64_t)a.nprob * a.G)), dim3(256), 0, f.st, a, tilemax,
+                       f.thr, f.obj, f.status);
 }
 
+// Few problems: 96 each, since with 256 they wait for each other's arrivals on
+// the count (43.8 against 44.3 us for the call above); many: a share of the chip.
 static int recheck_groups(const Args &a)
 {
-    const int want = std::max(8, std::min(256, 1024 / std::max(a.nprob, 1)));
+    const int want = std::max(8, std::min(96, 1024 / std::max(a.nprob, 1)));
     return std::max(1, std::min(want, a.tiles / 2));
 }
 
 template <int COLS>
-static void launch_fp32(bool fused, const Args &a, const Tune &t, const Fp32Launch &f)
+static void launch_fp32(bool fused, Args a, const Tune &t, const Fp32Launch &f)
 {
     if (fused) {
         if (a.k == 1)
@@ -3030,13 +3070,14 @@ static void launch_fp32(bool fused, const Args &a, const Tune &t, const Fp32Laun
     }
     const int64_t waves = (int64_t)a.nprob * a.tiles;
     const dim3 g((unsigned)((waves + 3) / 4));
+    a.G = recheck_groups(a);
     launch_setup(a, f);
     if (a.k == 1) {
         hipLaunchKernelGGL((k_tiles32<COLS, 1>), g, dim3(256), 0, f.st, a);
-        launch_recheck<COLS, 1>(a, a.tmax, recheck_groups(a), f);
+        launch_recheck<COLS, 1>(a, a.tmax, f);
     } else { // k = 3 uses k_rows3
         hipLaunchKernelGGL((k_tiles32<COLS, 2>), g, dim3(256), 0, f.st, a);
-        launch_recheck<COLS, 2>(a, a.tmax, recheck_groups(a), f);
+        launch_recheck<COLS, 2>(a, a.tmax, f);
     }
 }
 
@@ -3044,13 +3085,13 @@ static void launch_fp32(bool fused, const Args &a, const Tune &t, const Fp32Laun
 static void launch_fp32_search(const Plan &p, bool fused, Args a, const Tune &t, const Fp32Launch &f)
 {
     if (a.k == 3) {
-        const int G = recheck_groups(a);
-        float *tilemax = (float *)(a.best + (int64_t)a.nprob * G);
+        a.G = recheck_groups(a);
+        float *tilemax = (float *)(a.best + (int64_t)a.nprob * a.G);
         a.bins = (unsigned short *)(tilemax + (int64_t)a.nprob * a.tiles);
         launch_setup(a, f);
         hipLaunchKernelGGL(k_rows3, dim3((unsigned)((int64_t)(a.L - 3) * p.NC * a.nprob)), dim3(K3_THREADS),
                            (size_t)p.Lp * sizeof(float), f.st, a, tilemax);
-        launch_recheck<K3_COLS, 3>(a, tilemax, G, f);
+        launch_recheck<K3_COLS, 3>(a, tilemax, f);
     } else if (t.search_cols == 1) {
         launch_fp32<1>(fused, a, t, f);
     } else if (t.search_cols == 2) {
@@ -3128,6 +3169,7 @@ static Args plan_args(const Plan &p, const double *P, const double *Q, int nseg,
     a.tmax = (float *)(base + p.off_tmax);
     a.best = (Best *)(base + p.off_best);
     a.bins = nullptr; // k = 3: placed at the launch
+    a.G = 0;          // set at the launch
     return a;
 }
 
