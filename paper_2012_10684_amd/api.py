@@ -532,7 +532,8 @@ def _batch_segment(volumes, bin, k, q, per, mode, method, open_radius, tune, str
     for v in vols:
         if (per == "volume" or v.shape[0]) and (v.dtype != torch.int16 or not v.is_cuda):
             raise ValueError("segments must be contiguous int16 CUDA tensors")
-    dev = vols[0].device if vols else torch.device("cuda")
+    # the first problem's device: volumes without slices hold none and may be anywhere
+    dev = next((v.device for v in vols if per == "volume" or v.shape[0]), torch.device("cuda"))
     residues = None
     if open_radius is not None:
         if per != "slice":
