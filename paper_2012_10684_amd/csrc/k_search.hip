@@ -221,6 +221,15 @@ __device__ __forceinline__ double cls64(double dP, double dQ, double q, double s
     return fmin(fmax(h, 0.0), hmax);
 }
 
+// Lane l's value (l uniform over the wavefront).
+__device__ __forceinline__ double lane_f64(double v, int l)
+{
+    const long long b = __double_as_longlong(v);
+    const unsigned int lo = (unsigned int)__builtin_amdgcn_readlane((int)(b & 0xffffffffLL), l);
+    const unsigned int hi = (unsigned int)__builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // FP64 signed Lambda of the tuple t[0..k-1] directly from the prefix sums.
 // The classes go through a rolled loop with one call site of log: the tie
 // check runs for a handful of tuples per problem, so small code (few
@@ -1010,6 +1019,109 @@ __device__ __forceinline__ void tile_k2(const TileCtx &x, int b, int c, float th
     rows_k2_diag<SGN, COLS, PHASE>(x, max(r0, cbase), r1, cbase, hc, tc, t2v, thr, acc, best, pw);
 }
 
+// Phase 2 where every tuple is re-checked (thr = -inf: no finite error bound),
+// in FP64 without the keys.  The class terms are added in lambda64_k's order,
+// hence the same bits, but each is formed where it is shared: k = 2, the heads
+// one row per lane and the tails once per column, so a tuple costs its middle
+// class (two logarithms, six in lambda64_k); k = 3, also the class (t1, t2]
+// with the heads and (t2, t3] with the tails, so a tuple costs two additions
+// (eight logarithms).  Per column the first row reaching the best is kept, then
+// the first tuple of them.  Bounded by FP64 issue.  One problem with counts in
+// every bin, q = 2, on at most 96 workgroups: k = 3, 512 levels 135 us and 1024
+// levels 498, k = 2, 1024 levels 48 (5003, 27507 and 118 by lambda64_k; 1943, 6612
+// and 93 by lambda64_k over the whole chip).
+template <int COLS>
+__device__ __forceinline__ void tile_k2_all(const TileCtx &x, int b, int c, Cand &best)
+{
+    const int lane = threadIdx.x & 63, L = x.L, cbase = b * x.CW;
+    const int r0 = c * x.T1, r1 = min(r0 + x.T1, min(L - 2, cbase + x.CW - 1));
+    if (r0 >= r1)
+        return;
+    const double PL = x.P[x.Lb - 1], QL = x.Q[x.Lb - 1];
+    double pc[COLS], qc[COLS], tail[COLS], vb[COLS];
+    int vt[COLS];
+#pragma unroll
+    for (int v = 0; v < COLS; ++v) {
+        const int t2 = x.bin(min(cbase + v * 64 + lane, L - 2));
+        pc[v] = x.P[t2];
+        qc[v] = x.Q[t2];
+        tail[v] = cls64(PL - pc[v], QL - qc[v], x.q, x.sgn, x.hmax);
+        vb[v] = -INFINITY;
+        vt[v] = 0;
+    }
+    for (int rb = r0; rb < r1; rb += 64) {
+        const int tl = x.bin(min(rb + lane, r1 - 1));
+        const double pl = x.P[tl], ql = x.Q[tl];
+        const double hl = 0.0 + cls64(pl, ql, x.q, x.sgn, x.hmax);
+        const int n = min(64, r1 - rb);
+#pragma unroll 1
+        for (int i = 0; i < n; ++i) {
+            const double p = lane_f64(pl, i), q = lane_f64(ql, i), h = lane_f64(hl, i);
+#pragma unroll
+            for (int v = 0; v < COLS; ++v) {
+                const int t2 = cbase + v * 64 + lane;
+                const double key = (h + cls64(pc[v] - p, qc[v] - q, x.q, x.sgn, x.hmax)) + tail[v];
+                if (rb + i < t2 && t2 <= L - 2 && key > vb[v]) {
+                    vb[v] = key;
+                    vt[v] = rb + i;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < COLS; ++v) {
+        const int t[2] = {x.bin(vt[v]), x.bin(min(cbase + v * 64 + lane, L - 2))};
+        const long long code = make_code(2, t);
+        if (vb[v] > -INFINITY && better(vb[v], code, best.r, best.c))
+            best = Cand{vb[v], vb[v], code};
+    }
+}
+
+// Row t2 of k = 3: every t1 < t2 with the columns t3 = t2 + 1 + c, c = cb + v *
+// cs + lane for v < NV.
+template <int NV>
+__device__ __forceinline__ void row_k3_all(const TileCtx &x, int t2, int cb, int cs, Cand &best)
+{
+    const int lane = threadIdx.x & 63, L = x.L, b2 = x.bin(t2);
+    const double PL = x.P[x.Lb - 1], QL = x.Q[x.Lb - 1], p2 = x.P[b2], q2 = x.Q[b2];
+    double mid[NV], tail[NV], vb[NV];
+    int vt[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int t3 = t2 + 1 + cb + v * cs + lane, b3 = x.bin(min(t3, L - 2));
+        const double p3 = x.P[b3], q3 = x.Q[b3];
+        mid[v] = t3 <= L - 2 ? cls64(p3 - p2, q3 - q2, x.q, x.sgn, x.hmax) : -INFINITY;
+        tail[v] = cls64(PL - p3, QL - q3, x.q, x.sgn, x.hmax);
+        vb[v] = -INFINITY;
+        vt[v] = 0;
+    }
+    for (int rb = 0; rb < t2; rb += 64) {
+        const int tl = x.bin(min(rb + lane, t2 - 1));
+        const double pl = x.P[tl], ql = x.Q[tl];
+        const double al = (0.0 + cls64(pl, ql, x.q, x.sgn, x.hmax)) + cls64(p2 - pl, q2 - ql, x.q, x.sgn, x.hmax);
+        const int n = min(64, t2 - rb);
+#pragma unroll 2
+        for (int i = 0; i < n; ++i) {
+            const double a = lane_f64(al, i);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const double key = (a + mid[v]) + tail[v];
+                if (key > vb[v]) {
+                    vb[v] = key;
+                    vt[v] = rb + i;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int t[3] = {x.bin(vt[v]), b2, x.bin(min(t2 + 1 + cb + v * cs + lane, L - 2))};
+        const long long code = make_code(3, t);
+        if (vb[v] > -INFINITY && better(vb[v], code, best.r, best.c))
+            best = Cand{vb[v], vb[v], code};
+    }
+}
+
 template <int SGN, int COLS, int PHASE, int K>
 __device__ __forceinline__ void tile_body(const TileCtx &x, int b, int c, float thr, float &acc, Cand &best)
 {
@@ -1225,6 +1337,46 @@ __global__ void __launch_bounds__(K3_THREADS) k_rows3(Args a, float *tilemax)
         rows3_body<0>(a, tilemax, Arow, wm);
 }
 
+// What phase 2 reads for problem s, and its tiles.
+template <int K>
+__device__ __forceinline__ TileCtx recheck_ctx(const Args &a, int s, int &tiles)
+{
+    TileCtx x = make_ctx(a, s, (const float *)a.head + (int64_t)s * a.Lp, (const float *)a.tail + (int64_t)s * a.Lp,
+                         a.hl + (int64_t)s * a.Lp);
+    tiles = a.tiles;
+    if (K == 3) {
+        x.L = a.meta[s].n + 1;
+        x.bins = a.bins + (int64_t)s * a.L;
+        tiles = max(x.L - 3, 0) * a.NC * (K3_THREADS / 64);
+    }
+    return x;
+}
+
+// Phase 2 where every tuple is re-checked, k = 2 or 3: tile t by wavefront t
+// mod 4 of workgroup t / 4 mod G.
+template <int COLS, int K>
+__device__ __forceinline__ void recheck_all(const Args &a, int s, int g, int G, Cand &best)
+{
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    int tiles;
+    const TileCtx x = recheck_ctx<K>(a, s, tiles);
+    for (int tile = 4 * g + w; tile < tiles; tile += 4 * G) {
+        if constexpr (K == 2) {
+            tile_k2_all<COLS>(x, tile % a.NB, tile / a.NB, best);
+        } else {
+            const int rc = tile / (K3_THREADS / 64), t2 = 1 + rc / a.NC;
+            const int cb = (rc % a.NC) * K3_CHUNK + (tile % (K3_THREADS / 64)) * 64;
+            const int left = x.L - 2 - t2 - cb; // columns from cb on
+            if (left > 2 * K3_THREADS)
+                row_k3_all<4>(x, t2, cb, K3_THREADS, best);
+            else if (left > K3_THREADS)
+                row_k3_all<2>(x, t2, cb, K3_THREADS, best);
+            else if (left > 0)
+                row_k3_all<1>(x, t2, cb, K3_THREADS, best);
+        }
+    }
+}
+
 // Phase 2 of the multi-launch paths: G workgroups per problem, tile t (its max
 // in tilemax) belonging to workgroup t mod G (tiles that qualify are
 // neighbours).  The four wavefronts share the rows of every tile whose max
@@ -1239,23 +1391,12 @@ __device__ __forceinline__ void recheck_body(const Args &a, const float *tilemax
 {
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    TileCtx x = make_ctx(a, s, (const float *)a.head + (int64_t)s * a.Lp, (const float *)a.tail + (int64_t)s * a.Lp,
-                         a.hl + (int64_t)s * a.Lp);
-    int tiles = a.tiles;
-    if (K == 3) {
-        x.L = a.meta[s].n + 1;
-        x.bins = a.bins + (int64_t)s * a.L;
-        tiles = max(x.L - 3, 0) * a.NC * (K3_THREADS / 64);
-    }
+    int tiles;
+    const TileCtx x = recheck_ctx<K>(a, s, tiles);
     const float *tm = tilemax + (int64_t)s * a.tiles;
     for (int t0 = g; t0 < tiles; t0 += 64 * G) {
         const int ti = t0 + lane * G;
-        float mine = ti < tiles ? tm[ti] : -INFINITY;
-        if (K == 3 && !(thr > -INFINITY) && ti < tiles) { // every tuple: the whole chunk if it holds any
-            const int c4 = ti & ~(K3_THREADS / 64 - 1);
-            for (int i = 0; i < K3_THREADS / 64; ++i)
-                mine = fmaxf(mine, tm[c4 + i]);
-        }
+        const float mine = ti < tiles ? tm[ti] : -INFINITY;
         unsigned long long m = __ballot(mine > -INFINITY && mine >= thr);
         while (m) {
             const int tile = t0 + __builtin_ctzll(m) * G;
@@ -1351,7 +1492,9 @@ __global__ void __launch_bounds__(256) k_recheck(Args a, const float *tilemax, i
     if (M > -INFINITY) {
         const float thr = phase2_threshold(M, meta.delta);
         const double sgn = a.qc[s / a.nseg].sgn;
-        if (sgn > 0)
+        if (K > 1 && !(thr > -INFINITY))
+            recheck_all<COLS, K>(a, s, g, G, best);
+        else if (sgn > 0)
             recheck_body<1, COLS, K>(a, tilemax, s, g, G, thr, best);
         else if (sgn < 0)
             recheck_body<-1, COLS, K>(a, tilemax, s, g, G, thr, best);
