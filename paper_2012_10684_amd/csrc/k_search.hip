@@ -221,6 +221,16 @@ __device__ __forceinline__ double cls64(double dP, double dQ, double q, double s
     return fmin(fmax(h, 0.0), hmax);
 }
 
+// The same term with the test last, so that several terms' logarithms run
+// interleaved.  SHANNON: q = 1.
+template <bool SHANNON>
+__device__ __forceinline__ double cls64_sel(double dP, double dQ, double q, double sgn, double hmax)
+{
+    const double lp = log(dP);
+    const double h = SHANNON ? lp - dQ / dP : sgn * (log(dQ) - q * lp);
+    return dP > 0.0 ? fmin(fmax(h, 0.0), hmax) : -INFINITY;
+}
+
 // Lane l's value (l uniform over the wavefront).
 __device__ __forceinline__ double lane_f64(double v, int l)
 {
@@ -1028,9 +1038,10 @@ __device__ __forceinline__ void tile_k2(const TileCtx &x, int b, int c, float th
 // (eight logarithms).  Per column the first row reaching the best is kept, then
 // the first tuple of them.  Bounded by FP64 issue.  One problem with counts in
 // every bin, q = 2, on at most 96 workgroups: k = 3, 512 levels 135 us and 1024
-// levels 498, k = 2, 1024 levels 48 (5003, 27507 and 118 by lambda64_k; 1943, 6612
-// and 93 by lambda64_k over the whole chip).
-template <int COLS>
+// levels 498, k = 2, 1024 levels 47 (5003, 27507 and 118 by lambda64_k; 1943, 6612
+// and 93 by lambda64_k over the whole chip); k = 2 on one workgroup, 256 / 512 /
+// 1024 levels 79 / 266 / 980 (258 / 907 / 3386 by lambda64_k).
+template <int COLS, bool SHANNON>
 __device__ __forceinline__ void tile_k2_all(const TileCtx &x, int b, int c, Cand &best)
 {
     const int lane = threadIdx.x & 63, L = x.L, cbase = b * x.CW;
@@ -1045,14 +1056,14 @@ __device__ __forceinline__ void tile_k2_all(const TileCtx &x, int b, int c, Cand
         const int t2 = x.bin(min(cbase + v * 64 + lane, L - 2));
         pc[v] = x.P[t2];
         qc[v] = x.Q[t2];
-        tail[v] = cls64(PL - pc[v], QL - qc[v], x.q, x.sgn, x.hmax);
+        tail[v] = cls64_sel<SHANNON>(PL - pc[v], QL - qc[v], x.q, x.sgn, x.hmax);
         vb[v] = -INFINITY;
         vt[v] = 0;
     }
     for (int rb = r0; rb < r1; rb += 64) {
         const int tl = x.bin(min(rb + lane, r1 - 1));
         const double pl = x.P[tl], ql = x.Q[tl];
-        const double hl = 0.0 + cls64(pl, ql, x.q, x.sgn, x.hmax);
+        const double hl = 0.0 + cls64_sel<SHANNON>(pl, ql, x.q, x.sgn, x.hmax);
         const int n = min(64, r1 - rb);
 #pragma unroll 1
         for (int i = 0; i < n; ++i) {
@@ -1060,7 +1071,7 @@ __device__ __forceinline__ void tile_k2_all(const TileCtx &x, int b, int c, Cand
 #pragma unroll
             for (int v = 0; v < COLS; ++v) {
                 const int t2 = cbase + v * 64 + lane;
-                const double key = (h + cls64(pc[v] - p, qc[v] - q, x.q, x.sgn, x.hmax)) + tail[v];
+                const double key = (h + cls64_sel<SHANNON>(pc[v] - p, qc[v] - q, x.q, x.sgn, x.hmax)) + tail[v];
                 if (rb + i < t2 && t2 <= L - 2 && key > vb[v]) {
                     vb[v] = key;
                     vt[v] = rb + i;
@@ -1353,7 +1364,9 @@ __device__ __forceinline__ TileCtx recheck_ctx(const Args &a, int s, int &tiles)
 }
 
 // Phase 2 where every tuple is re-checked, k = 2 or 3: tile t by wavefront t
-// mod 4 of workgroup t / 4 mod G.
+// mod 4 of workgroup t / 4 mod G.  k = 2 counts the tiles along the rows: a
+// column block's rows end at the diagonal, so a wavefront that had one block's
+// tiles only would have up to twice its share.
 template <int COLS, int K>
 __device__ __forceinline__ void recheck_all(const Args &a, int s, int g, int G, Cand &best)
 {
@@ -1362,7 +1375,10 @@ __device__ __forceinline__ void recheck_all(const Args &a, int s, int g, int G, 
     const TileCtx x = recheck_ctx<K>(a, s, tiles);
     for (int tile = 4 * g + w; tile < tiles; tile += 4 * G) {
         if constexpr (K == 2) {
-            tile_k2_all<COLS>(x, tile % a.NB, tile / a.NB, best);
+            if (x.sgn == 0.0)
+                tile_k2_all<COLS, true>(x, tile / a.NC, tile % a.NC, best);
+            else
+                tile_k2_all<COLS, false>(x, tile / a.NC, tile % a.NC, best);
         } else {
             const int rc = tile / (K3_THREADS / 64), t2 = 1 + rc / a.NC;
             const int cb = (rc % a.NC) * K3_CHUNK + (tile % (K3_THREADS / 64)) * 64;
@@ -1642,9 +1658,12 @@ __device__ __forceinline__ void prune_rows(const TileCtx &x, int NB, float pthr,
 
 // The whole search of problem s by the calling workgroup, from its prefix
 // sums P, Q [L] (global memory, or LDS); stage: copy them to LDS for phase 2
-// (k = 2 from global memory).  Writes the result and returns its tuple code
-// (-1: no valid tuple) in every thread.
-template <int SGN, int COLS, int K>
+// (k = 2 from global memory); ALL: k = 2 re-checks every tuple by tile_k2_all
+// (not in k_segment, whose labels then took 3 % longer: the kernel is at its
+// limit of scalar registers, and a problem of a large batch is too small for an
+// infinite bound).  Writes the result and returns its tuple code (-1: no valid
+// tuple) in every thread.
+template <int SGN, int COLS, int K, bool ALL>
 __device__ __forceinline__ long long fused_body(const Args &a, FusedLds &sh, int s, const double *P, const double *Q,
                                                 bool stage, int32_t *__restrict__ thr_out, double *__restrict__ obj,
                                                 int32_t *__restrict__ status)
@@ -1731,22 +1750,27 @@ __device__ __forceinline__ long long fused_body(const Args &a, FusedLds &sh, int
         M = fmaxf(M, wmax[i]);
     if (M > -INFINITY) {
         const float thr = phase2_threshold(M, sh.sdelta);
-        // qualifying tiles found 64 at a time with a ballot (few qualify,
-        // typically one); k = 1: the i-th goes to wavefront i mod nw; k = 2:
-        // every wavefront takes a share of the rows of each of them
-        int nth = 0;
-        for (int base = 0; base < tiles; base += 64) {
-            const int t = base + lane;
-            unsigned long long m = __ballot(t < tiles && tmax[t] >= thr);
-            while (m) {
-                const int tile = base + __builtin_ctzll(m);
-                m &= m - 1;
-                float acc = -INFINITY;
-                if (K == 1) {
-                    if (nth++ % nw == w)
-                        tile_body<SGN, COLS, 2, K>(x, tile % NB, tile / NB, thr, acc, best);
-                } else {
-                    tile_k2<SGN, COLS, 2>(x, tile % NB, tile / NB, thr, acc, best, w, nw);
+        if (ALL && K == 2 && !(thr > -INFINITY)) { // every tuple: a tile per wavefront
+            for (int t = w; t < tiles; t += nw)
+                tile_k2_all<COLS, SGN == 0>(x, t / NC, t % NC, best);
+        } else {
+            // qualifying tiles found 64 at a time with a ballot (few qualify,
+            // typically one); k = 1: the i-th goes to wavefront i mod nw; k = 2:
+            // every wavefront takes a share of the rows of each of them
+            int nth = 0;
+            for (int base = 0; base < tiles; base += 64) {
+                const int t = base + lane;
+                unsigned long long m = __ballot(t < tiles && tmax[t] >= thr);
+                while (m) {
+                    const int tile = base + __builtin_ctzll(m);
+                    m &= m - 1;
+                    float acc = -INFINITY;
+                    if (K == 1) {
+                        if (nth++ % nw == w)
+                            tile_body<SGN, COLS, 2, K>(x, tile % NB, tile / NB, thr, acc, best);
+                    } else {
+                        tile_k2<SGN, COLS, 2>(x, tile % NB, tile / NB, thr, acc, best, w, nw);
+                    }
                 }
             }
         }
@@ -1789,11 +1813,11 @@ __global__ void __launch_bounds__(FUSED_THREADS) k_fused(Args a, int32_t *__rest
     const double *P = a.P + (int64_t)(s % a.nseg) * a.L;
     const double *Q = a.Q + (int64_t)s * a.L;
     if (sgn > 0)
-        fused_body<1, COLS, K>(a, sh, s, P, Q, true, thr_out, obj, status);
+        fused_body<1, COLS, K, true>(a, sh, s, P, Q, true, thr_out, obj, status);
     else if (sgn < 0)
-        fused_body<-1, COLS, K>(a, sh, s, P, Q, true, thr_out, obj, status);
+        fused_body<-1, COLS, K, true>(a, sh, s, P, Q, true, thr_out, obj, status);
     else
-        fused_body<0, COLS, K>(a, sh, s, P, Q, true, thr_out, obj, status);
+        fused_body<0, COLS, K, true>(a, sh, s, P, Q, true, thr_out, obj, status);
 }
 
 // The prefix pass and the one-workgroup search in one launch (ts_segment): the
@@ -1824,11 +1848,11 @@ __global__ void __launch_bounds__(FUSED_THREADS) k_scan_fused(Args a, const uint
     prefix_row([h](int b) { return h[b]; }, L, E, a.qc[s / a.nseg].q, Pl, Ql, qs, reinterpret_cast<int *>(qs + L), ps);
     const double sgn = a.qc[s / a.nseg].sgn;
     if (sgn > 0)
-        fused_body<1, COLS, K>(a, sh, s, Pl, Ql, false, thr_out, obj, status);
+        fused_body<1, COLS, K, true>(a, sh, s, Pl, Ql, false, thr_out, obj, status);
     else if (sgn < 0)
-        fused_body<-1, COLS, K>(a, sh, s, Pl, Ql, false, thr_out, obj, status);
+        fused_body<-1, COLS, K, true>(a, sh, s, Pl, Ql, false, thr_out, obj, status);
     else
-        fused_body<0, COLS, K>(a, sh, s, Pl, Ql, false, thr_out, obj, status);
+        fused_body<0, COLS, K, true>(a, sh, s, Pl, Ql, false, thr_out, obj, status);
 }
 
 // LDS area A of k_scan_fused, and all of it.
@@ -2461,11 +2485,11 @@ __global__ void __launch_bounds__(1024) k_segment(SegArgs g, Args a, int32_t *__
         const double sgn = a.qc[j].sgn;
         long long code;
         if (sgn > 0)
-            code = fused_body<1, SEG_COLS, K>(a, sh, sj, Pl, Ql, false, thr_out, obj, status);
+            code = fused_body<1, SEG_COLS, K, false>(a, sh, sj, Pl, Ql, false, thr_out, obj, status);
         else if (sgn < 0)
-            code = fused_body<-1, SEG_COLS, K>(a, sh, sj, Pl, Ql, false, thr_out, obj, status);
+            code = fused_body<-1, SEG_COLS, K, false>(a, sh, sj, Pl, Ql, false, thr_out, obj, status);
         else
-            code = fused_body<0, SEG_COLS, K>(a, sh, sj, Pl, Ql, false, thr_out, obj, status);
+            code = fused_body<0, SEG_COLS, K, false>(a, sh, sj, Pl, Ql, false, thr_out, obj, status);
         if (threadIdx.x == 0 && j < TS_MAX_LABEL_SETS) {
             for (int i = K - 1; i >= 0; --i) {
                 tsh[j][i] = code < 0 ? -1 : (int)(code & 4095);

@@ -25,7 +25,8 @@ def _hists(L, n, sparse, seed):
     h = rng.integers(10**8 // L, 10**9 // L, (n, L))
     if sparse:
         h[rng.random((n, L)) < 0.4] = 0
-    h[0, :2] = h[-1, -1] = 5000
+    if L > 8:
+        h[0, :2] = h[-1, -1] = 5000
     h[np.arange(n), rng.integers(0, L, n)] = 20
     return h.astype(np.uint32)
 
@@ -77,3 +78,35 @@ def test_no_slower_than_the_plain_form():
     full = _us(lambda: api.threshold_search(P, Qs, 3, Q))
     plain = _us(lambda: api.threshold_search(P, Qs, 3, Q, api.SEARCH_PLAIN))
     assert full <= plain, (full, plain)
+
+
+@pytest.mark.parametrize("block", [256, 512, 1024])
+@pytest.mark.parametrize("L", [3, 5, 66, 130, 257, 400, 1000])
+def test_every_tuple_in_one_workgroup(L, block):
+    P, Qs = _prefix(_hists(L, 3, L > 8, L + block))
+    want = api.threshold_search(P, Qs, 2, Q, api.SEARCH_PLAIN)
+    got = api.threshold_search(P, Qs, 2, Q, tune={"search_path": 1, "search_block": block})
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("tune", [{"segment_parts": 1}, {"search_path": 1}, {"search_path": 2}])
+def test_every_tuple_in_segment(tune):
+    v = torch.randint(0, 200, (1, 8, 512, 512), device="cuda").to(torch.int16)
+    v[0, 0, 0, :3] = 230  # three voxels among two million: no finite bound at q = 3
+    batch, binn = api.Batch.whole(v), api.binning(0, 255, 256)
+    hist, got, _ = api.segment(batch, binn, 2, 3.0, tune=tune)
+    P, Qs = api.prefix(hist, 3.0)
+    want = api.threshold_search(P, Qs, 2, 3.0, api.SEARCH_PLAIN)
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+
+
+def test_one_workgroup_time():
+    # 32640 tuples in one workgroup: the finite call takes about a tenth of the
+    # logarithms; six times its time is twice what the FP64 issue rate asks for
+    P, Qs = _prefix(_hists(256, 1, False, 3))
+    P1, Q1 = api.prefix(to_dev(_hists(256, 1, False, 3).view(np.int32)), 0.8)
+    full = _us(lambda: api.threshold_search(P, Qs, 2, Q, tune={"search_path": 1}), 15)
+    finite = _us(lambda: api.threshold_search(P1, Q1, 2, 0.8, tune={"search_path": 1}), 15)
+    assert full <= 6 * finite, (full, finite)
