@@ -379,7 +379,7 @@ ts_status ts_threshold_search_noalloc(const double *P, const double *Q, int32_t 
         return st;
     if (nseg == 0)
         return TS_OK;
-    const size_t need = search_need_bytes(nseg * nq, nbins, k, mode, t);
+    const size_t need = search_need_bytes(nseg, nbins, k, nq, q, mode, t);
     if (need > TS_NOALLOC_SCRATCH_BYTES)
         return fail(TS_ERR_WORKSPACE, "ts_threshold_search_noalloc: these sizes need " + std::to_string(need) +
                                           " bytes of scratch, more than the fixed " +

@@ -2593,9 +2593,9 @@ static void launch_seg_km(dim3 g, dim3 b, size_t lds, hipStream_t st, const SegA
     hipLaunchKernelGGL((k_segment<K, MAP>), g, b, lds, st, sa, a, thr, obj, status);
 }
 
-static ts_status launch_scan_search(const uint32_t *hist, double *P, double *Q, int nseg, int L, int k, int nq,
-                                    const double *q, int mode, void *ws, int32_t *thr, double *obj, int32_t *status,
-                                    const Tune &t, hipStream_t st);
+static ts_status launch_scan_search(const uint32_t *hist, double voxels, double *P, double *Q, int nseg, int L, int k,
+                                    int nq, const double *q, int mode, void *ws, int32_t *thr, double *obj,
+                                    int32_t *status, const Tune &t, hipStream_t st);
 
 ts_status launch_segment(const ts_batch &b, const BinMap &bm, int k, int nq, const double *q, int mode,
                          uint32_t *hist, int32_t *thr, double *obj, int32_t *status, const LabelSets *sets, void *ws,
@@ -2612,7 +2612,8 @@ ts_status launch_segment(const ts_batch &b, const BinMap &bm, int k, int nq, con
         ts_status e;
         if ((e = launch_histogram(b, bm, hist, t, st)) != TS_OK)
             return e;
-        if ((e = launch_scan_search(hist, P, Q, nseg, L, k, nq, q, mode, sw, thr, obj, status, t, st)) != TS_OK)
+        if ((e = launch_scan_search(hist, (double)b.total / nseg, P, Q, nseg, L, k, nq, q, mode, sw, thr, obj, status,
+                                    t, st)) != TS_OK)
             return e;
         return sets ? launch_label(b, bm, *sets, nq, k, t, st) : TS_OK;
     }
@@ -3289,23 +3290,45 @@ QConst make_qconst(double q, int L)
     return c;
 }
 
+// Whether some problem of a call may have no finite error bound (then every
+// tuple is re-checked in FP64): problem_delta needs 2^-46 Q(L-1) / (smallest
+// step of Q) below about 1e-3.  For q > 1, Q(L-1) <= 1 and a bin of one voxel is
+// a step of N^-q, so N^q <= 2^36 voxels suffice; for q <= 1 the ratio is at most
+// about N, beyond the card's memory where it matters.  voxels: of a problem on
+// average, infinite where a call does not know them.
+static bool bound_may_be_infinite(int nq, const double *q, double voxels)
+{
+    for (int j = 0; j < nq; ++j)
+        if (q[j] > 1.0 && q[j] * log2(voxels) > 36.0)
+            return true;
+    return false;
+}
+
 // One workgroup per problem (k_fused, nothing in the workspace) when that
-// fills the chip or the problem is small, unless the tuning forces a path.  At
-// k = 2 the one workgroup takes 17 to 23 us up to 384 levels, for one problem
-// as for 250, against 19 to 45 over several launches; 24 to 28 at 512 levels,
-// against 20 for one problem, 27 for 16 and 41 for 82.
-static bool fused_path(const Plan &p, int nprob, const Tune &t)
+// fills the chip or the problem is small, unless the tuning forces a path.
+// k = 2, us in one workgroup against several launches, CT histograms and ones
+// with counts in every bin, finite bound: 256 levels, 1 problem 14 / 17.5, 19.5 /
+// 20; 320 levels 15 / 17, 24 / 22; 384 levels 18 / 17, 32 / 20; 512 levels, 16
+// problems 18 / 22, 36 / 33; 768 levels, 16 problems 26 / 27.5, 60 / 43, 32
+// problems 27 / 32, 61 / 49; 1024 levels, 32 problems 32 / 42, 74 / 73.  A
+// problem whose every tuple is re-checked takes one CU 79 us at 256 levels, 266
+// at 512 and 985 at 1000, the several launches 69 and 138 for 15 problems of 512
+// and 1000 levels: about 64 problems fill the chip either way.
+static bool fused_path(const Plan &p, int nprob, const Tune &t, bool may_be_infinite)
 {
     const bool fp32 = p.mode == TS_SEARCH_FP32_TIECHECK || p.mode == TS_SEARCH_FP32_ONLY;
     const bool can_fuse = fp32 && p.tiles <= FUSED_MAX_TILES && p.Lp <= FUSED_MAX_L &&
                           (p.k == 1 || (p.k == 2 && p.L <= FUSED_MAX_L2));
-    return can_fuse && (t.search_path == 1 || (t.search_path == 0 && (p.k == 1 || p.L <= 384 || nprob >= 16)));
+    const int small = may_be_infinite ? 256 : 320;                             // levels that always do
+    const int many = may_be_infinite ? 64 : p.L <= 512 ? 16 : 32; // problems that do beyond
+    return can_fuse &&
+           (t.search_path == 1 || (t.search_path == 0 && (p.k == 1 || p.L <= small || nprob >= many)));
 }
 
-size_t search_need_bytes(int nprob, int L, int k, int mode, const Tune &t)
+size_t search_need_bytes(int nseg, int L, int k, int nq, const double *q, int mode, const Tune &t)
 {
-    const Plan p = make_plan(nprob, L, k, mode, t.search_cols, t.search_rows);
-    return fused_path(p, nprob, t) ? 0 : p.bytes;
+    const Plan p = make_plan(nseg * nq, L, k, mode, t.search_cols, t.search_rows);
+    return fused_path(p, nseg * nq, t, bound_may_be_infinite(nq, q, INFINITY)) ? 0 : p.bytes;
 }
 
 static Args plan_args(const Plan &p, const double *P, const double *Q, int nseg, int nq, const double *q, void *ws)
@@ -3340,15 +3363,16 @@ static Args plan_args(const Plan &p, const double *P, const double *Q, int nseg,
     return a;
 }
 
-// ts_segment's prefix sums and search from the histograms: in the search's own
-// launches for the FP32 search, as separate calls for the other modes.
-static ts_status launch_scan_search(const uint32_t *hist, double *P, double *Q, int nseg, int L, int k, int nq,
-                                    const double *q, int mode, void *ws, int32_t *thr, double *obj, int32_t *status,
-                                    const Tune &t, hipStream_t st)
+// ts_segment's prefix sums and search from the histograms (of problems of so
+// many voxels on average): in the search's own launches for the FP32 search, as
+// separate calls for the other modes.
+static ts_status launch_scan_search(const uint32_t *hist, double voxels, double *P, double *Q, int nseg, int L, int k,
+                                    int nq, const double *q, int mode, void *ws, int32_t *thr, double *obj,
+                                    int32_t *status, const Tune &t, hipStream_t st)
 {
     if (mode == TS_SEARCH_FP32_TIECHECK || mode == TS_SEARCH_FP32_ONLY) {
         const Plan p = make_plan(nseg * nq, L, k, mode, t.search_cols, t.search_rows);
-        const bool fused = fused_path(p, nseg * nq, t);
+        const bool fused = fused_path(p, nseg * nq, t, bound_may_be_infinite(nq, q, voxels));
         if (!fused || scan_fused_lds(L, p.Lp, k, p.tiles) <= SEG_MAX_LDS) {
             launch_fp32_search(p, fused, plan_args(p, P, Q, nseg, nq, q, ws), t,
                                Fp32Launch{hist, P, Q, thr, obj, status, st});
@@ -3413,7 +3437,7 @@ ts_status launch_search(const double *P, const double *Q, int nseg, int L, int k
     }
 
     if (mode == TS_SEARCH_FP32_TIECHECK || mode == TS_SEARCH_FP32_ONLY) {
-        launch_fp32_search(p, fused_path(p, nprob, t), a, t,
+        launch_fp32_search(p, fused_path(p, nprob, t, bound_may_be_infinite(nq, q, INFINITY)), a, t,
                            Fp32Launch{nullptr, nullptr, nullptr, thr, obj, status, st});
         return check_launch("ts_threshold_search");
     }

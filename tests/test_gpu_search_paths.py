@@ -1,0 +1,66 @@
+"""The two ways a k = 2 search runs (one workgroup per problem, several
+launches) give the same bits, and the one chosen by the sizes is the faster of
+the two or close to it where they differ most: histograms with counts in every
+bin, with a finite error bound and with none."""
+import numpy as np
+import pytest
+
+from gpu_util import to_dev
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2012_10684_amd import api  # noqa: E402
+
+
+def _prefix(L, n, q, gaps, seed):
+    rng = np.random.default_rng(seed)
+    h = rng.integers(10**8 // L, 10**9 // L, (n, L))
+    if gaps:
+        h[rng.random((n, L)) < 0.4] = 0
+    h[np.arange(n), rng.integers(0, L, n)] = 20  # q = 2: no finite bound
+    return api.prefix(to_dev(h.astype(np.uint32).view(np.int32)), q)
+
+
+# around the lines: 256 / 257 and 320 / 321 levels, 16, 32 and 64 problems
+SIZES = [(256, 1), (257, 1), (257, 63), (257, 64), (320, 3), (321, 3), (321, 15), (321, 16), (512, 16), (513, 16),
+         (513, 31), (513, 32), (1024, 2)]
+
+
+@pytest.mark.parametrize("q", [0.8, 2.0])
+@pytest.mark.parametrize("L,n", SIZES)
+def test_paths_agree(L, n, q):
+    P, Q = _prefix(L, n, q, True, L + n)
+    res = [api.threshold_search(P, Q, 2, q, tune={"search_path": p}) for p in (0, 1, 2)]
+    res.append(api.threshold_search_noalloc(P, Q, 2, q))
+    for r in res[1:]:
+        for a, b in zip(res[0], r):
+            assert torch.equal(a, b)
+
+
+def _us(f, reps=9, calls=20):
+    f()
+    t = []
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(calls):
+            f()
+        b.record()
+        b.synchronize()
+        t.append(a.elapsed_time(b) * 1e3 / calls)
+    return sorted(t)[reps // 2]
+
+
+# where the two differ by a factor of 1.3 to 10
+@pytest.mark.parametrize("L,n,q", [(384, 1, 0.8), (768, 16, 0.8), (1024, 1, 0.8), (1024, 100, 0.8), (384, 1, 2.0),
+                                   (512, 16, 2.0), (1000, 32, 2.0)])
+def test_choice(L, n, q):
+    P, Q = _prefix(L, n, q, False, L + n)
+    ws = torch.empty(api.workspace_bytes(n, L, 2), dtype=torch.uint8, device="cuda")
+    out = api.threshold_search(P, Q, 2, q)
+    t = [_us(lambda: api.threshold_search(P, Q, 2, q, ws=ws, out=out, tune={"search_path": p})) for p in (0, 1, 2)]
+    assert t[0] <= 1.15 * min(t[1:]), t
