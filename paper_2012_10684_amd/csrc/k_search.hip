@@ -3176,11 +3176,18 @@ template <int COLS, int K>
 static void launch_fused(const Args &a, int block, const Fp32Launch &f)
 {
     const dim3 g((unsigned)a.nprob);
-    // 512 threads finish a problem sooner (82 problems of 200 levels, k = 2:
-    // 18 against 20 us), 256 more of them at once where several share a CU (900
-    // of 256 levels: 33 against 43 us)
-    if (!block)
-        block = a.nprob > 2 * device_cu_count() ? 256 : 512;
+    // 512 threads finish a problem sooner, 256 more of them at once where several
+    // share a CU, us with 256 against 512 threads, sparse histograms and ones with
+    // counts in every bin.  k = 2: 256 levels, 500 problems 21 / 20, 600 24 / 30;
+    // 384 levels, 600 problems 30 / 34, 66 / 63, 900 34 / 41, 75 / 77; 512 levels,
+    // 600 problems 35 / 37, 77 / 70, 900 41 / 45, 91 / 89; 768 levels, 900 problems
+    // 58 / 62, 166 / 158; 1024 levels 95 / 82, 250 / 204 (the LDS of a problem holds
+    // three per CU).  k = 1: 1024 levels, 600 problems 10 / 12; 4096 levels, 600
+    // problems 20 / 18, 900 22 / 27.
+    if (!block) {
+        const int per_cu = a.L <= (K == 2 ? 320 : 2048) ? 2 : 3;
+        block = a.nprob > per_cu * device_cu_count() && !(K == 2 && a.L > 512) ? 256 : 512;
+    }
     if (!f.hist) {
         hipLaunchKernelGGL((k_fused<COLS, K>), g, dim3((unsigned)block), fused_lds_bytes(a.Lp, K, a.tiles), f.st, a,
                            f.thr, f.obj, f.status);

@@ -64,3 +64,17 @@ def test_choice(L, n, q):
     out = api.threshold_search(P, Q, 2, q)
     t = [_us(lambda: api.threshold_search(P, Q, 2, q, ws=ws, out=out, tune={"search_path": p})) for p in (0, 1, 2)]
     assert t[0] <= 1.15 * min(t[1:]), t
+
+
+@pytest.mark.parametrize("L,n", [(256, 400), (256, 900), (512, 600), (768, 600), (1024, 900)])
+def test_block_choice(L, n):
+    P, Q = _prefix(L, n, 0.8, False, L + n)
+    ws = torch.empty(api.workspace_bytes(n, L, 2), dtype=torch.uint8, device="cuda")
+    out = tuple(x.clone() for x in api.threshold_search(P, Q, 2, 0.8))
+    res, t = [], []
+    for b in (0, 256, 512):
+        f = lambda: api.threshold_search(P, Q, 2, 0.8, ws=ws, out=out, tune={"search_path": 1, "search_block": b})  # noqa: E731
+        t.append(_us(f))
+        res.append([x.clone() for x in out])
+    assert all(torch.equal(a, b) for r in res[1:] for a, b in zip(res[0], r))
+    assert t[0] <= 1.08 * min(t[1:]), t
