@@ -38,6 +38,7 @@ constexpr int DP_THREADS = 256;
 constexpr int DP_FINAL_THREADS = 1024;
 constexpr int DP_FINAL_LDS = 16384; // first indices staged by k_dp_final
 constexpr int DP_BLOCK_BINS = 256; // levels of a problem that one workgroup takes whole
+constexpr int DP_ROWS = 4;         // rows of a workgroup of k_dp_rows
 constexpr int DP_STEP = DP_THREADS / 64; // candidates pushed per step, one per wavefront
 
 struct DPQ {
@@ -165,6 +166,110 @@ __global__ void __launch_bounds__(DP_THREADS) k_dp_level(DPArgs a, int m)
             }
         dp_v(a, m, s)[t] = best;
         dp_next(a, m, s)[t] = (uint16_t)bu; // not read where the best is -inf
+    }
+}
+
+// The same for DP_ROWS neighbouring t per workgroup, for calls whose workgroups
+// fill the chip several times over: bounded by the logarithms of the class terms,
+// of which FIRST forms two more per u for V_0 (half of all with one row per
+// workgroup), and by the workgroups' own loads and reductions.  The level before
+// leaves -inf for bins that repeat, so theirs are not compared again.  30 problems
+// of 1024 levels, counts in every bin: k = 2 161 us, 240 by k_dp_level; k = 6 637
+// against 754, and 319 against 367 on CT volumes.
+template <bool FIRST>
+__global__ void __launch_bounds__(DP_THREADS) k_dp_rows(DPArgs a, int m)
+{
+    constexpr int T = DP_ROWS;
+    __shared__ double red[T][DP_THREADS / 64];
+    __shared__ int redu[T][DP_THREADS / 64];
+    const int L = a.L, nt = (L - 1 + T - 1) / T;
+    const int s = blockIdx.x / nt, t0 = blockIdx.x % nt * T;
+    const double q = a.qs.q[s / a.nseg];
+    const double *P = a.P + (int64_t)(s % a.nseg) * L, *Q = a.Q + (int64_t)s * L;
+    const double *Vp = dp_v(a, m - 1, s); // not read by FIRST
+    double *V = dp_v(a, m, s);
+    double pt[T], qt[T];
+    bool row[T], some = false; // rows that can hold a threshold
+#pragma unroll
+    for (int j = 0; j < T; ++j) {
+        const int t = min(t0 + j, L - 2);
+        pt[j] = P[t];
+        qt[j] = Q[t];
+        row[j] = t0 + j <= L - 2 && !dp_repeats(P, Q, t);
+        some = some || row[j];
+    }
+    const double PL = P[L - 1], QL = Q[L - 1];
+    int u = t0 + 1 + threadIdx.x; // u - 1 >= 0; past the row's end its last bin is read and not used
+    auto at = [&](int i) { return min(i, L - 1); };
+    double pu = P[at(u)], qu = Q[at(u)];
+    double pb = FIRST ? P[at(u) - 1] : 0.0, qb = FIRST ? Q[at(u) - 1] : 0.0, vu = FIRST ? 0.0 : Vp[at(u)];
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int j = 0; j < T; ++j)
+            if (t0 + j <= L - 2 && !row[j])
+                V[t0 + j] = -INFINITY;
+    }
+    if (!some)
+        return;
+    double sgn, hmax;
+    dp_consts(q, L, sgn, hmax);
+    double best[T];
+    int bu[T];
+#pragma unroll
+    for (int j = 0; j < T; ++j) {
+        best[j] = -INFINITY;
+        bu[j] = 0x7fffffff;
+    }
+    while (__any(u <= L - 2)) {
+        const bool use = u <= L - 2 && (FIRST ? !(pu == pb && qu == qb) : vu > -INFINITY);
+        const int cu = u;
+        const double cp = pu, cq = qu, cv = vu;
+        u += blockDim.x;
+        pu = P[at(u)], qu = Q[at(u)];
+        if (FIRST)
+            pb = P[at(u) - 1], qb = Q[at(u) - 1];
+        else
+            vu = Vp[at(u)];
+        if (use) {
+            const double v = FIRST ? dp_h(PL - cp, QL - cq, q, sgn, hmax) : cv;
+#pragma unroll
+            for (int j = 0; j < T; ++j) {
+                if (row[j]) {
+                    const double x = dp_h(cp - pt[j], cq - qt[j], q, sgn, hmax) + v;
+                    if (x > best[j] && (j == 0 || cu > t0 + j)) {
+                        best[j] = x;
+                        bu[j] = cu;
+                    }
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < T; ++j) {
+        const double wbest = wave_max_d(best[j]);
+        int wu = best[j] == wbest ? bu[j] : 0x7fffffff;
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1)
+            wu = min(wu, __shfl_xor(wu, o, 64));
+        if ((threadIdx.x & 63) == 0) {
+            red[j][threadIdx.x >> 6] = wbest;
+            redu[j][threadIdx.x >> 6] = wu;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < T) {
+        const int j = threadIdx.x, t = t0 + j;
+        double b = red[j][0];
+        int ub = redu[j][0];
+        for (int w = 1; w < (int)(blockDim.x >> 6); ++w)
+            if (red[j][w] > b || (red[j][w] == b && redu[j][w] < ub)) {
+                b = red[j][w];
+                ub = redu[j][w];
+            }
+        if (t <= L - 2) { // a repeating bin's is -inf (again)
+            V[t] = b;
+            dp_next(a, m, s)[t] = (uint16_t)ub; // not read where the best is -inf
+        }
     }
 }
 
@@ -470,11 +575,18 @@ ts_status launch_dp(const double *P, const double *Q, int nseg, int L, int k, in
             hipLaunchKernelGGL(k_dp_block<16>, g, blk, 0, st, a, thr, obj, status);
         return check_launch("ts_threshold_search_dp");
     }
-    const dim3 g((unsigned)((int64_t)a.nprob * (L - 1)));
-    if (k > 1)
-        hipLaunchKernelGGL(k_dp_level<true>, g, dim3(DP_THREADS), 0, st, a, 1);
-    for (int m = 2; m < k; ++m)
-        hipLaunchKernelGGL(k_dp_level<false>, g, dim3(DP_THREADS), 0, st, a, m);
+    // four rows per workgroup where that leaves 1792 or more of them, seven per
+    // CU: 30 problems of 300 levels, k = 6, 125 us against 140 (CT 78 against 85),
+    // 12 of 512 levels 90 against 97, but 102 against 83 on CT volumes
+    if ((int64_t)a.nprob * (L - 1) >= 7168) {
+        const dim3 g((unsigned)((int64_t)a.nprob * ((L - 1 + DP_ROWS - 1) / DP_ROWS)));
+        for (int m = 1; m < k; ++m)
+            hipLaunchKernelGGL(m == 1 ? k_dp_rows<true> : k_dp_rows<false>, g, dim3(DP_THREADS), 0, st, a, m);
+    } else {
+        const dim3 g((unsigned)((int64_t)a.nprob * (L - 1)));
+        for (int m = 1; m < k; ++m)
+            hipLaunchKernelGGL(m == 1 ? k_dp_level<true> : k_dp_level<false>, g, dim3(DP_THREADS), 0, st, a, m);
+    }
     hipLaunchKernelGGL(k_dp_final, dim3((unsigned)a.nprob), dim3(DP_FINAL_THREADS), 0, st, a, thr, obj, status);
     return check_launch("ts_threshold_search_dp");
 }
