@@ -38,8 +38,8 @@ constexpr int DP_THREADS = 256;
 constexpr int DP_FINAL_THREADS = 1024;
 constexpr int DP_FINAL_LDS = 16384; // first indices staged by k_dp_final
 constexpr int DP_BLOCK_BINS = 256; // levels of a problem that one workgroup takes whole
+constexpr int DP_BLOCK_WAVES = 8;  // of such a workgroup, at most
 constexpr int DP_ROWS = 4;         // rows of a workgroup of k_dp_rows
-constexpr int DP_STEP = DP_THREADS / 64; // candidates pushed per step, one per wavefront
 
 struct DPQ {
     double q[TS_MAX_Q];
@@ -275,8 +275,8 @@ __global__ void __launch_bounds__(DP_THREADS) k_dp_rows(DPArgs a, int m)
 
 // LDS of dp_tuple: two stages' exchange, by stage parity (one barrier each).
 struct DPTupleLds {
-    double d[2][4][DP_THREADS / 64];
-    int c[2][DP_THREADS / 64];
+    double d[2][4][DP_BLOCK_WAVES];
+    int c[2][DP_BLOCK_WAVES];
 };
 
 // Result of a problem whose maximum is M (-inf: no tuple), its thresholds
@@ -429,24 +429,26 @@ __global__ void __launch_bounds__(DP_FINAL_THREADS) k_dp_final(DPArgs a, int32_t
 // are pushed to those before them from the last to the first,
 // V_m(t) = max(V_m(t), g(t+1 .. u) + V_{m-1}(u)),
 // so that a class term is formed once for all levels.  The terms do not
-// depend on V: four candidates u at a time, wavefront w forms those of the
-// w-th for every t into an LDS tile, one step ahead of its use.  A step:
-//   apply the four u of the step before (V from LDS) to the wavefronts below
-//   them; the wavefront owning this step's four pushes them one by one, V(u)
+// depend on V: NW candidates u at a time, wavefront w forms those of the w-th
+// for every t into an LDS tile, one step ahead of its use.  A step:
+//   apply the NW u of the step before (V from LDS) to the wavefronts below
+//   them; the wavefront owning this step's NW pushes them one by one, V(u)
 //   read from its lane, and stores their V; the next step's tile; one
 //   barrier (three tiles in turn).
 // Bounded by the logarithms (about 95 FP64 instructions each, a dependent
-// chain): 600 problems of 256 levels, about 130 candidates, k = 4: 92 us
-// (three level launches and the tuple's took 733); one problem 46 us.  With
-// the terms formed by each candidate's own wavefront, where the wavefronts
-// wait for each other in turn, 115 and 102 us.
-template <int KM>
-__global__ void __launch_bounds__(DP_THREADS) k_dp_block(DPArgs a, int32_t *__restrict__ thr,
-                                                         double *__restrict__ obj, int32_t *__restrict__ status)
+// chain): 600 problems of 256 levels, about 130 candidates, k = 4: 88 us
+// (three level launches and the tuple's took 733); one problem 36 us with eight
+// wavefronts, 46 with four.  With the terms formed by each candidate's own
+// wavefront, where the wavefronts wait for each other in turn, 115 and 102 us.
+template <int KM, int NW>
+__global__ void __launch_bounds__(64 * NW) k_dp_block(DPArgs a, int32_t *__restrict__ thr,
+                                                      double *__restrict__ obj, int32_t *__restrict__ status)
 {
+    constexpr int DP_STEP = NW; // candidates pushed per step, one per wavefront
     __shared__ double sP[DP_BLOCK_BINS], sQ[DP_BLOCK_BINS]; // prefix sums of the candidates
     __shared__ double sV[KM][DP_BLOCK_BINS];
-    __shared__ double sg[3][DP_STEP][DP_BLOCK_BINS];
+    extern __shared__ double sgdyn[]; // dp_block_lds
+    double(*sg)[DP_STEP][DP_BLOCK_BINS] = reinterpret_cast<double(*)[DP_STEP][DP_BLOCK_BINS]>(sgdyn);
     __shared__ int sbin[DP_BLOCK_BINS];
     __shared__ int wcount[DP_STEP];
     __shared__ DPTupleLds sh;
@@ -560,19 +562,37 @@ ts_status launch_dp(const double *P, const double *Q, int nseg, int L, int k, in
         a.qs.q[j] = q[j < nq ? j : 0];
     a.V = (double *)ws;
     // One workgroup per problem takes as long for one problem as for the chip
-    // full of them (a chain over the candidates: k = 4, 16 us at 64 levels, 25
-    // at 128, 48 at 256, on CT slices); the level kernels take 5 us a level
-    // and more with every problem (k = 4: 18-19 us for one problem, 26 for 12
-    // at 128 levels, 46 for 24 at 256).  The two meet near this line for k = 2
-    // .. 8; more levels than threads have only the level kernels.
-    if (L <= DP_BLOCK_BINS && 5 * (int64_t)a.nprob * (k - 1) >= 2 * (L - 64)) {
-        const dim3 g((unsigned)a.nprob), blk(DP_THREADS);
-        if (k <= 4)
-            hipLaunchKernelGGL(k_dp_block<4>, g, blk, 0, st, a, thr, obj, status);
-        else if (k <= 8)
-            hipLaunchKernelGGL(k_dp_block<8>, g, blk, 0, st, a, thr, obj, status);
-        else
-            hipLaunchKernelGGL(k_dp_block<16>, g, blk, 0, st, a, thr, obj, status);
+    // full of them (a chain over the candidates); a level takes about 4.5 us and
+    // more with every problem.  The lines below are fitted to both, measured over
+    // 8 to 256 levels, 1 to 300 problems and k = 2 .. 16, between histograms with
+    // counts in every bin and CT slices with counts in half of them, in us (one
+    // workgroup / levels): 64 levels, 1 problem, k = 2 16 / 10 and 12 / 10, k = 4
+    // 18 / 22 and 14 / 18; 128 levels, 24 problems, k = 4 35 / 37 and 20 / 32; 256
+    // levels, 24 problems, k = 4 83 / 64 and 37 / 45, 60 problems 84 / 104 and 37 /
+    // 83, k = 2 82 / 43 and 35 / 34.  Eight wavefronts per problem while every
+    // problem has a CU of its own (256 levels, k = 4, 60 problems 111 -> 83 us),
+    // four beyond (900 problems of 128 levels with eight 56 us, 50 with four),
+    // below 32 levels and past 8 thresholds, where the chain itself bounds it.
+    const double level = 6.0 + (k - 1) * (4.5 + 0.0018 * a.nprob * L);
+    const double block = L * (k <= 4 ? 0.22 : k <= 8 ? 0.32 : 0.46);
+    if (L <= DP_BLOCK_BINS && k > 1 && level >= block) {
+        const bool eight = a.nprob <= device_cu_count() && L >= 32;
+#define TS_DP(KM, NW)                                                                                               \
+    const size_t lds = sizeof(double) * 3 * NW * DP_BLOCK_BINS;                                                   \
+    allow_dynamic_lds((const void *)k_dp_block<KM, NW>, lds);                                                     \
+    hipLaunchKernelGGL((k_dp_block<KM, NW>), dim3((unsigned)a.nprob), dim3(64 * NW), lds, st, a, thr, obj, status)
+        if (k <= 4 && eight) {
+            TS_DP(4, 8);
+        } else if (k <= 4) {
+            TS_DP(4, 4);
+        } else if (k <= 8 && eight) {
+            TS_DP(8, 8);
+        } else if (k <= 8) {
+            TS_DP(8, 4);
+        } else {
+            TS_DP(16, 4);
+        }
+#undef TS_DP
         return check_launch("ts_threshold_search_dp");
     }
     // four rows per workgroup where that leaves 1792 or more of them, seven per
