@@ -42,6 +42,9 @@ constexpr int H2_THREADS = 1024;
 constexpr int H2_MAX_W = 4096;    // widest row
 constexpr int H2_MAX_L = 256;     // 2D histograms up to 256 x 256
 constexpr int H2_MIN_ROWS = 16;   // rows a workgroup takes at least
+constexpr int H2_MIN_PIX = 4096;  // pixels of an image that is not split
+constexpr int H2_SMALL = 16384;   // pixels of a small image
+constexpr size_t H2_LDS = 160 * 1024;
 constexpr int S2_CPL = 4;         // columns per lane (L <= 256)
 constexpr int S2_TAB = 1024;      // p^q (or p ln p) of counts below this from an LDS table
 constexpr int S2_RING = 2;        // rows of counts in flight ahead of the row being summed
@@ -88,19 +91,21 @@ __host__ __device__ inline int hist2d_words(int L) { return (L + 1) / 2 * L; }
 // histogram, and one band of an image per workgroup left the last round of
 // workgroups short.  A row loop that copied its loaded registers at the end
 // waited there for the load: 99 us.
-template <int KIND, bool RAGGED>
+template <int KIND, bool RAGGED, int REPS>
 __global__ void __launch_bounds__(H2_THREADS) k_hist2d(const int16_t *const *__restrict__ vox, int nseg, int whole,
                                                        int parts, int H, int W, Hist2dShape sh, BinMap bm, uint32_t mul24,
                                                        uint32_t *__restrict__ hist)
 {
-    // [words of the plane | two corner sums | the sweep's per-wavefront maxima]
+    // [REPS copies of the plane's words | two corner sums | the sweep's per-wavefront maxima]
     extern __shared__ uint32_t sm[];
     const int L = bm.L, nw2 = hist2d_words(L);
     uint32_t *plane = sm;
     const int nw4 = (nw2 + 3) & ~3; // the words past the plane stay 0
     uint4 *plane4 = reinterpret_cast<uint4 *>(sm);
-    uint32_t *corner = plane + nw4, *wmax = corner + 2;
+    const int nall = nw4 * REPS;
+    uint32_t *corner = plane + nall, *wmax = corner + 2;
     const int lane = threadIdx.x & 63;
+    uint32_t *mine = plane + (lane & (REPS - 1)) * nw4; // the copy this lane counts into
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     // this lane's row group: chunk of columns and run of rows
     const int grp = (wv << (6 - sh.gsh)) + (lane >> sh.gsh);
@@ -116,16 +121,16 @@ __global__ void __launch_bounds__(H2_THREADS) k_hist2d(const int16_t *const *__r
     const u16x2 half2 = {(unsigned short)((L + 1) / 2), (unsigned short)((L + 1) / 2)};
     const uint32_t fmul = (uint32_t)L << 15, top = 9u * (uint32_t)(L - 1) * 0x10001u;
 
-    for (int i = threadIdx.x; i < nw4 / 4; i += blockDim.x)
+    for (int i = threadIdx.x; i < nall / 4; i += blockDim.x)
         plane4[i] = make_uint4(0u, 0u, 0u, 0u);
-    if (threadIdx.x < 2)
+    if (threadIdx.x < 2 + H2_THREADS / 64) // and the maxima, of which a small workgroup writes a part
         corner[threadIdx.x] = 0u;
     __syncthreads();
 
     // the largest cell of the plane, for the whole workgroup
     auto plane_max = [&]() {
         u16x2 m = {0, 0};
-        for (int i = threadIdx.x; i < nw4 / 4; i += blockDim.x) {
+        for (int i = threadIdx.x; i < nall / 4; i += blockDim.x) {
             const uint4 w4 = plane4[i];
             m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w4.x));
             m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w4.y));
@@ -255,9 +260,9 @@ __global__ void __launch_bounds__(H2_THREADS) k_hist2d(const int16_t *const *__r
                         const uint32_t c1 = __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, t[j]), (u16x2){0, 3641},
                                                                    __umul24(f >> 16, fmul), false);
                         if (!RAGGED || 2 * j < nv)
-                            atomicAdd(plane + (c0 >> 15), 1u << (up & 0xffffu));
+                            atomicAdd(mine + (c0 >> 15), 1u << (up & 0xffffu));
                         if (!RAGGED || 2 * j + 1 < nv)
-                            atomicAdd(plane + (c1 >> 15), 1u << (up >> 16));
+                            atomicAdd(mine + (c1 >> 15), 1u << (up >> 16));
                     }
                 }
             }
@@ -300,15 +305,16 @@ __global__ void __launch_bounds__(H2_THREADS) k_hist2d(const int16_t *const *__r
                     store = false;
                     __syncthreads();
                 }
-                for (int i = threadIdx.x; i < nw2; i += blockDim.x) {
+                for (int i = threadIdx.x; i < nall; i += blockDim.x) {
                     const uint32_t w2 = plane[i];
+                    const int cell = REPS > 1 ? i % nw4 : i; // a copy's last words stay 0
                     uint32_t keep = w2;
                     if (w2 & 0x8000u) {
-                        atomicAdd(&hs[nw2 + i], w2 & 0xffffu);
+                        atomicAdd(&hs[nw2 + cell], w2 & 0xffffu);
                         keep &= 0xffff0000u;
                     }
                     if (w2 & 0x80000000u) {
-                        atomicAdd(&hs[i], w2 >> 16);
+                        atomicAdd(&hs[cell], w2 >> 16);
                         keep &= 0xffffu;
                     }
                     if (keep != w2)
@@ -337,6 +343,16 @@ __global__ void __launch_bounds__(H2_THREADS) k_hist2d(const int16_t *const *__r
                 plane4[i] = make_uint4(0u, 0u, 0u, 0u);
                 uint32_t c[4] = {w4.x >> 16, w4.y >> 16, w4.z >> 16, w4.w >> 16};
                 uint32_t d[4] = {w4.x & 0xffffu, w4.y & 0xffffu, w4.z & 0xffffu, w4.w & 0xffffu};
+                for (int r = 1; r < REPS; ++r) {
+                    const uint4 x4 = plane4[r * (nw4 / 4) + i];
+                    plane4[r * (nw4 / 4) + i] = make_uint4(0u, 0u, 0u, 0u);
+                    const uint32_t x[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        c[j] += x[j] >> 16;
+                        d[j] += x[j] & 0xffffu;
+                    }
+                }
                 c[0] += i == 0 ? corner[0] : 0u;
                 if ((last - nw2) >> 2 == i) {
 #pragma unroll
@@ -358,12 +374,17 @@ __global__ void __launch_bounds__(H2_THREADS) k_hist2d(const int16_t *const *__r
             }
         } else {
             for (int i = threadIdx.x; i < nw2; i += blockDim.x) {
-                const uint32_t w2 = plane[i];
-                plane[i] = 0u;
-                if (w2 >> 16)
-                    atomicAdd(&hs[i], w2 >> 16);
-                if (w2 & 0xffffu) // a half past the last cell counts nothing
-                    atomicAdd(&hs[nw2 + i], w2 & 0xffffu);
+                uint32_t hi = 0u, lo = 0u;
+                for (int r = 0; r < REPS; ++r) {
+                    const uint32_t w2 = plane[r * nw4 + i];
+                    plane[r * nw4 + i] = 0u;
+                    hi += w2 >> 16;
+                    lo += w2 & 0xffffu;
+                }
+                if (hi)
+                    atomicAdd(&hs[i], hi);
+                if (lo) // a half past the last cell counts nothing
+                    atomicAdd(&hs[nw2 + i], lo);
             }
             if (threadIdx.x < 2 && corner[threadIdx.x])
                 atomicAdd(&hs[threadIdx.x ? last : 0], corner[threadIdx.x]);
@@ -425,29 +446,53 @@ ts_status launch_hist2d(const ts_batch &b, int H, int W, const BinMap &bm, uint3
                            b.nseg, H, W, bm, hist);
         return check_launch("ts_histogram2d");
     }
-    // Row groups of 16, 32 or 64 lanes: those that leave the fewest lanes
-    // without columns, several chunks per row counted a sixteenth dearer (the
-    // columns beside a chunk are loaded apart).  552 columns are 69 lanes: 12
-    // rows of five 16-lane chunks at once keep 828 of 1024 lanes, 8 rows of two
-    // wavefronts 552.
-    Hist2dShape sh{6, 1, 1};
+    // Few levels and many pixels: copies of the plane by lane, since a wavefront's
+    // counts then meet in a handful of words (300 images of 512 x 512, 16 levels
+    // over the whole CT range: 158 us with one copy, 69 with eight).
+    const int reps = bm.L <= 32 && b.total >= (1 << 24) ? 8 : 1;
+    const size_t lds = ((size_t)((hist2d_words(bm.L) + 3) & ~3) * reps + 2 + H2_THREADS / 64) * 4;
     const int lanes = (W + 7) / 8;
-    for (int g = 6, best = 0; g >= 4; --g) {
-        const int nch = (lanes + (1 << g) - 1) >> g, nrun = (H2_THREADS >> g) / nch;
+    // Many small images whose planes share a CU: workgroups of 512 or 256 threads,
+    // as many as the LDS or 2048 threads hold, since clearing, counting and adding
+    // up follow each other within one.  64 levels, 2000 images of 16 x 16 38 -> 12
+    // us, 1000 of 64 x 64 22 -> 10; 600 of 128 x 96 at 128 levels, four planes per
+    // CU, are better off with one workgroup (28 against 33).
+    const int cus = device_cu_count(), fit = (int)std::min<size_t>(8, H2_LDS / lds);
+    const bool tiny = (int64_t)H * W <= H2_SMALL;
+    const int per = !tiny || b.nseg <= cus ? 1 : b.nseg <= 2 * cus ? (fit > 1 ? 2 : 1)
+                    : fit == 8 || (fit > 1 && (int64_t)H * W <= H2_MIN_PIX) ? 4 : 1; // of H2_THREADS
+    const int threads = lanes * per <= H2_THREADS ? H2_THREADS / per : H2_THREADS;
+    // Row groups of 16, 32 or 64 lanes, or of fewer where they hold a row: those
+    // that leave the fewest lanes without columns, several chunks per row counted
+    // a sixteenth dearer (the columns beside a chunk are loaded apart).  552
+    // columns are 69 lanes: 12 rows of five 16-lane chunks at once keep 828 of
+    // 1024 lanes, 8 rows of two wavefronts 552.  300 images of 4096 x 8 at 64
+    // levels: 93 us with groups of 16 lanes, 20 with one lane a row.
+    Hist2dShape sh{6, 1, 1};
+    for (int g = 6, best = 0; g >= 0; --g) {
+        const int nch = (lanes + (1 << g) - 1) >> g, nrun = (threads >> g) / nch;
         const int score = nrun * lanes * (nch > 1 ? 15 : 16);
-        if (score > best) {
+        if (score > best && (g >= 4 || nch == 1)) {
             best = score;
             sh = Hist2dShape{g, nch, nrun};
         }
     }
-    // Workgroups: one per CU, with at least H2_MIN_ROWS rows each (clearing
-    // and adding up the plane takes as long as counting about as many).
-    const int64_t rows = (int64_t)b.nseg * H;
-    const int nwg = (int)std::max<int64_t>(1, std::min<int64_t>(device_cu_count(), rows / H2_MIN_ROWS));
+    // Workgroups: one per CU (small images: as many as fit), each with an image
+    // of its own or at least H2_MIN_ROWS rows (clearing and adding up the plane
+    // takes as long as counting about as many; images of H2_MIN_PIX pixels are not
+    // split, which would need the clearing launch), and below one per CU equal
+    // parts of every image.  300 images of 1 x 4096 at 64 levels: 69 us by rows
+    // alone, 7 with a workgroup each.
+    const int64_t most = (int64_t)cus * (threads < H2_THREADS ? std::min(fit, 2048 / threads) : 1);
+    int64_t want = (int64_t)b.nseg * ((int64_t)H * W <= H2_MIN_PIX ? 1 : std::max(1, H / H2_MIN_ROWS));
+    if (want > most)
+        want = std::min<int64_t>(most, tiny && b.nseg >= cus ? b.nseg : std::max<int64_t>(b.nseg, (int64_t)b.nseg * H / H2_MIN_ROWS));
+    const int nwg = (int)want;
     // Whole images first, as many as fill every workgroup equally: those store
     // their histograms; the rest's rows are split evenly and added to cleared
-    // histograms.
-    const int whole = b.nseg / nwg * nwg;
+    // histograms.  A second round of small images takes less than the clearing
+    // launch and the split.
+    const int whole = tiny && b.nseg >= nwg && b.nseg < 2 * nwg ? b.nseg : b.nseg / nwg * nwg;
     // A workgroup whose rows cross into another image adds up two planes, 5 to
     // 10 us each: parts that keep to one image, unless they leave more than an
     // eighth of the workgroups idle.
@@ -458,19 +503,20 @@ ts_status launch_hist2d(const ts_batch &b, int H, int W, const BinMap &bm, uint3
         if (e != TS_OK)
             return e;
     }
-    const size_t lds = ((size_t)((hist2d_words(bm.L) + 3) & ~3) + 2 + H2_THREADS / 64) * 4;
     const uint32_t mul24 = binmap_mul24(bm);
     const int kind = levels_kind(bm);
-    const dim3 g((unsigned)nwg), blk(H2_THREADS);
-#define TS_H2(K, R)                                                                                                 \
-    allow_dynamic_lds((const void *)k_hist2d<K, R>, lds);                                                         \
-    hipLaunchKernelGGL((k_hist2d<K, R>), g, blk, lds, st, b.vox, b.nseg, whole, parts, H, W, sh, bm,   \
-                       mul24, hist)
+    const dim3 g((unsigned)nwg), blk(threads);
+#define TS_H2(K, R, C)                                                                                              \
+    allow_dynamic_lds((const void *)k_hist2d<K, R, C>, lds);                                                      \
+    hipLaunchKernelGGL((k_hist2d<K, R, C>), g, blk, lds, st, b.vox, b.nseg, whole, parts, H, W, sh, bm, mul24, hist)
+#define TS_H2K(R, C)                                                                                                \
+    if (kind == 0) { TS_H2(0, R, C); } else if (kind == 1) { TS_H2(1, R, C); } else { TS_H2(2, R, C); }
     if (W % 8 == 0) {
-        if (kind == 0) { TS_H2(0, false); } else if (kind == 1) { TS_H2(1, false); } else { TS_H2(2, false); }
+        if (reps == 1) { TS_H2K(false, 1) } else { TS_H2K(false, 8) }
     } else {
-        if (kind == 0) { TS_H2(0, true); } else if (kind == 1) { TS_H2(1, true); } else { TS_H2(2, true); }
+        if (reps == 1) { TS_H2K(true, 1) } else { TS_H2K(true, 8) }
     }
+#undef TS_H2K
 #undef TS_H2
     return check_launch("ts_histogram2d");
 }
