@@ -61,7 +61,7 @@ __device__ __forceinline__ int bin_of_t(int v, const BinMap &bm)
     if (MAP & 1)
         b = __umulhi(d * (uint32_t)bm.L, bm.mul) >> bm.shift;
     else
-        b = __umul24(d, bm.mul) >> bm.shift;
+        b = (uint32_t)__umul24(d, bm.mul) >> bm.shift; // the call returns int: products from 2^31 on are negative
     if ((MAP & 2) && v > bm.hi)
         b = (uint32_t)(bm.L - 1);
     return (int)b;
