@@ -177,18 +177,25 @@ ts_status make_binmap(const ts_binning &bin, BinMap *bm)
             ok = true;
         }
     }
-    for (uint32_t s = 0; s < 32 && !ok; ++s) {
+    bool wok = W == 1; // every offset is 0
+    m.wmul = m.wshift = 0;
+    for (uint32_t s = 0; s < 32 && !wok; ++s) {
         if ((uint64_t)(W - 1) * L >= (1ull << 32))
             break;
         uint64_t mul = ((1ull << (32 + s)) / W) + 1; // floor(2^(32+s) / W) + 1
         if (mul >= (1ull << 32))
             break;
         if (check_map(W, L, mul, s, true)) {
-            m.mul = (uint32_t)mul;
-            m.shift = s;
-            m.wide = 1;
-            ok = true;
+            m.wmul = (uint32_t)mul;
+            m.wshift = s;
+            wok = true;
         }
+    }
+    if (!ok && wok) {
+        m.mul = m.wmul;
+        m.shift = m.wshift;
+        m.wide = 1;
+        ok = true;
     }
     if (!ok)
         return fail(TS_ERR_UNSUPPORTED, "binning: no exact integer bin map found");
