@@ -21,13 +21,11 @@
 
 namespace ts {
 
-// Cut values of problem s for every set, computed by one lane per (set,
-// threshold) and broadcast through readlane (wavefront-uniform results).
-// (t+1) W <= 4095 * 65536 < 2^32, so the ceiling division is exact in uint32.
-// NS * KM <= 64 lanes.
+// Cut values of problem s for every set, one lane per (set, threshold): lane KM
+// u + j holds cut j of set u.  (t+1) W <= 4095 * 65536 < 2^32, so the ceiling
+// division is exact in uint32.  NS * KM <= 64 lanes.
 template <int NS, int KM>
-__device__ __forceinline__ void wave_cuts(const LabelSets &sets, int s, int k, const BinMap &bm,
-                                          Cuts<KM> (&cuts)[NS])
+__device__ __forceinline__ int wave_cuts(const LabelSets &sets, int s, int k, const BinMap &bm)
 {
     static_assert(NS * KM <= 64, "one lane per (set, threshold)");
     const int lane = threadIdx.x & 63;
@@ -48,50 +46,76 @@ __device__ __forceinline__ void wave_cuts(const LabelSets &sets, int s, int k, c
     // the whole row must be a strictly ascending tuple in [0, L-2]
     const bool ok = have && ((bal >> (u * KM)) & ((1ull << KM) - 1ull)) == (1ull << KM) - 1ull;
     const uint32_t W = (uint32_t)((int64_t)bm.hi - bm.lo + 1);
-    const int c = ok ? bm.lo + (int)(((uint32_t)(t + 1) * W + (uint32_t)bm.L - 1) / (uint32_t)bm.L) : 0x7fffffff;
+    return ok ? bm.lo + (int)(((uint32_t)(t + 1) * W + (uint32_t)bm.L - 1) / (uint32_t)bm.L) : 0x7fffffff;
+}
+
+// Set u's cuts from the lanes that hold them, uniform over the wavefront.
+template <int KM>
+__device__ __forceinline__ PCuts<KM> set_cuts(int c, int u)
+{
+    Cuts<KM> cuts;
 #pragma unroll
-    for (int u2 = 0; u2 < NS; ++u2) {
-#pragma unroll
-        for (int j2 = 0; j2 < KM; ++j2) // up to 64 values: vector registers beyond the 8-cut case
-            cuts[u2].c[j2] = KM <= 8 ? __builtin_amdgcn_readlane(c, KM * u2 + j2) : __shfl(c, KM * u2 + j2, 64);
-    }
+    for (int j = 0; j < KM; ++j)
+        cuts.c[j] = __builtin_amdgcn_readlane(c, KM * u + j);
+    return pack_cuts(cuts);
 }
 
 // The n <= blockDim * 8 * U voxels at src (one piece of one problem): 16-byte
 // loads of 8 voxels, every load of a thread in flight before the first is
 // used, 8-byte stores per set; the last n mod 8 voxel by voxel.  AL: src is
 // 16-byte and every dst 8-byte aligned (else any alignment).
+// Above eight cuts one set after the other, so that one set's cuts are held at a
+// time (all 48 of three sets spilled: 20000 problems of 1000 voxels, 751 -> 908
+// us, now 741).
 template <int NS, int U, int KM, bool AL>
 __device__ __forceinline__ void label_piece(const TS_GLOBAL int16_t *src, TS_GLOBAL uint8_t *const (&dst)[NS], int n,
-                                            const Cuts<KM> (&cuts)[NS])
+                                            int c)
 {
-    PCuts<KM> pc[NS];
+    constexpr bool ALL = KM <= 8; // every set's cuts at once
+    PCuts<KM> pc[ALL ? NS : 1];
+    if constexpr (ALL) {
 #pragma unroll
-    for (int u = 0; u < NS; ++u)
-        pc[u] = pack_cuts(cuts[u]);
+        for (int u = 0; u < NS; ++u)
+            pc[u] = set_cuts<KM>(c, u);
+    }
     const TS_GLOBAL v4i_any *vp = reinterpret_cast<const TS_GLOBAL v4i_any *>(src);
-    const int nvec = n >> 3;
+    const int nvec = n >> 3, tb = nvec << 3;
     v4i w[U];
 #pragma unroll
     for (int j = 0; j < U; ++j) {
         const int i = threadIdx.x + j * blockDim.x;
         w[j] = i < nvec ? (v4i)__builtin_nontemporal_load(vp + i) : v4i{0, 0, 0, 0};
     }
+    if constexpr (ALL) {
 #pragma unroll
-    for (int j = 0; j < U; ++j) {
-        const int i = threadIdx.x + j * blockDim.x;
-        if (i < nvec) {
+        for (int j = 0; j < U; ++j) {
+            const int i = threadIdx.x + j * blockDim.x;
+            if (i < nvec) {
+#pragma unroll
+                for (int u = 0; u < NS; ++u)
+                    store_lab8(dst[u], i, lab8(w[j], pc[u]), AL);
+            }
+        }
+        if ((int)threadIdx.x < n - tb) {
+            const int v = src[tb + threadIdx.x];
 #pragma unroll
             for (int u = 0; u < NS; ++u)
-                store_lab8(dst[u], i, lab8(w[j], pc[u]), AL);
+                dst[u][tb + threadIdx.x] = (uint8_t)lab1p(v, pc[u]);
         }
-    }
-    const int tb = nvec << 3;
-    if ((int)threadIdx.x < n - tb) {
-        const int v = src[tb + threadIdx.x];
+    } else {
+        const int v = (int)threadIdx.x < n - tb ? src[tb + threadIdx.x] : 0;
 #pragma unroll
-        for (int u = 0; u < NS; ++u)
-            dst[u][tb + threadIdx.x] = (uint8_t)lab1p(v, pc[u]);
+        for (int u = 0; u < NS; ++u) {
+            pc[0] = set_cuts<KM>(c, u);
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const int i = threadIdx.x + j * blockDim.x;
+                if (i < nvec)
+                    store_lab8(dst[u], i, lab8(w[j], pc[0]), AL);
+            }
+            if ((int)threadIdx.x < n - tb)
+                dst[u][tb + threadIdx.x] = (uint8_t)lab1p(v, pc[0]);
+        }
     }
 }
 
@@ -123,8 +147,7 @@ __global__ void __launch_bounds__(1024) k_label(const int16_t *const *__restrict
 #pragma unroll
     for (int u = 0; u < NS; ++u)
         os[u] = sets.out[u][s];
-    Cuts<KM> cuts[NS];
-    wave_cuts<NS, KM>(sets, s, k, bm, cuts);
+    int cuts = wave_cuts<NS, KM>(sets, s, k, bm);
     if (!(o0 <= t0 && t0 < o1)) {
         s = find_segment(offs, nseg, t0);
         while (s + 1 < nseg && offs[s + 1] <= t0) // skip empty segments
@@ -135,7 +158,7 @@ __global__ void __launch_bounds__(1024) k_label(const int16_t *const *__restrict
 #pragma unroll
         for (int u = 0; u < NS; ++u)
             os[u] = sets.out[u][s];
-        wave_cuts<NS, KM>(sets, s, k, bm, cuts);
+        cuts = wave_cuts<NS, KM>(sets, s, k, bm);
     }
     if (t1 <= o1) { // the whole tile in one problem
         const TS_GLOBAL int16_t *src = gp(vs) + (t0 - o0);
@@ -170,7 +193,7 @@ __global__ void __launch_bounds__(1024) k_label(const int16_t *const *__restrict
 #pragma unroll
             for (int u = 0; u < NS; ++u)
                 os[u] = sets.out[u][s];
-            wave_cuts<NS, KM>(sets, s, k, bm, cuts);
+            cuts = wave_cuts<NS, KM>(sets, s, k, bm);
         }
     }
     // many problems in the tile: voxel by voxel, segments walked forward
