@@ -189,14 +189,22 @@ def _device_tables(tables: Sequence[np.ndarray], device) -> List[torch.Tensor]:
 def _problems(tensors: Sequence[torch.Tensor], per: str):
     """Addresses and element counts of the problems of contiguous tensors: one
     per slice of the first dimension or per tensor."""
-    ptrs, sizes = [], []
-    for t in tensors:
-        n = t.shape[0] if per == "slice" else 1
-        m = t.numel() // n if n else 0
-        ptrs.append(t.data_ptr() + np.arange(n, dtype=np.int64) * (m * t.element_size()))
-        sizes.append(np.full(n, m, np.int64))
-    none = np.zeros(0, np.int64)
-    return np.concatenate([none, *ptrs]), np.concatenate([none, *sizes])
+    if per == "slice" and 1 <= len(tensors) <= 3:  # fewer array calls than the general form
+        ptrs, sizes = [], []
+        for t in tensors:
+            n = t.shape[0]
+            m = t.numel() // n if n else 0
+            ptrs.append(t.data_ptr() + np.arange(n, dtype=np.int64) * (m * t.element_size()))
+            sizes.append(np.full(n, m, np.int64))
+        return np.concatenate(ptrs), np.concatenate(sizes)
+    base = np.array([t.data_ptr() for t in tensors], np.int64)
+    if per == "volume":
+        return base, np.array([t.numel() for t in tensors], np.int64)
+    n = np.array([t.shape[0] for t in tensors], np.int64)
+    m = np.array([t.numel() for t in tensors], np.int64) // np.maximum(n, 1)
+    step = m * np.array([t.element_size() for t in tensors], np.int64)
+    at = np.arange(n.sum(), dtype=np.int64) - np.repeat(np.cumsum(n) - n, n)  # slice of its volume
+    return np.repeat(base, n) + at * np.repeat(step, n), np.repeat(m, n)
 
 
 class Batch:
@@ -550,10 +558,14 @@ def _batch_segment(volumes, bin, k, q, per, mode, method, open_radius, tune, str
     ptrs, sizes = _problems(src, per)
     tables = [ptrs, np.concatenate([np.zeros(1, np.int64), np.cumsum(sizes)])] + [_problems(lj, per)[0] for lj in labels]
     open_sizes = []
-    for v in vols if residues is not None else []:
-        p, m = _problems([v], "slice")
-        tables += [p, np.concatenate([np.zeros(1, np.int64), np.cumsum(m)])]
-        open_sizes.append(m)
+    if residues is not None:
+        p, m = _problems(vols, "slice")
+        at = 0
+        for v in vols:
+            n = v.shape[0]
+            tables += [p[at:at + n], np.arange(n + 1, dtype=np.int64) * (m[at] if n else 0)]
+            open_sizes.append(m[at:at + n])
+            at += n
     d = _device_tables(tables, dev)
     batch = Batch._from_tables(src, sizes, d[0], d[1])
     out_ptrs = d[2:2 + len(qs)]
