@@ -3312,22 +3312,28 @@ static bool bound_may_be_infinite(int nq, const double *q, double voxels)
 }
 
 // One workgroup per problem (k_fused, nothing in the workspace) when that
-// fills the chip or the problem is small, unless the tuning forces a path.
-// k = 2, us in one workgroup against several launches, CT histograms and ones
-// with counts in every bin, finite bound: 256 levels, 1 problem 14 / 17.5, 19.5 /
-// 20; 320 levels 15 / 17, 24 / 22; 384 levels 18 / 17, 32 / 20; 512 levels, 16
-// problems 18 / 22, 36 / 33; 768 levels, 16 problems 26 / 27.5, 60 / 43, 32
-// problems 27 / 32, 61 / 49; 1024 levels, 32 problems 32 / 42, 74 / 73.  A
-// problem whose every tuple is re-checked takes one CU 79 us at 256 levels, 266
+// fills the chip or the problem is small, unless the tuning forces a path.  The
+// lines are where histograms with counts in every bin, for which the one
+// workgroup is dearest, lose nothing by it; k = 2, us in one workgroup against
+// several launches, CT histograms and dense ones, finite bound.  From prefix sums:
+// 256 levels, 1 problem 14 / 17.5, 19.5 / 20; 320 levels 15 / 17, 24 / 22; 384
+// levels 18 / 17, 32 / 20, 16 problems 18 / 20, 33 / 28; 768 levels, 16 problems 26
+// / 27.5, 60 / 43, 32 problems 27 / 32, 61 / 49; 1024 levels, 16 problems 32 / 35,
+// 73 / 63.  In ts_segment (scan), whose one workgroup forms the prefix sums too:
+// 384 levels, 1 problem 28 / 30, 44 / 35, 8 problems 29 / 32, 45 / 38; 768 levels,
+// 24 problems 39 / 43, 72 / 57; 1024 levels, 16 problems 41 / 49, 70 / 74.
+// A problem whose every tuple is re-checked takes one CU 79 us at 256 levels, 266
 // at 512 and 985 at 1000, the several launches 69 and 138 for 15 problems of 512
 // and 1000 levels: about 64 problems fill the chip either way.
-static bool fused_path(const Plan &p, int nprob, const Tune &t, bool may_be_infinite)
+static bool fused_path(const Plan &p, int nprob, const Tune &t, bool may_be_infinite, bool scan)
 {
     const bool fp32 = p.mode == TS_SEARCH_FP32_TIECHECK || p.mode == TS_SEARCH_FP32_ONLY;
     const bool can_fuse = fp32 && p.tiles <= FUSED_MAX_TILES && p.Lp <= FUSED_MAX_L &&
                           (p.k == 1 || (p.k == 2 && p.L <= FUSED_MAX_L2));
-    const int small = may_be_infinite ? 256 : 320;                             // levels that always do
-    const int many = may_be_infinite ? 64 : p.L <= 512 ? 16 : 32; // problems that do beyond
+    const int small = may_be_infinite ? 256 : 320; // levels that always do
+    int many = 64;                                 // problems that do beyond
+    if (!may_be_infinite)
+        many = scan && p.L <= 384 ? 4 : p.L <= 512 || p.L > 896 ? 16 : scan ? 24 : 32;
     return can_fuse &&
            (t.search_path == 1 || (t.search_path == 0 && (p.k == 1 || p.L <= small || nprob >= many)));
 }
@@ -3335,7 +3341,7 @@ static bool fused_path(const Plan &p, int nprob, const Tune &t, bool may_be_infi
 size_t search_need_bytes(int nseg, int L, int k, int nq, const double *q, int mode, const Tune &t)
 {
     const Plan p = make_plan(nseg * nq, L, k, mode, t.search_cols, t.search_rows);
-    return fused_path(p, nseg * nq, t, bound_may_be_infinite(nq, q, INFINITY)) ? 0 : p.bytes;
+    return fused_path(p, nseg * nq, t, bound_may_be_infinite(nq, q, INFINITY), false) ? 0 : p.bytes;
 }
 
 static Args plan_args(const Plan &p, const double *P, const double *Q, int nseg, int nq, const double *q, void *ws)
@@ -3379,7 +3385,7 @@ static ts_status launch_scan_search(const uint32_t *hist, double voxels, double 
 {
     if (mode == TS_SEARCH_FP32_TIECHECK || mode == TS_SEARCH_FP32_ONLY) {
         const Plan p = make_plan(nseg * nq, L, k, mode, t.search_cols, t.search_rows);
-        const bool fused = fused_path(p, nseg * nq, t, bound_may_be_infinite(nq, q, voxels));
+        const bool fused = fused_path(p, nseg * nq, t, bound_may_be_infinite(nq, q, voxels), true);
         if (!fused || scan_fused_lds(L, p.Lp, k, p.tiles) <= SEG_MAX_LDS) {
             launch_fp32_search(p, fused, plan_args(p, P, Q, nseg, nq, q, ws), t,
                                Fp32Launch{hist, P, Q, thr, obj, status, st});
@@ -3444,7 +3450,7 @@ ts_status launch_search(const double *P, const double *Q, int nseg, int L, int k
     }
 
     if (mode == TS_SEARCH_FP32_TIECHECK || mode == TS_SEARCH_FP32_ONLY) {
-        launch_fp32_search(p, fused_path(p, nprob, t, bound_may_be_infinite(nq, q, INFINITY)), a, t,
+        launch_fp32_search(p, fused_path(p, nprob, t, bound_may_be_infinite(nq, q, INFINITY), false), a, t,
                            Fp32Launch{nullptr, nullptr, nullptr, thr, obj, status, st});
         return check_launch("ts_threshold_search");
     }

@@ -25,9 +25,9 @@ def _prefix(L, n, q, gaps, seed):
     return api.prefix(to_dev(h.astype(np.uint32).view(np.int32)), q)
 
 
-# around the lines: 256 / 257 and 320 / 321 levels, 16, 32 and 64 problems
+# around the lines: 256 / 257, 320 / 321, 512 / 513 and 896 / 897 levels, 16, 32 and 64 problems
 SIZES = [(256, 1), (257, 1), (257, 63), (257, 64), (320, 3), (321, 3), (321, 15), (321, 16), (512, 16), (513, 16),
-         (513, 31), (513, 32), (1024, 2)]
+         (513, 31), (513, 32), (896, 16), (897, 15), (897, 16), (1024, 2)]
 
 
 @pytest.mark.parametrize("q", [0.8, 2.0])
@@ -39,6 +39,16 @@ def test_paths_agree(L, n, q):
     for r in res[1:]:
         for a, b in zip(res[0], r):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("L,n", [(321, 3), (321, 4), (384, 4), (385, 15), (385, 16), (513, 23), (513, 24), (896, 16), (897, 15), (897, 16)])
+def test_segment_paths_agree(L, n):
+    v = torch.randint(0, 4 * L, (n, 3000), device="cuda").to(torch.int16)
+    batch, binn = api.Batch([x for x in v]), api.binning(0, 4 * L - 1, L)
+    res = [api.segment(batch, binn, 2, 0.8, tune={"search_path": p}) for p in (0, 1, 2)]
+    for h, o, lab in res[1:]:
+        assert torch.equal(h, res[0][0]) and torch.equal(torch.cat(lab[0]), torch.cat(res[0][2][0]))
+        assert all(torch.equal(a, b) for a, b in zip(o, res[0][1]))
 
 
 def _us(f, reps=9, calls=20):
