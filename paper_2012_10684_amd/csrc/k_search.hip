@@ -3184,9 +3184,14 @@ static void launch_fused(const Args &a, int block, const Fp32Launch &f)
     // 58 / 62, 166 / 158; 1024 levels 95 / 82, 250 / 204 (the LDS of a problem holds
     // three per CU).  k = 1: 1024 levels, 600 problems 10 / 12; 4096 levels, 600
     // problems 20 / 18, 900 22 / 27.
+    // With the prefix sums (f.hist) the LDS holds fewer problems per CU: k = 2, 300
+    // slices and two q, 384 levels 40 / 48, 76 / 79, 512 levels 47 / 53, 92 / 88;
+    // three q, 512 levels 52 / 63, 107 / 109, 768 levels 66 / 76, 182 / 178.
     if (!block) {
-        const int per_cu = a.L <= (K == 2 ? 320 : 2048) ? 2 : 3;
-        block = a.nprob > per_cu * device_cu_count() && !(K == 2 && a.L > 512) ? 256 : 512;
+        const int two = f.hist ? 384 : 320; // levels up to which two problems per CU suffice
+        const int per_cu = a.L <= (K == 2 ? two : 2048) ? 2 : 3;
+        const bool wide = K == 2 && a.L > 512 && !f.hist;
+        block = a.nprob > per_cu * device_cu_count() && !wide ? 256 : 512;
     }
     if (!f.hist) {
         hipLaunchKernelGGL((k_fused<COLS, K>), g, dim3((unsigned)block), fused_lds_bytes(a.Lp, K, a.tiles), f.st, a,
@@ -3386,7 +3391,13 @@ static ts_status launch_scan_search(const uint32_t *hist, double voxels, double 
     if (mode == TS_SEARCH_FP32_TIECHECK || mode == TS_SEARCH_FP32_ONLY) {
         const Plan p = make_plan(nseg * nq, L, k, mode, t.search_cols, t.search_rows);
         const bool fused = fused_path(p, nseg * nq, t, bound_may_be_infinite(nq, q, voxels), true);
-        if (!fused || scan_fused_lds(L, p.Lp, k, p.tiles) <= SEG_MAX_LDS) {
+        // From 1024 levels the scan takes 1024 threads per problem, one problem on a CU:
+        // with more problems than CUs the prefix sums have a launch of their own, us
+        // against one launch, 300 slices: k = 1, 1024 levels 28 / 35, with three q 39 /
+        // 61; 4096 levels 48 / 54, 71 / 98; k = 2, 1024 levels 55 / 66, with counts in
+        // every bin 124 / 131; up to 256 slices 42 / 37 and 86 / 70.
+        const bool waits = fused && prefix_threads(L) > 512 && nseg * nq > device_cu_count();
+        if (!waits && (!fused || scan_fused_lds(L, p.Lp, k, p.tiles) <= SEG_MAX_LDS)) {
             launch_fp32_search(p, fused, plan_args(p, P, Q, nseg, nq, q, ws), t,
                                Fp32Launch{hist, P, Q, thr, obj, status, st});
             return check_launch("ts_segment");

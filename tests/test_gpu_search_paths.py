@@ -51,6 +51,31 @@ def test_segment_paths_agree(L, n):
         assert all(torch.equal(a, b) for a, b in zip(o, res[0][1]))
 
 
+# from 1024 levels, on both sides of one problem per CU, the prefix sums and the
+# search are one launch or two; 300 slices of k = 1 and three q took 1.4 to 1.6
+# times the separate calls in one launch
+@pytest.mark.parametrize("q", [[0.8], [0.5, 1.0, 2.0]])
+@pytest.mark.parametrize("L,k,n", [(1024, 2, 0), (1024, 2, 1), (1024, 1, 0), (1024, 1, 1), (2500, 1, 1), (4096, 1, 44)])
+def test_wide_scan_agrees(L, k, n, q):
+    n += torch.cuda.get_device_properties(0).multi_processor_count
+    v = torch.randint(0, L, (n, 32, 32), device="cuda").to(torch.int16)
+    batch, binn = api.Batch.slices(v), api.binning(0, L - 1, L)
+    h, out, _ = api.segment(batch, binn, k, q, labels=False)
+    hist = api.histogram(batch, binn)
+    assert torch.equal(h, hist)
+    assert all(torch.equal(a, b) for a, b in zip(out, api.threshold_search(*api.prefix(hist, q), k, q)))
+    if n == 300 or (L == 1024 and k == 1 and len(q) == 3):
+        P, Q = api.prefix(hist, q)
+        ws = torch.empty(api.segment_workspace_bytes(n, L, k, len(q)), dtype=torch.uint8, device="cuda")
+
+        def separate():
+            api.histogram(batch, binn, out=hist)
+            api.prefix(hist, q, P=P, Q=Q)
+            api.threshold_search(P, Q, k, q, ws=ws, out=out)
+        one, three = _us(lambda: api.segment(batch, binn, k, q, labels=False, hist=hist, out=out, ws=ws)), _us(separate)
+        assert one <= 1.15 * three, (one, three)
+
+
 def _us(f, reps=9, calls=20):
     f()
     t = []
