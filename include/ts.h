@@ -130,7 +130,7 @@ typedef struct {
     int32_t search_path;     /* 1: one workgroup per problem (k <= 2, nbins <= 1024, or k = 1),
                                 2: one launch per search phase; 0: chosen from the sizes */
     int32_t search_block;    /* threads per workgroup on the one-workgroup path: 256, 512 or 1024
-                                (0: chosen from the number of problems) */
+                                (0: chosen from the levels and the number of problems) */
     int32_t segment_parts;   /* ts_segment: workgroups per problem, 1..64 (1: the whole path of a
                                 problem in one workgroup and one launch) */
     int32_t segment_block;   /* ts_segment: threads per workgroup: 256, 512 or 1024 (raised to what

@@ -5,8 +5,10 @@
 // {i > t, j > s} (quadrants 1 and 3) and the arg max over (t, s) of the
 // pseudo-additive objective.  Only t thresholds the image (ts_label, k = 1).
 //
-// k_hist2d: one workgroup per CU, an equal share of the images' rows each.  The
-// whole L x L plane is counted in LDS as 16-bit cells (two per word; 128 KiB
+// k_hist2d: one workgroup per CU; each counts whole images and stores their
+// planes, and the images left over are split into parts by rows, which add to
+// theirs.  Small images take smaller workgroups, several per CU, an image each.
+// The whole L x L plane is counted in LDS as 16-bit cells (two per word; 128 KiB
 // at L = 256).  A lane holds 8 neighbouring columns and walks down the rows:
 // gray levels, row sums of three and the sums of three rows stay in
 // registers as packed 16-bit pairs, the neighbours' edge columns come by lane

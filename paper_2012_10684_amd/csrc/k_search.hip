@@ -19,22 +19,27 @@
 //           in FP32 (log2 units), and a per-problem bound delta on the
 //           difference between any FP32 key and the FP64 value computed from
 //           the same prefix sums;
-//   pairs   (k = 3) rows A_t2(t1) = head(t1) + g(t1, t2) and
-//           R_t2(t3) = g(t2, t3) + tail(t3), stored in the workspace;
 //   phase 1 every tuple's FP32 key, one tile per wavefront: lanes hold the
 //           last threshold(s) in registers, the earlier threshold is a
-//           wavefront-uniform loop whose operands come through scalar loads;
+//           wavefront-uniform loop;
 //           wavefront max -> tile max, atomic max -> problem max M.
-//           k = 3 reuses the whole R row for every t1: one add and one max
-//           per tuple;
+//           k = 3: a workgroup per t2 and chunk of t3, the row A_t2(t1) =
+//           head(t1) + g(t1, t2) in LDS and R_t2(t3) = g(t2, t3) + tail(t3) in
+//           registers for every t1: one add and one max per tuple;
 //   phase 2 tiles whose max is >= M - 2 delta re-evaluate their tuples; every
 //           tuple with an FP32 key >= M - 2 delta is evaluated in FP64 and the
 //           best (FP64 value, then lexicographically first tuple) is kept.
 //           The FP64 arg max is always in that set, so the result is the FP64
-//           arg max;
-//   final   one workgroup per problem reduces the tile bests, writes the tuple,
-//           S = expm1(Lambda)/(1-q) and the status.
-// FP64 mode evaluates every key in FP64 directly (A/R rows in FP64 for k=3).
+//           arg max.  Where the bound is infinite every tuple is evaluated, by
+//           rows and columns that share their class terms (k_segment keeps the
+//           form of the finite bound);
+//   result  the tuple, S = expm1(Lambda)/(1-q) and the status, by the
+//           problem's one workgroup, or by the last of those that share its
+//           phase 2.
+// The phases run in one workgroup per problem or in a launch each (set-up,
+// phase 1, phase 2 with the result).
+// FP64 mode evaluates every key in FP64 directly (k = 3: rows A and R in FP64
+// stored in the workspace) and takes the best in a launch of its own.
 //
 // q = 1 is the Shannon limit (Kapur's objective): class entropies
 // S_j = ln w_j - E_j / w_j with E_j the class sum of p ln p (the prefix Q then

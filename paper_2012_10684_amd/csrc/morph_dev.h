@@ -236,8 +236,9 @@ __device__ __forceinline__ void mv_levels(uint32_t (&O)[MV_TY], uint32_t (&V)[MV
         mv_levels<MAXOP, R, HH + 1, NI, PS, S>(O, V, I, planes, c);
 }
 
-// Bounded by the vector operations (packed minima and byte aligns, about 30
-// wavefront instructions per row of 128 pixels at r = 10) and the LDS reads of
+// Bounded by the vector operations (at r = 10 69 wavefront instructions per row
+// of 128 pixels for the erosion and 80 for the dilation by the counters, of
+// which about 17 form the runs and 30 fold the offsets) and the LDS reads of
 // the offsets (26 words per column pair and row, 57 % of the time at 128 B per
 // clock): 300 slices of 512 x 512, r = 10, both passes 207 -> 193 us when the
 // runs were formed by doubling (17 instead of 20 operations per row), whole
