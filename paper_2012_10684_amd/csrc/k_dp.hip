@@ -570,13 +570,17 @@ ts_status launch_dp(const double *P, const double *Q, int nseg, int L, int k, in
     // 18 / 22 and 14 / 18; 128 levels, 24 problems, k = 4 35 / 37 and 20 / 32; 256
     // levels, 24 problems, k = 4 83 / 64 and 37 / 45, 60 problems 84 / 104 and 37 /
     // 83, k = 2 82 / 43 and 35 / 34.  Eight wavefronts per problem while every
-    // problem has a CU of its own (256 levels, k = 4, 60 problems 111 -> 83 us),
-    // four beyond (900 problems of 128 levels with eight 56 us, 50 with four),
-    // below 32 levels and past 8 thresholds, where the chain itself bounds it.
+    // problem has a CU of its own (256 levels, k = 4, 60 problems 111 -> 83 us) and
+    // while two share one where a step has enough terms (257 problems, k = 2, 256
+    // levels 160 -> 141 and, CT, 51 -> 47; 128 levels 58 -> 53 and 24 -> 24; k = 6, 256
+    // levels 188 -> 170 and 64 -> 62, but 128 levels 72 -> 69 and 31 -> 33), four
+    // beyond (900 problems of 128 levels with eight 56 us, 50 with four), below 32
+    // levels and past 8 thresholds, where the chain itself bounds it.
     const double level = 6.0 + (k - 1) * (4.5 + 0.0018 * a.nprob * L);
     const double block = L * (k <= 4 ? 0.22 : k <= 8 ? 0.32 : 0.46);
     if (L <= DP_BLOCK_BINS && k > 1 && level >= block) {
-        const bool eight = a.nprob <= device_cu_count() && L >= 32;
+        const int per_cu = L >= (k <= 4 ? 128 : 192) ? 2 : 1;
+        const bool eight = a.nprob <= per_cu * device_cu_count() && L >= 32;
 #define TS_DP(KM, NW)                                                                                               \
     const size_t lds = sizeof(double) * 3 * NW * DP_BLOCK_BINS;                                                   \
     allow_dynamic_lds((const void *)k_dp_block<KM, NW>, lds);                                                     \

@@ -62,6 +62,18 @@ def test_against_the_exhaustive_search(L, n, k):
     assert (obj - o2).abs().max().item() <= 8 * (k + 1) * 2.0**-53 * obj.abs().max().item()
 
 
+# eight wavefronts up to two problems per CU from 128 levels (k <= 4) or 192 (k <= 8)
+@pytest.mark.parametrize("L,k", [(127, 2), (128, 2), (128, 5), (191, 8), (192, 8), (256, 4)])
+def test_two_problems_per_cu(L, k):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    P, Q = api.prefix(to_dev(_hists(np.random.default_rng(L * k), L, 2 * cus + 1).view(np.int32)), 0.7)
+    want = api.threshold_search_dp(P, Q, k, 0.7)
+    for n in (cus, cus + 1, 2 * cus):
+        for a, b in zip(api.threshold_search_dp(P[:n].contiguous(), Q[:n].contiguous(), k, 0.7), want):
+            rows = b.view(2 * cus + 1, -1)[:n]  # as bytes: the objective of an empty problem is NaN
+            assert a.cpu().numpy().tobytes() == rows.cpu().numpy().tobytes(), n
+
+
 def _us(P, Q, k, reps=9, calls=50):
     n, L = P.shape
     ws = torch.empty(api.workspace_dp_bytes(n, L, k), dtype=torch.uint8, device="cuda")
@@ -83,7 +95,7 @@ def _dense(L, n):
     return api.prefix(to_dev(h.astype(np.uint32).view(np.int32)), 0.7)
 
 
-@pytest.mark.parametrize("L,n,k", [(64, 100, 1), (64, 1, 2), (100, 24, 2), (256, 12, 8)])
+@pytest.mark.parametrize("L,n,k", [(64, 100, 1), (64, 1, 2), (100, 24, 2), (256, 12, 8), (256, 257, 2)])
 def test_choice(L, n, k):
     P, Q = _dense(L, n)
     # the same problems where only the level form runs, which must form the same terms
