@@ -3191,9 +3191,10 @@ static void launch_fused(const Args &a, int block, const Fp32Launch &f)
     // problems 20 / 18, 900 22 / 27.
     // With the prefix sums (f.hist) the LDS holds fewer problems per CU: k = 2, 300
     // slices and two q, 384 levels 40 / 48, 76 / 79, 512 levels 47 / 53, 92 / 88;
-    // three q, 512 levels 52 / 63, 107 / 109, 768 levels 66 / 76, 182 / 178.
+    // 768 levels 59 / 63, 154 / 141; three q, 512 levels 52 / 63, 107 / 109, 768 levels
+    // 66 / 76, 182 / 178.
     if (!block) {
-        const int two = f.hist ? 384 : 320; // levels up to which two problems per CU suffice
+        const int two = f.hist ? 512 : 320; // levels up to which two problems per CU suffice
         const int per_cu = a.L <= (K == 2 ? two : 2048) ? 2 : 3;
         const bool wide = K == 2 && a.L > 512 && !f.hist;
         block = a.nprob > per_cu * device_cu_count() && !wide ? 256 : 512;
